@@ -34,6 +34,9 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 METRIC = "replica-gradient GB/s through detect+median (K=15,r=3,d=11.2M); % of HBM peak"
 KERNEL_SOURCES = ["paper_2108_02416_amd/csrc/aspis_kernels.hip",
+                  "paper_2108_02416_amd/csrc/aspis_device.h",
+                  "paper_2108_02416_amd/csrc/aspis_ws.h",
+                  "paper_2108_02416_amd/csrc/aspis_ws_r3.hip",
                   "paper_2108_02416_amd/csrc/aspis_internal.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_fused_K15_r3_d11.2M.json")
 

@@ -43,743 +43,11 @@
 #include <atomic>
 #include <cstdint>
 
-#include "aspis_internal.h"
+#include "aspis_ws.h"
 
 namespace aspis {
 
 namespace {
-
-// ---------------------------------------------------------------------------
-// helpers
-
-// Order-preserving map of a binary32 bit pattern to an unsigned key:
-// unsigned order of keys == IEEE-754 totalOrder of the floats.
-__device__ __forceinline__ uint32_t to_key(uint32_t b) {
-    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
-}
-__device__ __forceinline__ uint32_t from_key(uint32_t k) {
-    return (k & 0x80000000u) ? (k ^ 0x80000000u) : ~k;
-}
-
-// Reductions over groups of G consecutive lanes (G a power of two <= 64).
-// Offsets below 16 use DPP row permutations: after the two quad steps every
-// lane of a quad holds the quad's value, and the half-row / row mirrors pair
-// each lane with one lane of the other half.
-enum class Op { And, Or, Add, Max, Min };
-
-template <Op OP>
-__device__ __forceinline__ uint32_t combine(uint32_t a, uint32_t b) {
-    if constexpr (OP == Op::And) return a & b;
-    if constexpr (OP == Op::Or) return a | b;
-    if constexpr (OP == Op::Max) return a > b ? a : b;
-    if constexpr (OP == Op::Min) return a < b ? a : b;
-    return a + b;
-}
-
-// Two 16-bit unsigned lanes of a word at once (v_pk_min_u16, v_pk_max_u16,
-// v_pk_add_u16: integer lanes, no carry between them).
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
-                                                                  __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
-                                                                  __builtin_bit_cast(u16x2, b)));
-}
-__device__ __forceinline__ uint32_t pk_add_u16(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) + __builtin_bit_cast(u16x2, b));
-}
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-
-template <int G, Op OP>
-__device__ __forceinline__ uint32_t group_reduce(uint32_t v) {
-    static_assert(G >= 1 && G <= 64 && (G & (G - 1)) == 0, "group size");
-    if constexpr (G >= 2) v = combine<OP>(v, dpp<0xB1>(v));    // quad_perm [1,0,3,2]
-    if constexpr (G >= 4) v = combine<OP>(v, dpp<0x4E>(v));    // quad_perm [2,3,0,1]
-    if constexpr (G >= 8) v = combine<OP>(v, dpp<0x141>(v));   // row_half_mirror
-    if constexpr (G >= 16) v = combine<OP>(v, dpp<0x140>(v));  // row_mirror
-    if constexpr (G >= 32) v = combine<OP>(v, (uint32_t)__shfl_xor((int)v, 16, 64));
-    if constexpr (G >= 64) v = combine<OP>(v, (uint32_t)__shfl_xor((int)v, 32, 64));
-    return v;
-}
-
-// Inclusive prefix sum over groups of G consecutive lanes; g = lane index
-// within the group.  A group inside one 16-lane row shifts with DPP row_shr;
-// row_shr does not cross rows, so wider groups shift through ds_bpermute.
-template <int G>
-__device__ __forceinline__ uint32_t group_scan(uint32_t v, int g) {
-#pragma unroll
-    for (int k = 1; k < G; k <<= 1) {
-        uint32_t y;
-        if constexpr (G <= 16) {
-            if (k == 1) y = dpp<0x111>(v);
-            else if (k == 2) y = dpp<0x112>(v);
-            else if (k == 4) y = dpp<0x114>(v);
-            else y = dpp<0x118>(v);
-        } else {
-            y = (uint32_t)__shfl_up((int)v, k, 64);
-        }
-        v += (g >= k) ? y : 0u;
-    }
-    return v;
-}
-
-// Threads per workgroup of the tile kernels for tile width T: 1024 down to
-// 16-wide tiles, then one wave (64 lanes) per column.
-template <int T>
-constexpr int tile_block() { return T >= 16 ? 1024 : 64 * T; }
-
-// LDS layout of a [rows x T] key tile read by G lanes per column.  Row j
-// lives at j*T; within the row, column c is stored at c ^ swz(j % G).  The
-// G lanes of a column read rows j == g (mod G); the swizzle puts the 32
-// lanes of every half-wave in 32 distinct banks.
-template <int T, int G>
-__host__ __device__ constexpr int tile_swz_of(int g) {
-    static_assert(T == 4 || T == 8 || T == 16 || T == 32 || T == 64 || T == 128, "tile width");
-    static_assert(G >= 1 && G <= 64 && (G & (G - 1)) == 0, "lanes per column");
-    if constexpr (T >= 32) {
-        static_assert(G <= 32, "swizzle needs at most 32 lanes per wide column");
-        return g * (32 / G);
-    } else {
-        return (g / (32 / T)) & (T - 1);
-    }
-}
-
-// The promise above, checked at compile time for every (T, G) the kernels
-// instantiate: the first word each lane of a half-wave reads lies in a bank
-// (of 32) of its own.  A lane's later rows lie G*T words further, a multiple
-// of 32, so they keep the same banks.
-template <int T, int G>
-constexpr bool tile_swz_conflict_free() {
-    for (int h = 0; h < T * G; h += 32) {
-        uint32_t used = 0;
-        for (int i = h; i < h + 32 && i < T * G; ++i) {
-            const int c = i / G, g = i % G;
-            const int bank = (g * T + (c ^ tile_swz_of<T, G>(g))) % 32;
-            if (used & (1u << bank)) return false;
-            used |= 1u << bank;
-        }
-    }
-    return true;
-}
-
-template <int T, int G>
-__device__ __forceinline__ int tile_swz(int g) {
-    static_assert(tile_swz_conflict_free<T, G>(), "tile swizzle leaves a bank conflict");
-    return tile_swz_of<T, G>(g);
-}
-
-// Store the keys of row j, columns 4cq..4cq+3.
-template <int T, int G>
-__device__ __forceinline__ void put_keys(uint32_t *tile, int j, int cq, const uint32_t k[4]) {
-    const int sw = tile_swz<T, G>(j % G);
-    if constexpr (T >= 32 && (32 / G) % 4 == 0) {
-        // the swizzle keeps each aligned group of four columns together
-        *reinterpret_cast<uint4 *>(&tile[j * T + ((4 * cq) ^ sw)]) = make_uint4(k[0], k[1], k[2], k[3]);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) tile[j * T + ((4 * cq + e) ^ sw)] = k[e];
-    }
-}
-
-constexpr int kSelBatch = 8;   // LDS reads in flight per lane
-
-// Per-column histogram of the selection (kHistBuckets buckets plus one
-// overflow bucket); the column stride of kHistStride words keeps each
-// column's bucket block 16-byte aligned and puts equal buckets of
-// neighbouring columns in different banks.
-constexpr int kHistWindow = 7;   // key bits resolved by one histogram round
-static_assert(kHistBuckets == 1 << kHistWindow && kHistStride > kHistBuckets, "histogram");
-
-__host__ __device__ constexpr int64_t hist_words(int T) { return (int64_t)T * kHistStride; }
-
-// One pass over a lane's candidates, in batches of kSelBatch LDS reads.
-template <int STRIDE, typename F>
-__device__ __forceinline__ void for_each_candidate(const uint32_t *base, int cnt, F &&fn) {
-    int x = 0;
-    for (; x + kSelBatch <= cnt; x += kSelBatch) {
-        uint32_t v[kSelBatch];
-#pragma unroll
-        for (int u = 0; u < kSelBatch; ++u) v[u] = base[(x + u) * STRIDE];
-#pragma unroll
-        for (int u = 0; u < kSelBatch; ++u) fn(v[u]);
-    }
-    for (; x < cnt; ++x) fn(base[x * STRIDE]);
-}
-
-// In-place compaction of a lane's candidates: keeps the values for which
-// keep(v) holds, in order.  Every value is stored at the write cursor, which
-// advances only for kept values; a batch is read before any of its slots is
-// overwritten and the cursor never passes the read point.  Returns the
-// number kept.
-template <int STRIDE, typename F>
-__device__ __forceinline__ int compact(uint32_t *base, int cnt, F &&keep) {
-    int w = 0, x = 0;
-    for (; x + kSelBatch <= cnt; x += kSelBatch) {
-        uint32_t v[kSelBatch];
-#pragma unroll
-        for (int u = 0; u < kSelBatch; ++u) v[u] = base[(x + u) * STRIDE];
-#pragma unroll
-        for (int u = 0; u < kSelBatch; ++u) {
-            base[w * STRIDE] = v[u];
-            w += keep(v[u]) ? 1 : 0;
-        }
-    }
-    for (; x < cnt; ++x) {
-        const uint32_t v = base[x * STRIDE];
-        base[w * STRIDE] = v;
-        w += keep(v) ? 1 : 0;
-    }
-    return w;
-}
-
-// Lower median (rank floor((n-1)/2)) of each of the T columns of the LDS key
-// tile holding n rows, found by the G lanes stid = c*G + g of each column c;
-// written to out[k0 + c] for k0 + c < d.  hist: the workgroup's histogram
-// block (hist_words(T) words, zero on entry; left zero on exit except for
-// the overflow buckets).
-//
-// Exact selection on the keys in two stages:
-//  1. histogram rounds while many candidates remain: the bits above the
-//     highest bit where the candidates differ are common to all of them, so
-//     the next kHistWindow bits below it split the candidates into ordered
-//     buckets; an LDS histogram and a prefix scan over the buckets give the
-//     bucket holding the sought rank, and only its members are kept
-//     (compacted in place).  The first round decides the sign from the
-//     count of sign-clear keys and works on the magnitude bits (the keys of
-//     negative values hold them complemented); keys of the other sign land
-//     in the overflow bucket or past every bucket of the sought sign.
-//  2. bitwise MSB radix select on the few survivors: split on the highest
-//     differing bit, keep the side holding the rank, until all are equal.
-// Lane g owns rows g, g+G, ...; its x-th candidate lives at base[x*STRIDE].
-template <int T, int G>
-__device__ __forceinline__ void select_tile(uint32_t *tile, uint32_t *hist, int n, int64_t k0,
-                                            int64_t d, float *out, int stid) {
-    constexpr int STRIDE = G * T;
-    constexpr int BPL = kHistBuckets / G;   // buckets scanned per lane
-    static_assert(BPL >= 2 && BPL % 2 == 0, "buckets per lane");
-    const int g = stid % G;
-    const int c = stid / G;
-    uint32_t *base = tile + g * T + (c ^ tile_swz<T, G>(g));
-    uint32_t *hcol = hist + c * kHistStride;
-    int cnt = (n > g) ? (n - g + G - 1) / G : 0;
-    int total = n;
-    uint32_t m = (uint32_t)(n - 1) / 2;
-
-    // first pass: common magnitude bits and the count of sign-clear keys
-    uint32_t am = 0xFFFFFFFFu, om = 0u, z = 0u;
-    for_each_candidate<STRIDE>(base, cnt, [&](uint32_t v) {
-        const uint32_t mag = (v ^ ~(uint32_t)((int32_t)v >> 31)) & 0x7FFFFFFFu;
-        am &= mag;
-        om |= mag;
-        z += v >> 31;
-    });
-    am = group_reduce<G, Op::And>(am);
-    om = group_reduce<G, Op::Or>(om);
-    z = (uint32_t)total - group_reduce<G, Op::Add>(z);   // keys with the top bit clear
-
-    auto and_or = [&](uint32_t &a, uint32_t &o) {
-        a = 0xFFFFFFFFu;
-        o = 0u;
-        for_each_candidate<STRIDE>(base, cnt, [&](uint32_t v) {
-            a &= v;
-            o |= v;
-        });
-        a = group_reduce<G, Op::And>(a);
-        o = group_reduce<G, Op::Or>(o);
-    };
-    // one histogram round over the candidates whose keys lie in
-    // [bias, bias + 2^(hb+1)); keeps the bucket holding rank m
-    auto hist_round = [&](uint32_t bias, int hb) {
-        const int sh = hb >= kHistWindow - 1 ? hb - (kHistWindow - 1) : 0;
-        for_each_candidate<STRIDE>(base, cnt, [&](uint32_t v) {
-            const uint32_t b = min((v - bias) >> sh, (uint32_t)kHistBuckets);
-            atomicAdd(&hcol[b], 1u);
-        });
-        // bucket holding rank m: B = number of buckets whose inclusive
-        // prefix count is <= m, below = the largest such prefix
-        uint32_t h[BPL];
-#pragma unroll
-        for (int q = 0; q < BPL; q += 2) {
-            const uint2 w2 = *reinterpret_cast<const uint2 *>(&hcol[g * BPL + q]);
-            h[q] = w2.x;
-            h[q + 1] = w2.y;
-        }
-#pragma unroll
-        for (int q = 0; q < BPL; q += 2)
-            *reinterpret_cast<uint2 *>(&hcol[g * BPL + q]) = make_uint2(0u, 0u);
-        uint32_t tot = 0u;
-#pragma unroll
-        for (int q = 0; q < BPL; ++q) tot += h[q];
-        uint32_t run = group_scan<G>(tot, g) - tot;
-        uint32_t le = 0u, below = 0u;
-#pragma unroll
-        for (int q = 0; q < BPL; ++q) {
-            run += h[q];
-            const bool ok = run <= m;
-            le += ok ? 1u : 0u;
-            below = ok ? run : below;
-        }
-        le = group_reduce<G, Op::Add>(le);
-        below = group_reduce<G, Op::Max>(below);
-        m -= below;
-        const uint32_t lo = bias + (le << sh);
-        const uint32_t width = 1u << sh;
-        cnt = compact<STRIDE>(base, cnt, [&](uint32_t v) { return v - lo < width; });
-        total = (int)group_reduce<G, Op::Add>((uint32_t)cnt);
-    };
-
-    uint32_t a, o, varying;
-    bool have_count = false;
-    if (total > 2 * G) {
-        uint32_t sgn = 0x80000000u;
-        if (m < z) sgn = 0u;
-        else m -= z;
-        const uint32_t vm = am ^ om;
-        if (vm == 0u) {   // every candidate has the same magnitude
-            a = sgn ? (0x80000000u | am) : (~am & 0x7FFFFFFFu);
-            varying = 0u;
-        } else {
-            const int hb = 31 - __clz(vm);
-            const uint32_t hi = 0x7FFFFFFFu & ~((2u << hb) - 1u);
-            hist_round(sgn ? (0x80000000u | (am & hi)) : (~am & hi), hb);
-            and_or(a, o);
-            varying = a ^ o;
-            // the sign is settled now; every round settles the bits from the
-            // highest differing one down to the window's lowest, so the next
-            // round starts strictly lower (at most 31 / kHistWindow more)
-            for (int round = 0; varying != 0u && total > 2 * G && round < 5; ++round) {
-                const int hb2 = 31 - __clz(varying);
-                hist_round(a & ~((2u << hb2) - 1u), hb2);
-                and_or(a, o);
-                varying = a ^ o;
-            }
-        }
-    } else {
-        and_or(a, o);
-        varying = a ^ o;
-        have_count = (varying >> 31) != 0u;   // z counts zeros of the top bit
-    }
-
-    // each step settles the highest differing bit: at most 32 steps
-    for (int step = 0; varying != 0u && step < 32; ++step) {
-        const uint32_t bit = 1u << (31 - __clz(varying));
-        if (!have_count) {
-            z = 0u;
-            for_each_candidate<STRIDE>(base, cnt, [&](uint32_t v) { z += (v & bit) == 0u; });
-            z = group_reduce<G, Op::Add>(z);
-        }
-        have_count = false;
-        uint32_t want;
-        if (m < z) {
-            want = 0u;
-        } else {
-            want = bit;
-            m -= z;
-        }
-        cnt = compact<STRIDE>(base, cnt, [&](uint32_t v) { return (v & bit) == want; });
-        and_or(a, o);
-        varying = a ^ o;
-    }
-    if (g == 0 && k0 + c < d) out[k0 + c] = __uint_as_float(from_key(a));
-}
-
-// ---------------------------------------------------------------------------
-// Half-key tiles.  The LDS tile holds only the high 16 bits of every key,
-// two rows per word, so a tile of the same LDS size is twice as wide (and
-// the row segments read from HBM twice as long).  The high half of the
-// sought key is selected exactly on the tile; the low halves are then read
-// back from the replica rows, only for the rows whose high half equals it
-// (about one row per column on continuous data; every row when all high
-// halves of a column are equal, which costs speed, not exactness).
-//
-// Layout for a streaming role of RPI rows per sweep: rows j and j + RPI,
-// which one lane loads in two consecutive sweeps, share the word of
-// pair-row p = (j / 2RPI) * RPI + j % RPI (j / RPI even: low half), stored
-// at p*T + (c ^ swz(p % G)), so a lane writes whole words.  Rows without a
-// kept value (past the last row, or a dropped file) hold the largest key,
-// 0xFFFF, as do the low halves read back for them: appending elements that
-// are not below any other leaves every rank below the kept count in place.
-
-constexpr int kHalfWindow = 6;                  // key bits per histogram round
-constexpr int kHalfBuckets = 1 << kHalfWindow;
-constexpr int kHalfStride = kHalfBuckets + 2;   // words per column block
-constexpr uint32_t kHalfTop = 0xFFFFu;          // largest key: padding rows
-
-__host__ __device__ constexpr int64_t half_hist_words(int T) { return (int64_t)T * kHalfStride; }
-// streaming rows per sweep of a tile T columns wide, for `fill` streaming
-// threads of four columns each
-__host__ __device__ constexpr int half_rpi(int T, int fill) { return fill * 4 / T; }
-// pair-rows of a tile of `rows` rows: whole pairs of sweeps
-__host__ __device__ constexpr int64_t half_pair_rows(int64_t rows, int T, int fill) {
-    return (rows + 2 * half_rpi(T, fill) - 1) / (2 * half_rpi(T, fill)) * half_rpi(T, fill);
-}
-__host__ __device__ constexpr int64_t half_tile_words(int64_t rows, int T, int fill) {
-    return half_pair_rows(rows, T, fill) * T;
-}
-
-// Row held by half h of pair-row p.
-template <int RPI>
-__device__ __forceinline__ int half_row(int p, int h) {
-    return (p / RPI) * 2 * RPI + h * RPI + p % RPI;
-}
-
-// The high halves of two full keys, packed (a's in the low 16 bits).
-__device__ __forceinline__ uint32_t pack_high(uint32_t a, uint32_t b) {
-    return (a >> 16) | (b & 0xFFFF0000u);
-}
-
-// Store pair-row p, columns 4cq..4cq+3, from the packed high halves of the
-// even sweep (lo: columns 0,1 and 2,3 in two registers) and of the odd one.
-template <int T, int G>
-__device__ __forceinline__ void put_pairs(uint32_t *tile, int p, int cq, const uint32_t lo[2],
-                                          const uint32_t hi[2]) {
-    uint32_t w[4];
-    w[0] = (lo[0] & 0xFFFFu) | (hi[0] << 16);
-    w[1] = (lo[0] >> 16) | (hi[0] & 0xFFFF0000u);
-    w[2] = (lo[1] & 0xFFFFu) | (hi[1] << 16);
-    w[3] = (lo[1] >> 16) | (hi[1] & 0xFFFF0000u);
-    const int sw = tile_swz<T, G>(p % G);
-    if constexpr (T >= 64 && (32 / G) % 4 == 0) {
-        // the swizzle keeps each aligned group of four columns together
-        *reinterpret_cast<uint4 *>(&tile[p * T + ((4 * cq) ^ sw)]) = make_uint4(w[0], w[1], w[2], w[3]);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) tile[p * T + ((4 * cq + e) ^ sw)] = w[e];
-    }
-}
-
-// Lower median of each of the T columns of a half-key tile of np pair-rows
-// holding nk kept values (1 <= nk, 2*np <= 65536), by the G lanes
-// stid = c*G + g of column c, written to out[k0 + c] for k0 + c < d.
-// row(j) gives the replica row of g behind tile row j, or -1 for a padding
-// row.  hist: half_hist_words(T) words, zero on entry and on exit.  The
-// tile is overwritten.  With REG > 0 (np a multiple of G, np / G <= REG)
-// the lane's words are read from the tile once, into registers, and every
-// later pass over the keys reads those (the median kernel measured 4-5 %
-// faster at 455 rows; the single pass, whose registers are taken by its
-// own state, keeps reading the tile).
-//
-//  1. one pass: the least key, the greatest key below 0xFFFF, the least
-//     sign-set and the greatest sign-clear key, and the count of sign-set
-//     keys (packed 16-bit min / max / add, two keys an instruction); settles
-//     the sign and the window [lo, hi] of the keys of that sign;
-//  2. histogram rounds over the window, each resolving kHalfWindow bits,
-//     until the sought high half H is known (at most 3 rounds; H = 0xFFFF
-//     when the rank falls past a sign-set window); nothing is compacted,
-//     every round reads all keys;
-//  3. one pass collecting the rows whose high half is H into the lane's
-//     16-bit slots (in place), then their low halves are read from g;
-//  4. bitwise radix select on those low halves for the remaining rank.
-template <int T, int G, int RPI, int REG = 0, typename RowFn>
-__device__ __forceinline__ void select_half_tile(uint32_t *tile, uint32_t *hist, int np, int nk,
-                                                 int64_t k0, int64_t d, float *out, int stid,
-                                                 const float *__restrict__ g, RowFn &&row) {
-    constexpr int STRIDE = G * T;   // words between a lane's pair-rows
-    constexpr int BPL = kHalfBuckets / G;
-    static_assert(BPL >= 2 && BPL % 2 == 0, "buckets per lane");
-    const int gl = stid % G;
-    const int c = stid / G;
-    uint32_t *base = tile + gl * T + (c ^ tile_swz<T, G>(gl));
-    uint16_t *base16 = reinterpret_cast<uint16_t *>(base);
-    uint32_t *hcol = hist + c * kHalfStride;
-    const int cnt = np > gl ? (np - gl + G - 1) / G : 0;   // words of this lane
-    uint32_t m = (uint32_t)(nk - 1) / 2;
-    // REG > 0: the lane's words are read once, into registers.  The caller
-    // passes np = half_pair_rows(...), a multiple of RPI = 4G, so every lane
-    // of the wave holds the same count, a multiple of 4, at most REG
-    static_assert(REG == 0 || RPI == 4 * G, "register mode needs RPI = 4G");
-    uint32_t kw[REG > 0 ? REG : 1];
-    const int cw = __builtin_amdgcn_readfirstlane(cnt);
-
-    // every key of the lane: fn(key, word x, half h) for pair-row gl + x*G
-    auto each = [&](auto &&fn) __attribute__((always_inline)) {
-        if constexpr (REG > 0) {
-            // cw is a multiple of 4 (np is a multiple of RPI = 4G)
-#pragma unroll
-            for (int xb = 0; xb < REG; xb += 4) {
-                if (xb < cw) {
-#pragma unroll
-                    for (int x = xb; x < xb + 4 && x < REG; ++x) {
-                        fn(kw[x] & 0xFFFFu, x, 0);
-                        fn(kw[x] >> 16, x, 1);
-                    }
-                }
-            }
-            return;
-        }
-        int x = 0;
-        for (; x + kSelBatch <= cnt; x += kSelBatch) {
-            uint32_t v[kSelBatch];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) v[u] = base[(x + u) * STRIDE];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) {
-                fn(v[u] & 0xFFFFu, x + u, 0);
-                fn(v[u] >> 16, x + u, 1);
-            }
-        }
-        for (; x < cnt; ++x) {
-            const uint32_t v = base[x * STRIDE];
-            fn(v & 0xFFFFu, x, 0);
-            fn(v >> 16, x, 1);
-        }
-    };
-    // the lane's x-th 16-bit slot (step 3 on)
-    auto slot = [&](int x) __attribute__((always_inline)) -> uint16_t & {
-        return base16[(x >> 1) * 2 * STRIDE + (x & 1)];
-    };
-
-    // 1. extremes and the sign count, both keys of a word at once in 16-bit
-    //    lanes: the least key, the greatest key below 0xFFFF (the greatest
-    //    key + 1, which wraps 0xFFFF to 0), and with the sign bit flipped the
-    //    least sign-set key and the greatest sign-clear key; the number of
-    //    sign-set keys
-    uint32_t mn2 = 0xFFFFFFFFu, mt2 = 0u, ms2 = 0xFFFFFFFFu, mc2 = 0u, ns = 0u;
-    auto stats = [&](uint32_t w) __attribute__((always_inline)) {
-        const uint32_t x = w ^ 0x80008000u;
-        mn2 = pk_min_u16(mn2, w);
-        mt2 = pk_max_u16(mt2, pk_add_u16(w, 0x00010001u));
-        ms2 = pk_min_u16(ms2, x);
-        mc2 = pk_max_u16(mc2, x);
-        ns += (uint32_t)__builtin_popcount(w & 0x80008000u);
-    };
-    if constexpr (REG > 0) {
-#pragma unroll
-        for (int xb = 0; xb < REG; xb += 4) {
-            if (xb < cw) {
-#pragma unroll
-                for (int x = xb; x < xb + 4 && x < REG; ++x) kw[x] = base[x * STRIDE];
-            }
-        }
-#pragma unroll
-        for (int xb = 0; xb < REG; xb += 4) {
-            if (xb < cw) {
-#pragma unroll
-                for (int x = xb; x < xb + 4 && x < REG; ++x) stats(kw[x]);
-            }
-        }
-    } else {
-        int x = 0;
-        for (; x + kSelBatch <= cnt; x += kSelBatch) {
-            uint32_t v[kSelBatch];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) v[u] = base[(x + u) * STRIDE];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) stats(v[u]);
-        }
-        for (; x < cnt; ++x) stats(base[x * STRIDE]);
-    }
-    auto lo16 = [](uint32_t v2, bool lower) __attribute__((always_inline)) {
-        const uint32_t a = v2 & 0xFFFFu, b = v2 >> 16;
-        return lower ? (a < b ? a : b) : (a > b ? a : b);
-    };
-    const uint32_t mn = group_reduce<G, Op::Min>(lo16(mn2, true));                // least key
-    const uint32_t mt = group_reduce<G, Op::Max>(lo16(mt2, false));               // greatest below 0xFFFF, + 1
-    const uint32_t ms = group_reduce<G, Op::Min>(lo16(ms2, true)) ^ 0x8000u;      // least sign-set
-    const uint32_t mc = group_reduce<G, Op::Max>(lo16(mc2, false)) ^ 0x8000u;     // greatest sign-clear
-    const uint32_t z = (uint32_t)(2 * np) - group_reduce<G, Op::Add>(ns);         // sign-clear count
-
-    // 2. the window [lo, hi] of the keys of the sought key's sign (below
-    //    0xFFFF); histogram rounds split it into kHalfBuckets buckets of
-    //    2^sh keys and keep the one holding rank m, until sh = 0 (16 bits:
-    //    three rounds at most).  A key above hi inside the window (0xFFFF, or
-    //    a sign-set key in a sign-clear window) is counted like any other:
-    //    it is above the sought key.  The rank past a sign-set window is a
-    //    0xFFFF key.
-    //    The round of single keys (sh = 0) also lists the lane's keys in its
-    //    window as (word, half, bucket) codes in the lane's 16-bit slots, in
-    //    place (the write cursor never passes the read cursor), and keeps
-    //    those of the sought bucket as row numbers: step 3 then has its rows
-    //    without another pass.  Not in a first round that may find the rank
-    //    past a sign-set window (the tile must stay whole for the 0xFFFF
-    //    pass), nor when a lane holds 512 words or more (9 bits of word).
-    uint32_t H = kHalfTop;
-    bool settled = false, collected = false;
-    int w = 0;
-    uint32_t lo, hi;
-    const bool clear_sign = m < z;
-    if (clear_sign) {
-        lo = mn;
-        hi = mc;
-    } else {
-        m -= z;
-        lo = ms;
-        hi = mt - 1u;
-        if (mt == 0u || hi < lo) settled = true;   // no sign-set key below 0xFFFF
-    }
-    if (!settled) {
-        uint32_t bias = lo;
-        const int width = 32 - __clz(hi - lo);   // bits of hi - lo (0 when equal)
-        int sh = width > kHalfWindow ? width - kHalfWindow : 0;
-        for (int round = 0; round < 3; ++round) {
-            const uint32_t span = (uint32_t)kHalfBuckets << sh;
-            const bool list = sh == 0 && (round > 0 || clear_sign) && np <= 511 * G;
-            if (list) {
-                each([&](uint32_t k, int x, int hf) {
-                    const uint32_t o = k - bias;
-                    if (o < span) {
-                        atomicAdd(&hcol[o], 1u);
-                        slot(w) = (uint16_t)(((uint32_t)x << 7) | ((uint32_t)hf << 6) | o);
-                        ++w;
-                    }
-                });
-            } else {
-                each([&](uint32_t k, int, int) {
-                    const uint32_t o = k - bias;
-                    if (o < span) atomicAdd(&hcol[o >> sh], 1u);
-                });
-            }
-            uint32_t h[BPL];
-#pragma unroll
-            for (int q = 0; q < BPL; q += 2) {
-                const uint2 w2 = *reinterpret_cast<const uint2 *>(&hcol[gl * BPL + q]);
-                h[q] = w2.x;
-                h[q + 1] = w2.y;
-            }
-#pragma unroll
-            for (int q = 0; q < BPL; q += 2)
-                *reinterpret_cast<uint2 *>(&hcol[gl * BPL + q]) = make_uint2(0u, 0u);
-            uint32_t tot = 0u;
-#pragma unroll
-            for (int q = 0; q < BPL; ++q) tot += h[q];
-            uint32_t run = group_scan<G>(tot, gl) - tot;
-            uint32_t le = 0u, below = 0u;
-#pragma unroll
-            for (int q = 0; q < BPL; ++q) {
-                run += h[q];
-                const bool ok = run <= m;
-                le += ok ? 1u : 0u;
-                below = ok ? run : below;
-            }
-            le = group_reduce<G, Op::Add>(le);
-            below = group_reduce<G, Op::Max>(below);
-            m -= below;
-            if (le == (uint32_t)kHalfBuckets) {   // past the window: a 0xFFFF key
-                settled = true;
-                break;
-            }
-            bias += le << sh;
-            if (sh == 0) {
-                if (list) {   // the listed keys of bucket le, as row numbers
-                    int n2 = 0;
-                    for (int j = 0; j < w; ++j) {
-                        const uint32_t v = slot(j);
-                        if ((v & 63u) == le) {
-                            slot(n2) = (uint16_t)half_row<RPI>(gl + (int)(v >> 7) * G, (int)(v >> 6) & 1);
-                            ++n2;
-                        }
-                    }
-                    w = n2;
-                    collected = true;
-                }
-                break;
-            }
-            sh = sh > kHalfWindow ? sh - kHalfWindow : 0;
-        }
-        if (!settled) H = bias;
-    }
-
-    // 3. rows whose high half is H, as row numbers in the lane's slots (the
-    //    write cursor never passes the read cursor), then their low halves
-    if (!collected) {
-        w = 0;
-        each([&](uint32_t k, int x, int hf) {
-            if (k == H) {
-                slot(w) = (uint16_t)half_row<RPI>(gl + x * G, hf);
-                ++w;
-            }
-        });
-    }
-    const bool valid = k0 + c < d;
-    constexpr int kGather = 4;   // row reads in flight per lane
-    for (int x0 = 0; x0 < w; x0 += kGather) {
-        uint32_t v[kGather];
-#pragma unroll
-        for (int u = 0; u < kGather; ++u) {
-            v[u] = 0xFFFFFFFFu;   // a padding row: the largest key
-            if (x0 + u < w) {
-                const int64_t rr = row(slot(x0 + u));
-                if (rr >= 0 && valid) v[u] = to_key(__float_as_uint(g[rr * d + k0 + c]));
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kGather; ++u)
-            if (x0 + u < w) slot(x0 + u) = (uint16_t)(v[u] & 0xFFFFu);
-    }
-
-    // 4. bitwise radix select of rank m among the low halves
-    auto and_or = [&](uint32_t &a, uint32_t &o) __attribute__((always_inline)) {
-        a = 0xFFFFu;
-        o = 0u;
-        for (int x = 0; x < w; ++x) {
-            const uint32_t v = slot(x);
-            a &= v;
-            o |= v;
-        }
-        a = group_reduce<G, Op::And>(a);
-        o = group_reduce<G, Op::Or>(o);
-    };
-    uint32_t a, o;
-    and_or(a, o);
-    uint32_t varying = a ^ o;
-    for (int step = 0; varying != 0u && step < 16; ++step) {
-        const uint32_t bit = 1u << (31 - __clz(varying));
-        uint32_t zc = 0u;
-        for (int x = 0; x < w; ++x) zc += (slot(x) & bit) == 0u;
-        zc = group_reduce<G, Op::Add>(zc);
-        uint32_t want;
-        if (m < zc) {
-            want = 0u;
-        } else {
-            want = bit;
-            m -= zc;
-        }
-        int nw = 0;
-        for (int x = 0; x < w; ++x) {
-            const uint16_t v = slot(x);
-            slot(nw) = v;
-            nw += (v & bit) == want ? 1 : 0;
-        }
-        w = nw;
-        and_or(a, o);
-        varying = a ^ o;
-    }
-    if (gl == 0 && valid) out[k0 + c] = __uint_as_float(from_key((H << 16) | a));
-}
-
-// One 16-byte load (16-byte aligned) from a replica row that the pass
-// reads once: a non-temporal load, which streams past the caches instead of
-// filling them with lines nothing reads again (measured 3-6 % faster than a
-// plain load on the 61 GB single pass).
-__device__ __forceinline__ uint4 load_stream(const float *p) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-// Load four consecutive coordinates [k, k+4) of one row as bit patterns;
-// coordinates at or beyond kend read as 0.
-template <bool VEC>
-__device__ __forceinline__ void load4(const float *row, int64_t k, int64_t kend,
-                                      uint32_t v[4]) {
-    if (VEC && k + 3 < kend) {
-        const uint4 q = load_stream(row + k);
-        v[0] = q.x;
-        v[1] = q.y;
-        v[2] = q.z;
-        v[3] = q.w;
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            v[e] = (k + e < kend) ? __float_as_uint(row[k + e]) : 0u;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // utility kernels
@@ -800,12 +68,6 @@ __global__ void fill_u64_kernel(uint64_t *p, int64_t n, uint64_t v) {
 
 constexpr int kAgreeUnroll = 4;                       // float4 per thread
 constexpr int64_t kAgreeChunk = (int64_t)kBlock * 4 * kAgreeUnroll;
-
-// Row of replica (i,s): i*R+s in the file-major tensor, or row_of[i*R+s]
-// when a row table is given.
-__device__ __forceinline__ int64_t replica_row(const int32_t *row_of, int64_t i, int R, int s) {
-    return row_of ? (int64_t)row_of[i * R + s] : i * R + s;
-}
 
 template <int R, bool VEC>
 __global__ void __launch_bounds__(kBlock)
@@ -1064,36 +326,6 @@ select_kernel(const int32_t *__restrict__ subsets,
 
 constexpr int kMedianBatch = 8;   // row loads per thread issued as one burst
 
-// The tiles a median launch computes: every tile, or (a repair after a
-// wrong guess) the tiles of the groups whose bit is set, bit b for tiles
-// [b << gshift, (b + 1) << gshift).  Uniform per workgroup.
-struct TileMask {
-    const uint32_t *bits = nullptr;
-    const int32_t *count = nullptr;   // groups set (no tile at all when 0)
-    int gshift = 0;
-    __device__ __forceinline__ bool has(int64_t t) const {
-        const int64_t b = t >> gshift;
-        return ((bits[b >> 5] >> (b & 31)) & 1u) != 0u;
-    }
-    // the first computed tile of t, t + step, ..., or one >= ntiles: t
-    // itself when its bit is set, else the bits of eight candidates at once
-    __device__ __forceinline__ int64_t next(int64_t t, int64_t step, int64_t ntiles) const {
-        if (bits == nullptr || t >= ntiles) return t;
-        if (*count == 0) return ntiles;
-        if (has(t)) return t;
-        for (t += step; t < ntiles; t += 8 * step) {
-            uint32_t hit = 0u;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t tu = t + u * step;
-                if (tu < ntiles && has(tu)) hit |= 1u << u;
-            }
-            if (hit) return t + (int64_t)(__ffs(hit) - 1) * step;
-        }
-        return ntiles;
-    }
-};
-
 template <int T, bool VEC>
 __global__ void __launch_bounds__(tile_block<T>())
 median_kernel(const float *__restrict__ g, int64_t d,
@@ -1216,426 +448,6 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
     }
     for (int64_t i = tid; i < f; i += BLOCK)
         if (pd[i]) atomicOr(&pair_diff[i], pd[i]);
-}
-
-// ---------------------------------------------------------------------------
-// fused agreement + median, warp-specialised: waves 0-7 stream tile t+1 into
-// registers (compare the r replicas, keep the guessed replica's keys) while
-// waves 8-15 run the selection on tile t in LDS; the keys are handed over
-// between two barriers.  The row loads and the selection overlap inside one
-// workgroup, so a single [f x T] tile of LDS per CU is enough.
-
-constexpr int kWsThreads = 1024;   // threads of a warp-specialised workgroup
-constexpr int kWsFill = 512;       // threads of the streaming role (default split)
-
-// sweeps per burst of loads: as many as the streaming role's registers hold
-// next to the tile's keys (SW x 4 registers, or SW x 2 with half keys).  The
-// 36-sweep tile spills either way; one sweep per burst spills least
-template <int R, int SW>
-constexpr int ws_batch() { return R == 3 ? (SW > 32 ? 1 : SW > 12 ? 2 : 3) : 1; }
-
-template <int T, int R, int SW, bool IND, bool HALF, int FILL, bool RTG = false>
-__global__ void __launch_bounds__(kWsThreads)
-fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f, int64_t d,
-                const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
-                const int32_t *__restrict__ n_sel, int64_t ntiles,
-                uint32_t *__restrict__ pair_diff, float *__restrict__ out) {
-    extern __shared__ uint32_t smem[];
-    constexpr int G = (kWsThreads - FILL) / T;   // selection lanes per column
-    constexpr int CPR = T / 4;           // float4 chunks per row segment
-    constexpr int RPI = FILL / CPR;      // rows per sweep of the streaming role
-    constexpr int B = ws_batch<R, SW>(); // sweeps per burst of loads
-    // key registers per sweep: 4 keys, or (HALF) 4 high halves packed in 2;
-    // a half-key tile's rows are the files themselves
-    constexpr int KW = HALF ? 2 : 4;
-    static_assert(!HALF || (SW % 2 == 0 && RPI == half_rpi(T, FILL) && RPI % 8 == 0 && R <= 7),
-                  "half-key sweeps");
-    // a file's pair-difference bits fit a nibble only at r = 3 (3 bits)
-    constexpr bool PDN = HALF && R == 3;
-    const int n = *n_sel;
-    const int64_t hwords = HALF ? half_hist_words(T) : hist_words(T);
-    const int64_t f8 = (f + 7) / 8;
-    uint32_t *hist = smem;               // selection histograms
-    uint32_t *tile = smem + hwords;
-    // per-file words.  Full keys: pd [f] pair-difference bits, ps [f]
-    // (tile row << 3) | slot or -1.  Half keys (tile row = file): ps [f/8],
-    // one nibble per file, 8 | slot or 0; pd [f/8] pair-difference nibbles
-    // at r = 3, else pd [f] words
-    uint32_t *pd = tile + (HALF ? half_tile_words(f, T, FILL) : f * T);
-    int32_t *ps = reinterpret_cast<int32_t *>(pd + (PDN ? f8 : f));
-    // [f*R] row table (IND): staged in LDS, or (RTG) read from global
-    // memory, where it stays cached, when LDS is needed for a wider tile
-    int32_t *rt_lds = ps + (HALF ? f8 : f);
-    const int32_t *rt = RTG ? row_of : rt_lds;
-    const int tid = threadIdx.x;
-    if constexpr (HALF) {
-        for (int64_t w = tid; w < f8; w += kWsThreads) {
-            uint32_t v = 0u;
-            for (int e = 0; e < 8; ++e) {
-                const int64_t i = 8 * w + e;
-                if (i < f && pos[i] >= 0) v |= (8u | (uint32_t)sel[i]) << (4 * e);
-            }
-            ps[w] = (int32_t)v;
-        }
-        for (int64_t w = tid; w < (PDN ? f8 : f); w += kWsThreads) pd[w] = 0u;
-    } else {
-        for (int64_t i = tid; i < f; i += kWsThreads) {
-            pd[i] = 0u;
-            ps[i] = pos[i] >= 0 ? (pos[i] << 3) | sel[i] : -1;
-        }
-    }
-    // the slot nibble of file i (HALF): 8 | slot when kept, else 0
-    auto nib = [&](int i) __attribute__((always_inline)) {
-        return ((uint32_t)ps[i >> 3] >> ((i & 7) * 4)) & 15u;
-    };
-    if constexpr (IND && !RTG)
-        for (int64_t i = tid; i < f * R; i += kWsThreads) rt_lds[i] = row_of[i];
-    for (int i = tid; i < hwords; i += kWsThreads) hist[i] = 0u;
-    __syncthreads();
-    // roles are whole waves: the first FILL/64 waves stream, the rest
-    // select; every wave executes the same number of barriers (1 + 2 per
-    // tile)
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (wave < FILL / 64) {
-        const int cq = tid % CPR, j0 = tid / CPR;
-        const int64_t sweep = (int64_t)RPI * R * d;   // elements between sweeps
-        uint32_t keys[SW][KW];
-        // pair-difference bits of the lane's files (sweep x: bits
-        // NP*(x % PER) of word x / PER), ORed over every tile in registers
-        // and merged into LDS once at the end
-        constexpr int NPB = R * (R - 1) / 2;
-        constexpr int PER = 32 / NPB;
-        uint32_t pdacc[(SW + PER - 1) / PER];
-#pragma unroll
-        for (int a = 0; a < (SW + PER - 1) / PER; ++a) pdacc[a] = 0u;
-        // the r replica chunks of one sweep, kept in registers (a value
-        // type, so that no per-lane indexing can turn it into memory)
-        struct Chunks {
-            uint4 q[R];
-        };
-        // issue the row loads of sweep x of tile t.  Every load is in bounds:
-        // a lane past the end of the rows (tail tile; d % 4 == 0) reads the
-        // last chunk of its row instead (a repeated chunk changes neither
-        // the agreement bits nor any written median), and a lane past the
-        // last file loads nothing (proc_sweep ignores it).
-        auto load_sweep = [&](int64_t t, int x) __attribute__((always_inline)) {
-            const int64_t col = min(t * T + 4 * cq, d - 4);
-            if constexpr (IND) {
-                int i = j0 + x * RPI;
-                asm volatile("" : "+v"(i));   // row addresses recomputed per tile
-                Chunks c;
-                if (i < f) {
-#pragma unroll
-                    for (int s = 0; s < R; ++s)
-                        c.q[s] = load_stream(g + (int64_t)rt[i * R + s] * d + col);
-                } else {
-#pragma unroll
-                    for (int s = 0; s < R; ++s) c.q[s] = make_uint4(0u, 0u, 0u, 0u);
-                }
-                return c;
-            }
-            const float *base = g + (int64_t)j0 * R * d + col;
-            int lim = (int)(f - j0);   // sweeps x with x * RPI < lim hold a file
-            // opaque copies of the tile's base address, the limit and the
-            // sweep stride: every row address and check below is recomputed
-            // from them, instead of the compiler carrying one pointer, one
-            // lane mask and one offset per sweep across tiles
-            int64_t stride = sweep;
-            asm volatile("" : "+v"(base), "+v"(lim), "+s"(stride));
-            Chunks c;
-            if (x * RPI < lim) {
-                const float *rows = base + x * stride;
-#pragma unroll
-                for (int s = 0; s < R; ++s) c.q[s] = load_stream(rows + s * d);
-            } else {
-#pragma unroll
-                for (int s = 0; s < R; ++s) c.q[s] = make_uint4(0u, 0u, 0u, 0u);
-            }
-            return c;
-        };
-        // compare the replicas of sweep x and keep the guessed replica's keys
-        // (HALF: its high key halves, packed two to a register, 0xFFFF for a
-        // file past the last or dropped)
-        auto proc_sweep = [&](int x, Chunks c) __attribute__((always_inline)) {
-            const int i = j0 + x * RPI;   // f <= C(64,3) here
-            if constexpr (HALF) {
-                keys[x][0] = 0xFFFFFFFFu;
-                keys[x][1] = 0xFFFFFFFFu;
-            }
-            if (i < f) {
-                uint32_t diff = 0u;
-                int p = 0;
-#pragma unroll
-                for (int s = 0; s < R; ++s)
-#pragma unroll
-                    for (int u = s + 1; u < R; ++u) {
-                        const uint32_t y = (c.q[s].x ^ c.q[u].x) | (c.q[s].y ^ c.q[u].y) |
-                                           (c.q[s].z ^ c.q[u].z) | (c.q[s].w ^ c.q[u].w);
-                        diff |= (y != 0u ? 1u : 0u) << p;
-                        ++p;
-                    }
-                pdacc[x / PER] |= diff << (NPB * (x % PER));
-                // HALF: file i's nibble, word (j0 >> 3) + x*RPI/8 (RPI is a
-                // multiple of 8), shift (j0 & 7) * 4 in every sweep
-                const int w8 = (j0 >> 3) + x * (RPI / 8), sh = (j0 & 7) * 4;
-                const int q = HALF ? (int)(((uint32_t)ps[w8] >> sh) & 15u) : ps[i];
-                const int s_sel = q & 7;
-                uint4 w = c.q[0];
-#pragma unroll
-                for (int s = 1; s < R; ++s)
-                    if (s_sel == s) w = c.q[s];
-                if constexpr (HALF) {
-                    if (q & 8) {
-                        keys[x][0] = pack_high(to_key(w.x), to_key(w.y));
-                        keys[x][1] = pack_high(to_key(w.z), to_key(w.w));
-                    }
-                } else {
-                    keys[x][0] = to_key(w.x);
-                    keys[x][1] = to_key(w.y);
-                    keys[x][2] = to_key(w.z);
-                    keys[x][3] = to_key(w.w);
-                }
-            }
-        };
-        // sweep 0 of the next tile, loaded early: before the barrier and the
-        // hand-over, so that loads stay in flight meanwhile.  The 36-sweep
-        // tile, the row-table reads and r = 5 (five chunks a sweep) have no
-        // registers to spare for it and load it with their tile
-        constexpr bool kEarly0 = SW <= 32 && !IND && R == 3;
-        Chunks c0;
-        // tile t from its sweep 0 (already in c0, or loaded first); the
-        // other sweeps go in bursts of B, all loads of a burst issued first
-        auto stream_rest = [&](int64_t t) __attribute__((always_inline)) {
-            if constexpr (!kEarly0) c0 = load_sweep(t, 0);
-            proc_sweep(0, c0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int xb = 1; xb < SW; xb += B) {
-                Chunks c[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) c[b] = load_sweep(t, xb + b);
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) proc_sweep(xb + b, c[b]);
-                // keep each burst's loads together: no scheduling across
-                // bursts, which would hold more loads in registers than fit
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        auto put_tile = [&]() __attribute__((always_inline)) {
-            if constexpr (HALF) {
-                // pair-rows j0 + k*RPI of the sweep pairs holding a file
-                int64_t fo = f;   // opaque: compared per tile, not held per pair
-                asm volatile("" : "+s"(fo));
-#pragma unroll
-                for (int k = 0; k < SW / 2; ++k)
-                    if (k * 2 * RPI < fo)
-                        put_pairs<T, G>(tile, j0 + k * RPI, cq, keys[2 * k], keys[2 * k + 1]);
-            } else {
-#pragma unroll
-                for (int x = 0; x < SW; ++x) {
-                    const int i = j0 + x * RPI;
-                    if (i < f) {
-                        const int q = ps[i];
-                        if (q >= 0) put_keys<T, G>(tile, q >> 3, cq, keys[x]);
-                    }
-                }
-            }
-        };
-        int64_t t = blockIdx.x;
-        if (t < ntiles) {
-            if constexpr (kEarly0) c0 = load_sweep(t, 0);
-            stream_rest(t);
-        }
-        if (kEarly0 && t + gridDim.x < ntiles) c0 = load_sweep(t + gridDim.x, 0);
-        if (t < ntiles) put_tile();
-        __syncthreads();
-        for (; t < ntiles; t += gridDim.x) {
-            const int64_t tn = t + gridDim.x;
-            if (tn < ntiles) stream_rest(tn);
-            if (kEarly0 && tn + gridDim.x < ntiles) c0 = load_sweep(tn + gridDim.x, 0);
-            __syncthreads();
-            if (tn < ntiles) put_tile();
-            __syncthreads();
-        }
-        // the lane's pair-difference bits into the workgroup's words
-#pragma unroll
-        for (int x = 0; x < SW; ++x) {
-            const int i = j0 + x * RPI;
-            const uint32_t b = (pdacc[x / PER] >> (NPB * (x % PER))) & ((1u << NPB) - 1u);
-            if (i < f && b) {
-                if constexpr (PDN)
-                    atomicOr(&pd[i >> 3], b << ((i & 7) * 4));
-                else
-                    atomicOr(&pd[i], b);
-            }
-        }
-    } else {
-        __syncthreads();
-        for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-            if (n > 0) {
-                if constexpr (HALF) {
-                    // tile row j is file j: its guessed replica's row of g
-                    auto row = [&](int j) __attribute__((always_inline)) -> int64_t {
-                        const uint32_t q = j < f ? nib(j) : 0u;
-                        if (!(q & 8u)) return -1;
-                        return IND ? (int64_t)rt[j * R + (q & 7)] : (int64_t)j * R + (q & 7);
-                    };
-                    select_half_tile<T, G, RPI>(tile, hist, (int)half_pair_rows(f, T, FILL), n,
-                                                t * T, d, out, tid - FILL, g, row);
-                } else {
-                    select_tile<T, G>(tile, hist, n, t * T, d, out, tid - FILL);
-                }
-            }
-            __syncthreads();
-            __syncthreads();
-        }
-    }
-    __syncthreads();
-    for (int64_t i = tid; i < f; i += kWsThreads) {
-        const uint32_t b = PDN ? ((pd[i >> 3] >> ((i & 7) * 4)) & 15u) : pd[i];
-        if (b) atomicOr(&pair_diff[i], b);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// median of the kept rows, warp-specialised like fused_ws_kernel: waves 0-7
-// stream the kept rows of tile t+1 (one row per kept file, through the row
-// list of the selection) into registers while waves 8-15 select on tile t.
-// Used by the two-pass path and after a wrong guess of the single pass.
-
-template <int SW>
-constexpr int mws_batch() { return SW >= 16 ? 4 : (SW < 6 ? SW : 6); }
-
-template <int T, int SW, bool HALF, int FILL>
-__global__ void __launch_bounds__(kWsThreads)
-median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restrict__ rows,
-                 const int32_t *__restrict__ n_sel, int64_t ntiles, float *__restrict__ out,
-                 TileMask mask) {
-    extern __shared__ uint32_t smem[];
-    constexpr int G = (kWsThreads - FILL) / T;   // selection lanes per column
-    constexpr int CPR = T / 4;           // float4 chunks per row segment
-    constexpr int RPI = FILL / CPR;      // rows per sweep of the streaming role
-    constexpr int B = mws_batch<SW>();   // sweeps per burst of loads
-    // key registers per sweep: 4 keys, or (HALF) 4 high halves packed in 2
-    constexpr int KW = HALF ? 2 : 4;
-    static_assert(!HALF || (SW % 2 == 0 && RPI == half_rpi(T, FILL)), "half-key sweeps");
-    const int n = *n_sel;
-    if (n <= 0) return;                  // uniform: no workgroup reaches a barrier
-    const int64_t hwords = HALF ? half_hist_words(T) : hist_words(T);
-    uint32_t *hist = smem;
-    uint32_t *tile = smem + hwords;
-    int32_t *rl = reinterpret_cast<int32_t *>(tile + (HALF ? half_tile_words(n, T, FILL)
-                                                           : (int64_t)n * T));   // [n] kept rows
-    const int tid = threadIdx.x;
-    for (int i = tid; i < n; i += kWsThreads) rl[i] = rows[i];
-    for (int i = tid; i < hwords; i += kWsThreads) hist[i] = 0u;
-    __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (wave < FILL / 64) {
-        const int cq = tid % CPR, j0 = tid / CPR;
-        uint32_t keys[SW][KW];
-        // one 16-byte chunk of kept row j (a lane past the last kept row
-        // re-reads row 0, which is never put; past the end of the rows it
-        // re-reads the row's last chunk, whose median is never written)
-        auto load_row = [&](int64_t t, int x) __attribute__((always_inline)) {
-            const int64_t col = min(t * T + 4 * cq, d - 4);
-            int j = j0 + x * RPI < n ? j0 + x * RPI : 0;
-            asm volatile("" : "+v"(j));   // row address recomputed per tile
-            return load_stream(g + (int64_t)rl[j] * d + col);
-        };
-        auto to_keys = [&](int x, uint4 q) __attribute__((always_inline)) {
-            if constexpr (HALF) {
-                // high key halves; 0xFFFF past the last kept row
-                const bool keep = j0 + x * RPI < n;
-                keys[x][0] = keep ? pack_high(to_key(q.x), to_key(q.y)) : 0xFFFFFFFFu;
-                keys[x][1] = keep ? pack_high(to_key(q.z), to_key(q.w)) : 0xFFFFFFFFu;
-            } else {
-                keys[x][0] = to_key(q.x);
-                keys[x][1] = to_key(q.y);
-                keys[x][2] = to_key(q.z);
-                keys[x][3] = to_key(q.w);
-            }
-        };
-        uint4 c0;   // sweep 0 of the next tile, loaded early
-        auto stream_rest = [&](int64_t t) __attribute__((always_inline)) {
-            to_keys(0, c0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int xb = 1; xb < SW; xb += B) {
-                uint4 c[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) c[b] = load_row(t, xb + b);
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) to_keys(xb + b, c[b]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        auto put_tile = [&]() __attribute__((always_inline)) {
-            if constexpr (HALF) {
-                int no = n;   // opaque: compared per tile, not held per pair
-                asm volatile("" : "+s"(no));
-#pragma unroll
-                for (int k = 0; k < SW / 2; ++k) {
-                    int p = j0 + k * RPI;
-                    // opaque: the LDS addresses are recomputed per tile
-                    // instead of being held in registers for every pair
-                    asm volatile("" : "+v"(p));
-                    if (k * 2 * RPI < no) put_pairs<T, G>(tile, p, cq, keys[2 * k], keys[2 * k + 1]);
-                }
-            } else {
-#pragma unroll
-                for (int x = 0; x < SW; ++x) {
-                    int j = j0 + x * RPI;
-                    asm volatile("" : "+v"(j));   // as above
-                    if (j < n) put_keys<T, G>(tile, j, cq, keys[x]);
-                }
-            }
-        };
-        // the workgroup's tiles: t, then tn (whose sweep 0 is loaded early)
-        const int64_t G0 = gridDim.x;
-        int64_t t = mask.next(blockIdx.x, G0, ntiles);
-        int64_t tn = mask.next(t + G0, G0, ntiles);
-        if (t < ntiles) {
-            c0 = load_row(t, 0);
-            stream_rest(t);
-        }
-        if (tn < ntiles) c0 = load_row(tn, 0);
-        if (t < ntiles) put_tile();
-        __syncthreads();
-        while (t < ntiles) {
-            const int64_t tnn = mask.next(tn + G0, G0, ntiles);
-            if (tn < ntiles) stream_rest(tn);
-            if (tnn < ntiles) c0 = load_row(tnn, 0);
-            __syncthreads();
-            if (tn < ntiles) put_tile();
-            __syncthreads();
-            t = tn;
-            tn = tnn;
-        }
-    } else {
-        __syncthreads();
-        for (int64_t t = mask.next(blockIdx.x, gridDim.x, ntiles); t < ntiles;
-             t = mask.next(t + gridDim.x, gridDim.x, ntiles)) {
-            if constexpr (HALF) {
-                auto row = [&](int j) __attribute__((always_inline)) -> int64_t {
-                    return j < n ? (int64_t)rl[j] : -1;
-                };
-                // FILL = 512: RPI = 4G, so every lane holds the same number of
-                // words, at most 2 SW
-                constexpr int REG = (FILL == kWsFill && RPI == 4 * G) ? 2 * SW : 0;
-                select_half_tile<T, G, RPI, REG>(tile, hist, (int)half_pair_rows(n, T, FILL), n,
-                                                 t * T, d, out, tid - FILL, g, row);
-            } else {
-                select_tile<T, G>(tile, hist, n, t * T, d, out, tid - FILL);
-            }
-            __syncthreads();
-            __syncthreads();
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2247,26 +1059,6 @@ hipError_t launch_select(const int32_t *subsets, const int8_t *vote, int64_t f, 
 
 namespace {
 
-// Warp-specialised plans.  Full keys: the widest tile (8..64 columns) whose
-// key block fits in LDS and whose rows fit the streaming role's registers
-// (at most 16 sweeps of 4 key registers).  Half keys, for many rows: a wider
-// tile (16..128 columns) with up to 32 sweeps of 2 key registers; taken
-// only when it is wider than the full-key tile, since below kHalfMinRows
-// rows a tile is streamed too quickly to hide the reads of the low halves.
-// Half keys try the even split of streaming and selecting waves first, then
-// 12 streaming waves and 4 selecting ones (kWsFillWide): 1.5x the rows per
-// sweep, so that thousands of rows fit the registers of a 32- or 64-column
-// tile.
-struct WsPlan {
-    int r = 3;
-    int T = 0;
-    int sweeps = 0;
-    bool half = false;
-    int fill = kWsFill;
-    bool rtg = false;   // row table read from global memory (not in LDS)
-};
-
-constexpr int kWsFillWide = 768;
 constexpr int64_t kHalfMinRows = 128;
 constexpr int64_t kHalfMaxRows = 60000;   // row numbers (with padding) fit 16 bits
 
@@ -2411,159 +1203,14 @@ WsPlan ws_plan(int64_t f, int r, bool vec, bool ind, bool full_keys = false) {
     return best;
 }
 
-// ---------------------------------------------------------------------------
-// The kernels built for each plan.  A launcher looks its kernel up here; a
-// plan with no entry is a planning error (reported by aspis_plan and the
-// launchers alike, never launched).
-
-using FusedWsFn = void (*)(const float *, const int32_t *, int64_t, int64_t, const int32_t *,
-                           const int32_t *, const int32_t *, int64_t, uint32_t *, float *);
-using MedianWsFn = void (*)(const float *, int64_t, const int32_t *, const int32_t *, int64_t,
-                            float *, TileMask);
+}  // namespace
 
 FusedWsFn fused_ws_fn(const WsPlan &p, bool ind) {
-    const int key = p.T * 1000 + p.sweeps * 10 + (p.half ? 1 : 0);
-#define ASPIS_KEY(TT, SWW, HH) TT * 1000 + SWW * 10 + (HH ? 1 : 0)
-    if (p.r == 5) {
-        // five replicas a file: half keys, file-major, even split
-        if (ind || !p.half || p.fill != kWsFill || p.rtg) return nullptr;
-        switch (key) {
-#define ASPIS_FWS5(TT, SWW) \
-    case ASPIS_KEY(TT, SWW, true): return &fused_ws_kernel<TT, 5, SWW, false, true, kWsFill, false>;
-            ASPIS_FWS5(128, 16)
-            ASPIS_FWS5(128, 30)
-            ASPIS_FWS5(128, 32)
-            ASPIS_FWS5(64, 16)
-            ASPIS_FWS5(64, 24)
-            ASPIS_FWS5(64, 32)
-            ASPIS_FWS5(32, 16)
-            ASPIS_FWS5(32, 24)
-            ASPIS_FWS5(32, 32)
-            ASPIS_FWS5(16, 16)
-            ASPIS_FWS5(16, 24)
-            ASPIS_FWS5(16, 32)
-#undef ASPIS_FWS5
-        default: return nullptr;
-        }
-    }
-    if (p.r != 3) return nullptr;
-    // file-major, or with the row table in LDS
-#define ASPIS_FWS(TT, SWW, HH)                                                  \
-    case ASPIS_KEY(TT, SWW, HH):                                                \
-        return ind ? &fused_ws_kernel<TT, 3, SWW, true, HH, kWsFill, false>     \
-                   : &fused_ws_kernel<TT, 3, SWW, false, HH, kWsFill, false>;
-    if (p.rtg) {
-        // row table read from global memory: wide split, half keys
-        if (!ind || !p.half || p.fill != kWsFillWide) return nullptr;
-        switch (key) {
-#define ASPIS_FWS_RTG(TT, SWW)  \
-    case ASPIS_KEY(TT, SWW, true): return &fused_ws_kernel<TT, 3, SWW, true, true, kWsFillWide, true>;
-            ASPIS_FWS_RTG(64, 24)
-            ASPIS_FWS_RTG(64, 32)
-            ASPIS_FWS_RTG(32, 24)
-            ASPIS_FWS_RTG(32, 32)
-#undef ASPIS_FWS_RTG
-        default: return nullptr;
-        }
-    }
-    if (p.fill == kWsFillWide) {
-        // wide split: half keys, file-major only
-        if (ind || !p.half) return nullptr;
-        switch (key) {
-#define ASPIS_FWS_WIDE(TT, SWW) \
-    case ASPIS_KEY(TT, SWW, true): return &fused_ws_kernel<TT, 3, SWW, false, true, kWsFillWide, false>;
-            ASPIS_FWS_WIDE(64, 24)
-            ASPIS_FWS_WIDE(64, 32)
-            ASPIS_FWS_WIDE(32, 24)
-            ASPIS_FWS_WIDE(32, 32)
-#undef ASPIS_FWS_WIDE
-        default: return nullptr;
-        }
-    }
-    if (p.fill != kWsFill) return nullptr;
-    if (p.half && p.T == 32 && p.sweeps == 36)   // no room for a row table in LDS
-        return ind ? nullptr : &fused_ws_kernel<32, 3, 36, false, true, kWsFill, false>;
-    switch (key) {
-#define ASPIS_FWS_FULL(TT)    \
-    ASPIS_FWS(TT, 2, false)   \
-    ASPIS_FWS(TT, 4, false)   \
-    ASPIS_FWS(TT, 8, false)   \
-    ASPIS_FWS(TT, 12, false)  \
-    ASPIS_FWS(TT, 16, false)
-#define ASPIS_FWS_HALF(TT)    \
-    ASPIS_FWS(TT, 16, true)   \
-    ASPIS_FWS(TT, 24, true)   \
-    ASPIS_FWS(TT, 32, true)
-        ASPIS_FWS_FULL(64)
-        ASPIS_FWS_FULL(32)
-        ASPIS_FWS_FULL(16)
-        ASPIS_FWS_FULL(8)
-        ASPIS_FWS(128, 8, true)
-        ASPIS_FWS(128, 16, true)
-        ASPIS_FWS(128, 24, true)
-        ASPIS_FWS(128, 26, true)
-        ASPIS_FWS(128, 28, true)
-        ASPIS_FWS(128, 30, true)
-        ASPIS_FWS(128, 32, true)
-        ASPIS_FWS_HALF(64)
-        ASPIS_FWS_HALF(32)
-        ASPIS_FWS_HALF(16)
-#undef ASPIS_FWS_HALF
-#undef ASPIS_FWS_FULL
-    default: return nullptr;
-    }
-#undef ASPIS_FWS
+    if (p.r == 5) return ind ? nullptr : fused_ws_r5_fn(p);
+    return ind ? fused_ws_r3_table_fn(p) : fused_ws_r3_fn(p);
 }
 
-MedianWsFn median_ws_fn(const WsPlan &p) {
-    const int key = p.T * 1000 + p.sweeps * 10 + (p.half ? 1 : 0);
-#define ASPIS_MWS(TT, SWW, HH, FF) \
-    case ASPIS_KEY(TT, SWW, HH): return &median_ws_kernel<TT, SWW, HH, FF>;
-    if (p.fill == kWsFillWide) {
-        if (!p.half) return nullptr;
-        switch (key) {
-            ASPIS_MWS(64, 16, true, kWsFillWide)
-            ASPIS_MWS(64, 24, true, kWsFillWide)
-            ASPIS_MWS(64, 32, true, kWsFillWide)
-            ASPIS_MWS(32, 16, true, kWsFillWide)
-            ASPIS_MWS(32, 24, true, kWsFillWide)
-            ASPIS_MWS(32, 32, true, kWsFillWide)
-        default: return nullptr;
-        }
-    }
-    if (p.fill != kWsFill) return nullptr;
-    switch (key) {
-#define ASPIS_MWS_FULL(TT)               \
-    ASPIS_MWS(TT, 4, false, kWsFill)     \
-    ASPIS_MWS(TT, 8, false, kWsFill)     \
-    ASPIS_MWS(TT, 12, false, kWsFill)
-#define ASPIS_MWS_HALF(TT)               \
-    ASPIS_MWS(TT, 16, true, kWsFill)     \
-    ASPIS_MWS(TT, 24, true, kWsFill)     \
-    ASPIS_MWS(TT, 32, true, kWsFill)
-        ASPIS_MWS_FULL(64)
-        ASPIS_MWS(64, 16, false, kWsFill)
-        ASPIS_MWS_FULL(32)
-        ASPIS_MWS_FULL(16)
-        ASPIS_MWS_FULL(8)
-        ASPIS_MWS(128, 8, true, kWsFill)
-        ASPIS_MWS(128, 16, true, kWsFill)
-        ASPIS_MWS(128, 24, true, kWsFill)
-        ASPIS_MWS(128, 26, true, kWsFill)
-        ASPIS_MWS(128, 28, true, kWsFill)
-        ASPIS_MWS(128, 30, true, kWsFill)
-        ASPIS_MWS(128, 32, true, kWsFill)
-        ASPIS_MWS_HALF(64)
-        ASPIS_MWS_HALF(32)
-        ASPIS_MWS(32, 36, true, kWsFill)
-        ASPIS_MWS_HALF(16)
-#undef ASPIS_MWS_HALF
-#undef ASPIS_MWS_FULL
-    default: return nullptr;
-    }
-#undef ASPIS_MWS
-#undef ASPIS_KEY
-}
+namespace {
 
 KernelPlan ws_kernel_plan(int kind, const WsPlan &p, int64_t lds, int table) {
     KernelPlan k;

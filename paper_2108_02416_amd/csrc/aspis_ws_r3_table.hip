@@ -1,0 +1,59 @@
+// aspis_ws_r3_table.hip -- the warp-specialised single pass at r = 3, rows
+// through a row table.
+#include "aspis_ws.h"
+
+namespace aspis {
+
+FusedWsFn fused_ws_r3_table_fn(const WsPlan &p) {
+    if (p.r != 3) return nullptr;
+    if (p.rtg) {
+        // row table read from global memory: wide split, half keys
+        if (!p.half || p.fill != kWsFillWide) return nullptr;
+#define W(TT, SWW) \
+    case ws_key(TT, SWW, true): return &fused_ws_kernel<TT, 3, SWW, true, true, kWsFillWide, true>;
+        switch (ws_key(p.T, p.sweeps, p.half)) {
+            W(64, 24)
+            W(64, 32)
+            W(32, 24)
+            W(32, 32)
+        default: return nullptr;
+        }
+#undef W
+    }
+    // row table in LDS: even split (no 36-sweep tile leaves room for it)
+    if (p.fill != kWsFill) return nullptr;
+#define ASPIS_FWS(TT, SWW, HH) \
+    case ws_key(TT, SWW, HH): return &fused_ws_kernel<TT, 3, SWW, true, HH, kWsFill, false>;
+    switch (ws_key(p.T, p.sweeps, p.half)) {
+#define ASPIS_FWS_FULL(TT)    \
+    ASPIS_FWS(TT, 2, false)   \
+    ASPIS_FWS(TT, 4, false)   \
+    ASPIS_FWS(TT, 8, false)   \
+    ASPIS_FWS(TT, 12, false)  \
+    ASPIS_FWS(TT, 16, false)
+#define ASPIS_FWS_HALF(TT)    \
+    ASPIS_FWS(TT, 16, true)   \
+    ASPIS_FWS(TT, 24, true)   \
+    ASPIS_FWS(TT, 32, true)
+        ASPIS_FWS_FULL(64)
+        ASPIS_FWS_FULL(32)
+        ASPIS_FWS_FULL(16)
+        ASPIS_FWS_FULL(8)
+        ASPIS_FWS(128, 8, true)
+        ASPIS_FWS(128, 16, true)
+        ASPIS_FWS(128, 24, true)
+        ASPIS_FWS(128, 26, true)
+        ASPIS_FWS(128, 28, true)
+        ASPIS_FWS(128, 30, true)
+        ASPIS_FWS(128, 32, true)
+        ASPIS_FWS_HALF(64)
+        ASPIS_FWS_HALF(32)
+        ASPIS_FWS_HALF(16)
+#undef ASPIS_FWS_HALF
+#undef ASPIS_FWS_FULL
+    default: return nullptr;
+    }
+#undef ASPIS_FWS
+}
+
+}  // namespace aspis
