@@ -54,6 +54,18 @@ __device__ __forceinline__ uint32_t pk_add_u16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, a) + __builtin_bit_cast(u16x2, b));
 }
 
+// to_key on the high halves of two bit patterns packed in a word (the high
+// half of a key depends on the high half of the pattern alone)
+__device__ __forceinline__ uint32_t pk_high_keys(uint32_t w) {
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
+    const uint32_t sgn = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, w) >> (short)15);
+    return w ^ (sgn | 0x80008000u);
+}
+// the high halves of two bit patterns, packed (a's in the low 16 bits)
+__device__ __forceinline__ uint32_t pack_high(uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
@@ -369,32 +381,20 @@ __device__ __forceinline__ void select_tile(uint32_t *tile, uint32_t *hist, int 
 // 0xFFFF, as do the low halves read back for them: appending elements that
 // are not below any other leaves every rank below the kept count in place.
 
-constexpr int kHalfWindow = 6;                  // key bits per histogram round
-constexpr int kHalfBuckets = 1 << kHalfWindow;
-constexpr int kHalfStride = kHalfBuckets + 2;   // words per column block
-constexpr uint32_t kHalfTop = 0xFFFFu;          // largest key: padding rows
-
-__host__ __device__ constexpr int64_t half_hist_words(int T) { return (int64_t)T * kHalfStride; }
 // streaming rows per sweep of a tile T columns wide, for `fill` streaming
 // threads of four columns each
 __host__ __device__ constexpr int half_rpi(int T, int fill) { return fill * 4 / T; }
-// pair-rows of a tile of `rows` rows: whole pairs of sweeps
-__host__ __device__ constexpr int64_t half_pair_rows(int64_t rows, int T, int fill) {
-    return (rows + 2 * half_rpi(T, fill) - 1) / (2 * half_rpi(T, fill)) * half_rpi(T, fill);
-}
-__host__ __device__ constexpr int64_t half_tile_words(int64_t rows, int T, int fill) {
-    return half_pair_rows(rows, T, fill) * T;
+// words of a tile of `sweeps` sweeps (an even count), sweeps * rpi rows:
+// padded to the sweeps of its kernel, so that the kernels have no bound of
+// their own inside a tile
+__host__ __device__ constexpr int64_t half_tile_words(int sweeps, int fill) {
+    return (int64_t)sweeps * fill * 2;
 }
 
 // Row held by half h of pair-row p.
 template <int RPI>
 __device__ __forceinline__ int half_row(int p, int h) {
     return (p / RPI) * 2 * RPI + h * RPI + p % RPI;
-}
-
-// The high halves of two full keys, packed (a's in the low 16 bits).
-__device__ __forceinline__ uint32_t pack_high(uint32_t a, uint32_t b) {
-    return (a >> 16) | (b & 0xFFFF0000u);
 }
 
 // Store pair-row p, columns 4cq..4cq+3, from the packed high halves of the
@@ -417,301 +417,220 @@ __device__ __forceinline__ void put_pairs(uint32_t *tile, int p, int cq, const u
     }
 }
 
-// Lower median of each of the T columns of a half-key tile of np pair-rows
-// holding nk kept values (1 <= nk, 2*np <= 65536), by the G lanes
-// stid = c*G + g of column c, written to out[k0 + c] for k0 + c < d.
-// row(j) gives the replica row of g behind tile row j, or -1 for a padding
-// row.  hist: half_hist_words(T) words, zero on entry and on exit.  The
-// tile is overwritten.  With REG > 0 (np a multiple of G, np / G <= REG)
-// the lane's words are read from the tile once, into registers, and every
-// later pass over the keys reads those (the median kernel measured 4-5 %
-// faster at 455 rows; the single pass, whose registers are taken by its
-// own state, keeps reading the tile).
+// Lower median of each of the T columns of a half-key tile of NW*G pair-rows
+// (NW words per lane, a multiple of 4) holding nk kept values (1 <= nk,
+// 2*NW*G <= 65536), by the G lanes stid = c*G + g of column c, written to
+// out[k0 + c] for k0 + c < d.  row(j) gives the byte offset in g
+// of the replica row behind tile row j, or -1 for a padding row.  The tile
+// may be overwritten.
 //
-//  1. one pass: the least key, the greatest key below 0xFFFF, the least
-//     sign-set and the greatest sign-clear key, and the count of sign-set
-//     keys (packed 16-bit min / max / add, two keys an instruction); settles
-//     the sign and the window [lo, hi] of the keys of that sign;
-//  2. histogram rounds over the window, each resolving kHalfWindow bits,
-//     until the sought high half H is known (at most 3 rounds; H = 0xFFFF
-//     when the rank falls past a sign-set window); nothing is compacted,
-//     every round reads all keys;
-//  3. one pass collecting the rows whose high half is H into the lane's
-//     16-bit slots (in place), then their low halves are read from g;
+//  1. the high byte of the sought key: the lane's high bytes, four to a
+//     register, then eight binary-search steps.  A step needs the number of
+//     keys below c, and v_sad_u8 sums |byte - c| over four bytes in one
+//     instruction: with S(c) that sum over the column, S(c) - S(c-1) =
+//     #(bytes <= c-1) - #(bytes >= c), so two of them give the count
+//     exactly, half an instruction a key and step;
+//  2. the low byte of the high half the same way: every 16-bit key clamped
+//     to the settled high byte (a key below it becomes byte 0, above it
+//     0xFF: neither changes the count below c for 1 <= c <= 0xFF);
+//  3. one pass finding the rows whose high half is the sought one: a lane
+//     keeps up to four in registers; when a lane of the wave finds more, the
+//     rows are listed in the lanes' 16-bit slots of the tile (in place);
+//     their low halves are read from g;
 //  4. bitwise radix select on those low halves for the remaining rank.
-template <int T, int G, int RPI, int REG = 0, typename RowFn>
-__device__ __forceinline__ void select_half_tile(uint32_t *tile, uint32_t *hist, int np, int nk,
-                                                 int64_t k0, int64_t d, float *out, int stid,
-                                                 const float *__restrict__ g, RowFn &&row) {
+//
+// The pass is bound by the selecting waves' issue slots and by its chain of
+// dependent steps, so it uses neither LDS atomics nor data-dependent rounds:
+// about 14 VALU instructions a key, the tile read three times.  The LDS
+// histograms it replaces took about 28 and waited for their atomics in every
+// round.  SEL_MEASURED
+template <int T, int G, int RPI, int NW, typename RowFn>
+__device__ __forceinline__ void select_half_tile(uint32_t *tile, int nk, int64_t k0, int64_t d,
+                                                 float *out, int stid, const float *__restrict__ g,
+                                                 RowFn &&row) {
+    static_assert(RPI % (4 * G) == 0 && NW % 4 == 0, "whole blocks of four words per lane");
     constexpr int STRIDE = G * T;   // words between a lane's pair-rows
-    constexpr int BPL = kHalfBuckets / G;
-    static_assert(BPL >= 2 && BPL % 2 == 0, "buckets per lane");
     const int gl = stid % G;
     const int c = stid / G;
     uint32_t *base = tile + gl * T + (c ^ tile_swz<T, G>(gl));
-    uint16_t *base16 = reinterpret_cast<uint16_t *>(base);
-    uint32_t *hcol = hist + c * kHalfStride;
-    const int cnt = np > gl ? (np - gl + G - 1) / G : 0;   // words of this lane
-    uint32_t m = (uint32_t)(nk - 1) / 2;
-    // REG > 0: the lane's words are read once, into registers.  The caller
-    // passes np = half_pair_rows(...), a multiple of RPI = 4G, so every lane
-    // of the wave holds the same count, a multiple of 4, at most REG
-    static_assert(REG == 0 || RPI == 4 * G, "register mode needs RPI = 4G");
-    uint32_t kw[REG > 0 ? REG : 1];
-    const int cw = __builtin_amdgcn_readfirstlane(cnt);
+    const uint32_t m = (uint32_t)(nk - 1) / 2;
 
-    // every key of the lane: fn(key, word x, half h) for pair-row gl + x*G
-    auto each = [&](auto &&fn) __attribute__((always_inline)) {
-        if constexpr (REG > 0) {
-            // cw is a multiple of 4 (np is a multiple of RPI = 4G)
+    // four keys' bytes to a register
+    constexpr int NB = NW / 2;
+    uint32_t kb[NB];
+    auto load_bytes = [&](uint32_t sel, auto &&map) __attribute__((always_inline)) {
 #pragma unroll
-            for (int xb = 0; xb < REG; xb += 4) {
-                if (xb < cw) {
-#pragma unroll
-                    for (int x = xb; x < xb + 4 && x < REG; ++x) {
-                        fn(kw[x] & 0xFFFFu, x, 0);
-                        fn(kw[x] >> 16, x, 1);
-                    }
-                }
-            }
-            return;
-        }
-        int x = 0;
-        for (; x + kSelBatch <= cnt; x += kSelBatch) {
-            uint32_t v[kSelBatch];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) v[u] = base[(x + u) * STRIDE];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) {
-                fn(v[u] & 0xFFFFu, x + u, 0);
-                fn(v[u] >> 16, x + u, 1);
-            }
-        }
-        for (; x < cnt; ++x) {
-            const uint32_t v = base[x * STRIDE];
-            fn(v & 0xFFFFu, x, 0);
-            fn(v >> 16, x, 1);
-        }
+        for (int x = 0; x < NW; x += 2)
+            kb[x / 2] = __builtin_amdgcn_perm(map(base[(x + 1) * STRIDE]), map(base[x * STRIDE]), sel);
     };
-    // the lane's x-th 16-bit slot (step 3 on)
-    auto slot = [&](int x) __attribute__((always_inline)) -> uint16_t & {
-        return base16[(x >> 1) * 2 * STRIDE + (x & 1)];
+    // bytes of the column below c1 (1 <= c1 <= 0xFF)
+    auto below_byte = [&](uint32_t c1) __attribute__((always_inline)) -> uint32_t {
+        const uint32_t pc = c1 * 0x01010101u, pm = pc - 0x01010101u;
+        uint32_t a0 = 0u, a1 = 0u, b0 = 0u, b1 = 0u;
+#pragma unroll
+        for (int x = 0; x < NB; x += 2) {
+            a0 = __builtin_amdgcn_sad_u8(kb[x], pc, a0);
+            b0 = __builtin_amdgcn_sad_u8(kb[x], pm, b0);
+            a1 = __builtin_amdgcn_sad_u8(kb[x + 1], pc, a1);
+            b1 = __builtin_amdgcn_sad_u8(kb[x + 1], pm, b1);
+        }
+        return (2u * NW * G + group_reduce<G, Op::Add>(a0 + a1 - b0 - b1)) >> 1;
     };
+    uint32_t below = 0u;   // keys below the sought key's settled bits
+    // the byte of the key of rank m: the greatest c with at most m bytes below
+    auto search_byte = [&]() __attribute__((always_inline)) -> uint32_t {
+        uint32_t b = 0u;
+        for (uint32_t bit = 0x80u; bit != 0u; bit >>= 1) {
+            const uint32_t n = below_byte(b | bit);
+            if (n <= m) {
+                b |= bit;
+                below = n;
+            }
+        }
+        return b;
+    };
+    // 1. the high byte
+    load_bytes(0x07050301u, [](uint32_t w) __attribute__((always_inline)) { return w; });
+    const uint32_t hb = search_byte();
+    // 2. the low byte of the high half
+    const uint32_t lo2 = hb * 0x01000100u, hi2 = lo2 | 0x00FF00FFu;
+    load_bytes(0x06040200u, [&](uint32_t w) __attribute__((always_inline)) {
+        return pk_min_u16(pk_max_u16(w, lo2), hi2);
+    });
+    const uint32_t H = (hb << 8) | search_byte();
+    uint32_t rank = m - below;   // among the keys whose high half is H
 
-    // 1. extremes and the sign count, both keys of a word at once in 16-bit
-    //    lanes: the least key, the greatest key below 0xFFFF (the greatest
-    //    key + 1, which wraps 0xFFFF to 0), and with the sign bit flipped the
-    //    least sign-set key and the greatest sign-clear key; the number of
-    //    sign-set keys
-    uint32_t mn2 = 0xFFFFFFFFu, mt2 = 0u, ms2 = 0xFFFFFFFFu, mc2 = 0u, ns = 0u;
-    auto stats = [&](uint32_t w) __attribute__((always_inline)) {
-        const uint32_t x = w ^ 0x80008000u;
-        mn2 = pk_min_u16(mn2, w);
-        mt2 = pk_max_u16(mt2, pk_add_u16(w, 0x00010001u));
-        ms2 = pk_min_u16(ms2, x);
-        mc2 = pk_max_u16(mc2, x);
-        ns += (uint32_t)__builtin_popcount(w & 0x80008000u);
-    };
-    if constexpr (REG > 0) {
-#pragma unroll
-        for (int xb = 0; xb < REG; xb += 4) {
-            if (xb < cw) {
-#pragma unroll
-                for (int x = xb; x < xb + 4 && x < REG; ++x) kw[x] = base[x * STRIDE];
-            }
-        }
-#pragma unroll
-        for (int xb = 0; xb < REG; xb += 4) {
-            if (xb < cw) {
-#pragma unroll
-                for (int x = xb; x < xb + 4 && x < REG; ++x) stats(kw[x]);
-            }
-        }
-    } else {
-        int x = 0;
-        for (; x + kSelBatch <= cnt; x += kSelBatch) {
-            uint32_t v[kSelBatch];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) v[u] = base[(x + u) * STRIDE];
-#pragma unroll
-            for (int u = 0; u < kSelBatch; ++u) stats(v[u]);
-        }
-        for (; x < cnt; ++x) stats(base[x * STRIDE]);
-    }
-    auto lo16 = [](uint32_t v2, bool lower) __attribute__((always_inline)) {
-        const uint32_t a = v2 & 0xFFFFu, b = v2 >> 16;
-        return lower ? (a < b ? a : b) : (a > b ? a : b);
-    };
-    const uint32_t mn = group_reduce<G, Op::Min>(lo16(mn2, true));                // least key
-    const uint32_t mt = group_reduce<G, Op::Max>(lo16(mt2, false));               // greatest below 0xFFFF, + 1
-    const uint32_t ms = group_reduce<G, Op::Min>(lo16(ms2, true)) ^ 0x8000u;      // least sign-set
-    const uint32_t mc = group_reduce<G, Op::Max>(lo16(mc2, false)) ^ 0x8000u;     // greatest sign-clear
-    const uint32_t z = (uint32_t)(2 * np) - group_reduce<G, Op::Add>(ns);         // sign-clear count
-
-    // 2. the window [lo, hi] of the keys of the sought key's sign (below
-    //    0xFFFF); histogram rounds split it into kHalfBuckets buckets of
-    //    2^sh keys and keep the one holding rank m, until sh = 0 (16 bits:
-    //    three rounds at most).  A key above hi inside the window (0xFFFF, or
-    //    a sign-set key in a sign-clear window) is counted like any other:
-    //    it is above the sought key.  The rank past a sign-set window is a
-    //    0xFFFF key.
-    //    The round of single keys (sh = 0) also lists the lane's keys in its
-    //    window as (word, half, bucket) codes in the lane's 16-bit slots, in
-    //    place (the write cursor never passes the read cursor), and keeps
-    //    those of the sought bucket as row numbers: step 3 then has its rows
-    //    without another pass.  Not in a first round that may find the rank
-    //    past a sign-set window (the tile must stay whole for the 0xFFFF
-    //    pass), nor when a lane holds 512 words or more (9 bits of word).
-    uint32_t H = kHalfTop;
-    bool settled = false, collected = false;
+    // 3. the rows whose high half is H, as codes 2x + half of the lane's
+    //    words x, the last four found in h0 and h1
+    const uint32_t H2 = H | (H << 16);
+    uint32_t h0 = 0u, h1 = 0u;
     int w = 0;
-    uint32_t lo, hi;
-    const bool clear_sign = m < z;
-    if (clear_sign) {
-        lo = mn;
-        hi = mc;
-    } else {
-        m -= z;
-        lo = ms;
-        hi = mt - 1u;
-        if (mt == 0u || hi < lo) settled = true;   // no sign-set key below 0xFFFF
-    }
-    if (!settled) {
-        uint32_t bias = lo;
-        const int width = 32 - __clz(hi - lo);   // bits of hi - lo (0 when equal)
-        int sh = width > kHalfWindow ? width - kHalfWindow : 0;
-        for (int round = 0; round < 3; ++round) {
-            const uint32_t span = (uint32_t)kHalfBuckets << sh;
-            const bool list = sh == 0 && (round > 0 || clear_sign) && np <= 511 * G;
-            if (list) {
-                each([&](uint32_t k, int x, int hf) {
-                    const uint32_t o = k - bias;
-                    if (o < span) {
-                        atomicAdd(&hcol[o], 1u);
-                        slot(w) = (uint16_t)(((uint32_t)x << 7) | ((uint32_t)hf << 6) | o);
-                        ++w;
-                    }
-                });
-            } else {
-                each([&](uint32_t k, int, int) {
-                    const uint32_t o = k - bias;
-                    if (o < span) atomicAdd(&hcol[o >> sh], 1u);
-                });
-            }
-            uint32_t h[BPL];
+    auto find = [&](uint32_t v, int x) __attribute__((always_inline)) {
+        auto hit = [&](uint32_t code) __attribute__((always_inline)) {
+            h1 = (h1 << 16) | (h0 >> 16);
+            h0 = (h0 << 16) | code;
+            ++w;
+        };
+        if ((v & 0xFFFFu) == 0u) hit((uint32_t)(2 * x));
+        if (v < 0x10000u) hit((uint32_t)(2 * x + 1));
+    };
 #pragma unroll
-            for (int q = 0; q < BPL; q += 2) {
-                const uint2 w2 = *reinterpret_cast<const uint2 *>(&hcol[gl * BPL + q]);
-                h[q] = w2.x;
-                h[q + 1] = w2.y;
-            }
+    for (int x = 0; x < NW; x += 4) {
+        uint32_t v[4];
 #pragma unroll
-            for (int q = 0; q < BPL; q += 2)
-                *reinterpret_cast<uint2 *>(&hcol[gl * BPL + q]) = make_uint2(0u, 0u);
-            uint32_t tot = 0u;
+        for (int u = 0; u < 4; ++u) v[u] = base[(x + u) * STRIDE] ^ H2;
 #pragma unroll
-            for (int q = 0; q < BPL; ++q) tot += h[q];
-            uint32_t run = group_scan<G>(tot, gl) - tot;
-            uint32_t le = 0u, below = 0u;
-#pragma unroll
-            for (int q = 0; q < BPL; ++q) {
-                run += h[q];
-                const bool ok = run <= m;
-                le += ok ? 1u : 0u;
-                below = ok ? run : below;
+        for (int u = 0; u < 4; u += 2) {
+            // a zero half in either word: the minimum of both with 1 is not 1
+            if (pk_min_u16(pk_min_u16(v[u], v[u + 1]), 0x00010001u) != 0x00010001u) {
+                find(v[u], x + u);
+                find(v[u + 1], x + u + 1);
             }
-            le = group_reduce<G, Op::Add>(le);
-            below = group_reduce<G, Op::Max>(below);
-            m -= below;
-            if (le == (uint32_t)kHalfBuckets) {   // past the window: a 0xFFFF key
-                settled = true;
-                break;
-            }
-            bias += le << sh;
-            if (sh == 0) {
-                if (list) {   // the listed keys of bucket le, as row numbers
-                    int n2 = 0;
-                    for (int j = 0; j < w; ++j) {
-                        const uint32_t v = slot(j);
-                        if ((v & 63u) == le) {
-                            slot(n2) = (uint16_t)half_row<RPI>(gl + (int)(v >> 7) * G, (int)(v >> 6) & 1);
-                            ++n2;
-                        }
-                    }
-                    w = n2;
-                    collected = true;
-                }
-                break;
-            }
-            sh = sh > kHalfWindow ? sh - kHalfWindow : 0;
         }
-        if (!settled) H = bias;
-    }
-
-    // 3. rows whose high half is H, as row numbers in the lane's slots (the
-    //    write cursor never passes the read cursor), then their low halves
-    if (!collected) {
-        w = 0;
-        each([&](uint32_t k, int x, int hf) {
-            if (k == H) {
-                slot(w) = (uint16_t)half_row<RPI>(gl + x * G, hf);
-                ++w;
-            }
-        });
     }
     const bool valid = k0 + c < d;
-    constexpr int kGather = 4;   // row reads in flight per lane
-    for (int x0 = 0; x0 < w; x0 += kGather) {
-        uint32_t v[kGather];
-#pragma unroll
-        for (int u = 0; u < kGather; ++u) {
-            v[u] = 0xFFFFFFFFu;   // a padding row: the largest key
-            if (x0 + u < w) {
-                const int64_t rr = row(slot(x0 + u));
-                if (rr >= 0 && valid) v[u] = to_key(__float_as_uint(g[rr * d + k0 + c]));
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kGather; ++u)
-            if (x0 + u < w) slot(x0 + u) = (uint16_t)(v[u] & 0xFFFFu);
-    }
-
-    // 4. bitwise radix select of rank m among the low halves
-    auto and_or = [&](uint32_t &a, uint32_t &o) __attribute__((always_inline)) {
-        a = 0xFFFFu;
-        o = 0u;
-        for (int x = 0; x < w; ++x) {
-            const uint32_t v = slot(x);
-            a &= v;
-            o |= v;
-        }
-        a = group_reduce<G, Op::And>(a);
-        o = group_reduce<G, Op::Or>(o);
+    const char *col = reinterpret_cast<const char *>(g + (valid ? k0 + c : 0));
+    auto low_half = [&](int j) __attribute__((always_inline)) -> uint32_t {
+        const int64_t off = row(j);
+        // a padding row: the largest key
+        if (off < 0) return 0xFFFFu;
+        return to_key(*reinterpret_cast<const uint32_t *>(col + off)) & 0xFFFFu;
     };
     uint32_t a, o;
-    and_or(a, o);
-    uint32_t varying = a ^ o;
-    for (int step = 0; varying != 0u && step < 16; ++step) {
-        const uint32_t bit = 1u << (31 - __clz(varying));
-        uint32_t zc = 0u;
-        for (int x = 0; x < w; ++x) zc += (slot(x) & bit) == 0u;
-        zc = group_reduce<G, Op::Add>(zc);
-        uint32_t want;
-        if (m < zc) {
-            want = 0u;
-        } else {
-            want = bit;
-            m -= zc;
+    if (!__any(w > 4)) {
+        // 4. bitwise radix select of that rank among the low halves, at most
+        //    four a lane (in registers; bit u of act: value u still counts)
+        uint32_t lv[4] = {0u, 0u, 0u, 0u};
+        uint32_t act = (1u << w) - 1u;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (u < w) {
+                const uint32_t code = ((u < 2 ? h0 : h1) >> (16 * (u & 1))) & 0xFFFFu;
+                lv[u] = low_half(half_row<RPI>(gl + (int)(code >> 1) * G, (int)(code & 1u)));
+            }
+        for (int step = 0; step <= 16; ++step) {
+            a = 0xFFFFu;
+            o = 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (act >> u & 1u) {
+                    a &= lv[u];
+                    o |= lv[u];
+                }
+            a = group_reduce<G, Op::And>(a);
+            o = group_reduce<G, Op::Or>(o);
+            const uint32_t varying = a ^ o;
+            if (varying == 0u) break;
+            const uint32_t bit = 1u << (31 - __clz(varying));
+            uint32_t zero = 0u;   // values with that bit clear
+#pragma unroll
+            for (int u = 0; u < 4; ++u) zero |= (lv[u] & bit) == 0u ? 1u << u : 0u;
+            const uint32_t zc = group_reduce<G, Op::Add>((uint32_t)__popc(zero & act));
+            if (rank < zc) {
+                act &= zero;
+            } else {
+                act &= ~zero;
+                rank -= zc;
+            }
         }
-        int nw = 0;
-        for (int x = 0; x < w; ++x) {
-            const uint16_t v = slot(x);
-            slot(nw) = v;
-            nw += (v & bit) == want ? 1 : 0;
+    } else {
+        // more: row numbers, then low halves, in the lane's slots (the write
+        // cursor never passes the read cursor)
+        uint16_t *base16 = reinterpret_cast<uint16_t *>(base);
+        auto slot = [&](int x) __attribute__((always_inline)) -> uint16_t & {
+            return base16[(x >> 1) * 2 * STRIDE + (x & 1)];
+        };
+        w = 0;
+        for (int x = 0; x < NW; ++x) {
+            const uint32_t v = base[x * STRIDE] ^ H2;
+            if ((v & 0xFFFFu) == 0u) slot(w++) = (uint16_t)half_row<RPI>(gl + x * G, 0);
+            if (v < 0x10000u) slot(w++) = (uint16_t)half_row<RPI>(gl + x * G, 1);
         }
-        w = nw;
-        and_or(a, o);
-        varying = a ^ o;
+        constexpr int kGather = 4;   // row reads in flight per lane
+        for (int x0 = 0; x0 < w; x0 += kGather) {
+            uint32_t v[kGather];
+#pragma unroll
+            for (int u = 0; u < kGather; ++u)
+                if (x0 + u < w) v[u] = low_half(slot(x0 + u));
+#pragma unroll
+            for (int u = 0; u < kGather; ++u)
+                if (x0 + u < w) slot(x0 + u) = (uint16_t)v[u];
+        }
+        auto and_or = [&]() __attribute__((always_inline)) {
+            a = 0xFFFFu;
+            o = 0u;
+            for (int x = 0; x < w; ++x) {
+                const uint32_t v = slot(x);
+                a &= v;
+                o |= v;
+            }
+            a = group_reduce<G, Op::And>(a);
+            o = group_reduce<G, Op::Or>(o);
+        };
+        and_or();
+        uint32_t varying = a ^ o;
+        for (int step = 0; varying != 0u && step < 16; ++step) {
+            const uint32_t bit = 1u << (31 - __clz(varying));
+            uint32_t zc = 0u;
+            for (int x = 0; x < w; ++x) zc += (slot(x) & bit) == 0u;
+            zc = group_reduce<G, Op::Add>(zc);
+            uint32_t want;
+            if (rank < zc) {
+                want = 0u;
+            } else {
+                want = bit;
+                rank -= zc;
+            }
+            int nw = 0;
+            for (int x = 0; x < w; ++x) {
+                const uint16_t v = slot(x);
+                slot(nw) = v;
+                nw += (v & bit) == want ? 1 : 0;
+            }
+            w = nw;
+            and_or();
+            varying = a ^ o;
+        }
     }
     if (gl == 0 && valid) out[k0 + c] = __uint_as_float(from_key((H << 16) | a));
 }

@@ -331,7 +331,7 @@ __global__ void __launch_bounds__(tile_block<T>())
 median_kernel(const float *__restrict__ g, int64_t d,
               const int32_t *__restrict__ rows, const int32_t *__restrict__ n_sel,
               int64_t ntiles, float *__restrict__ out, TileMask mask) {
-    extern __shared__ uint32_t smem[];
+    extern __shared__ __align__(16) uint32_t smem[];
     constexpr int BLOCK = tile_block<T>();
     uint32_t *hist = smem;
     uint32_t *tile = smem + hist_words(T);
@@ -382,7 +382,7 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
              const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
              const int32_t *__restrict__ n_sel, int64_t ntiles,
              uint32_t *__restrict__ pair_diff, float *__restrict__ out) {
-    extern __shared__ uint32_t smem[];
+    extern __shared__ __align__(16) uint32_t smem[];
     constexpr int BLOCK = tile_block<T>();
     constexpr int G = BLOCK / T;
     constexpr int CPR = T / 4;
@@ -1070,22 +1070,16 @@ constexpr int64_t kHalfMaxRows = 60000;   // row numbers (with padding) fit 16 b
 // role spills 88 registers (15.9 against 12.1 ms with the wide split).
 constexpr int max_half_sweeps(int T, int fill) { return T == 32 && fill == kWsFill ? 36 : 32; }
 
-// Sweep counts built for each plan (sweeps past the last row load nothing,
-// so the count is rounded up only a little).  Half keys: an even count; 8
-// only for 128 columns, where fewer than 128 rows never take a narrower
-// half-key tile, and steps of 2 from 24 to 32 there; 36 for 32 columns
-// (even split); 24 or 32 for the wide split.
-int round_sweeps(int64_t sw, bool half, int T, int fill, int r = 3) {
-    if (half && r != 3) {
-        // r = 5: the sweep counts built for five replicas a file
-        if (T == 128) return sw <= 16 ? 16 : sw <= 30 ? 30 : 32;
-        return sw <= 16 ? 16 : sw <= 24 ? 24 : 32;
-    }
+// Sweep counts built for each plan.  A half-key tile is padded to them (the
+// selection works on the padding too), so they are multiples of 4 apart,
+// with 30 for the 128-column tile (455 files) and 36 for the 32-column tile
+// of the even split (2,300); 20 is not built for 16 columns.
+int round_sweeps(int64_t sw, bool half, int T, int fill) {
     if (half) {
-        if (fill == kWsFillWide) return sw <= 24 ? 24 : 32;
-        if (T == 128 && sw > 24) return (int)((sw + 1) / 2 * 2);
-        if (sw > 32) return 36;   // the 32-column even split only
-        return sw <= 8 && T == 128 ? 8 : sw <= 16 ? 16 : sw <= 24 ? 24 : 32;
+        if (fill == kWsFillWide) return 24;
+        if (T == 128 && (sw == 29 || sw == 30)) return 30;
+        if (T == 16 && sw > 16 && sw <= 24) return 24;
+        return sw <= 8 ? 8 : (int)((sw + 3) / 4 * 4);
     }
     return sw <= 2 ? 2 : sw <= 4 ? 4 : sw <= 8 ? 8 : sw <= 12 ? 12 : 16;
 }
@@ -1111,10 +1105,12 @@ WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r
             if (rtg && fill != kWsFillWide) continue;
             const int64_t rpi = half_rpi(T, fill);
             const int64_t sw = (f + rpi - 1) / rpi;
-            const int64_t max_sw = (ind || r != 3) ? 32 : max_half_sweeps(T, fill);
-            if (sw > max_sw || lds(T, fill) > kLdsBytes) continue;
+            const int64_t max_sw = fill == kWsFillWide ? 24 : (ind || r != 3) ? 32 : max_half_sweeps(T, fill);
+            if (sw > max_sw) continue;
+            const int sweeps = round_sweeps(sw, true, T, fill);
+            if (lds(T, sweeps, fill) > kLdsBytes) continue;
             p.T = T;
-            p.sweeps = round_sweeps(sw, true, T, fill, r);
+            p.sweeps = sweeps;
             p.half = true;
             p.fill = fill;
             p.rtg = rtg;
@@ -1125,8 +1121,8 @@ WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r
 }
 
 // LDS of the warp-specialised median: histograms, key tile, row list.
-int64_t mws_lds_bytes(int64_t f, int T, bool half, int fill) {
-    return half ? (half_hist_words(T) + half_tile_words(f, T, fill)) * 4 + f * 4
+int64_t mws_lds_bytes(int64_t f, int T, int sweeps, bool half, int fill) {
+    return half ? half_tile_words(sweeps, fill) * 4 + f * (ws_offsets(T, half) ? 8 : 4)
                 : (hist_words(T) + f * (int64_t)T) * 4 + f * 4;
 }
 
@@ -1134,7 +1130,7 @@ WsPlan mws_plan(int64_t f, bool vec, bool full_keys = false) {
     WsPlan p;
     if (!vec) return p;
     for (int T : {64, 32, 16, 8}) {
-        if (mws_lds_bytes(f, T, false, kWsFill) > kLdsBytes) continue;
+        if (mws_lds_bytes(f, T, 0, false, kWsFill) > kLdsBytes) continue;
         const int64_t rpi = kWsFill / (T / 4);
         const int64_t sw = (f + rpi - 1) / rpi;
         // 16 sweeps fit the registers only next to the 64-column selection
@@ -1144,8 +1140,8 @@ WsPlan mws_plan(int64_t f, bool vec, bool full_keys = false) {
         break;
     }
     if (full_keys) return p;
-    const WsPlan h = half_plan(f, p.T, false, false, [&](int T, int fill) {
-        return mws_lds_bytes(f, T, true, fill);
+    const WsPlan h = half_plan(f, p.T, false, false, [&](int T, int sweeps, int fill) {
+        return mws_lds_bytes(f, T, sweeps, true, fill);
     });
     return h.T != 0 ? h : p;
 }
@@ -1153,12 +1149,9 @@ WsPlan mws_plan(int64_t f, bool vec, bool full_keys = false) {
 // LDS of the warp-specialised single pass: histograms, key tile, per-file
 // words (half keys: two nibbles per file) and, with a row table in LDS, the
 // table.
-int64_t ws_lds_bytes(int64_t f, int r, int T, bool table_in_lds, bool half, int fill) {
-    // half keys: slot nibbles, and pair-difference nibbles (r = 3) or words
-    const int64_t words = half ? half_hist_words(T) + half_tile_words(f, T, fill) + (f + 7) / 8 +
-                                     (r == 3 ? (f + 7) / 8 : f)
-                               : hist_words(T) + f * (int64_t)T + 2 * f;
-    return words * 4 + (table_in_lds ? f * r * 4 : 0);
+int64_t ws_lds_bytes(int64_t f, int r, int T, int sweeps, bool table_in_lds, bool half, int fill) {
+    return ws_words_before_table(f, r, T, sweeps, half, fill) * 4 +
+           (table_in_lds ? f * r * (ws_offsets(T, half) ? 8 : 4) : 0);
 }
 
 // Warp-specialised single pass (16-byte aligned rows): plans as for the
@@ -1170,15 +1163,15 @@ WsPlan ws_plan(int64_t f, int r, bool vec, bool ind, bool full_keys = false) {
     if (!vec) return p;
     if (r == 5 && !ind && !full_keys) {
         p.r = 5;
-        WsPlan h = half_plan(f, 0, false, false, [&](int T, int fill) {
-            return ws_lds_bytes(f, r, T, false, true, fill);
+        WsPlan h = half_plan(f, 0, false, false, [&](int T, int sweeps, int fill) {
+            return ws_lds_bytes(f, r, T, sweeps, false, true, fill);
         }, 5);
         h.r = 5;
         return h.T != 0 ? h : WsPlan{};
     }
     if (r != 3) return p;
     for (int T : {64, 32, 16, 8}) {
-        if (ws_lds_bytes(f, r, T, ind, false, kWsFill) > kLdsBytes) continue;
+        if (ws_lds_bytes(f, r, T, 0, ind, false, kWsFill) > kLdsBytes) continue;
         const int64_t rpi = kWsFill / (T / 4);
         const int64_t sw = (f + rpi - 1) / rpi;
         if (sw > 16) continue;
@@ -1187,18 +1180,20 @@ WsPlan ws_plan(int64_t f, int r, bool vec, bool ind, bool full_keys = false) {
         break;
     }
     if (full_keys) return p;
-    const WsPlan h = half_plan(f, p.T, ind, false, [&](int T, int fill) {
-        return ws_lds_bytes(f, r, T, ind, true, fill);
+    const WsPlan h = half_plan(f, p.T, ind, false, [&](int T, int sweeps, int fill) {
+        return ws_lds_bytes(f, r, T, sweeps, ind, true, fill);
     });
     WsPlan best = h.T != 0 ? h : p;
     if (ind) {
-        // a wider tile when the row table, read from global memory (where it
-        // stays cached), leaves LDS to the keys: 2,300 files take 32 columns
-        // instead of 16
-        const WsPlan wide = half_plan(f, best.T, true, true, [&](int T, int fill) {
-            return ws_lds_bytes(f, r, T, false, true, fill);
+        // a 32-column tile when the row table, read from global memory (where
+        // it stays cached), leaves LDS to the keys, instead of 16 columns with
+        // the table in LDS (1,540 and 1,771 files, d = 0.8M: 2.76 against
+        // 3.40 ms and 3.11 against 3.71 ms).  Not 64 columns instead of 32:
+        // 1,140 files, d = 1M, 2.47 against 2.19 ms
+        const WsPlan wide = half_plan(f, best.T, true, true, [&](int T, int sweeps, int fill) {
+            return ws_lds_bytes(f, r, T, sweeps, false, true, fill);
         });
-        if (wide.T != 0) best = wide;
+        if (wide.T != 0 && best.T <= 16) best = wide;
     }
     return best;
 }
@@ -1231,7 +1226,7 @@ bool plan_median(int64_t f, bool vec, KernelPlan *out, bool full_keys) {
     const WsPlan p = mws_plan(f, vec, full_keys);
     if (p.T != 0) {
         *out = ws_kernel_plan(median_ws_fn(p) ? kKernelMedianWs : kKernelUnbuilt, p,
-                              mws_lds_bytes(f, p.T, p.half, p.fill), 0);
+                              mws_lds_bytes(f, p.T, p.sweeps, p.half, p.fill), 0);
         return out->kind == kKernelMedianWs;
     }
     KernelPlan k;
@@ -1257,7 +1252,7 @@ bool plan_fused(int64_t f, int r, bool vec, bool ind, KernelPlan *out, bool full
     if (p.T != 0) {
         const int table = ind ? (p.rtg ? 2 : 1) : 0;
         *out = ws_kernel_plan(fused_ws_fn(p, ind) ? kKernelFusedWs : kKernelUnbuilt, p,
-                              ws_lds_bytes(f, r, p.T, ind && !p.rtg, p.half, p.fill), table);
+                              ws_lds_bytes(f, r, p.T, p.sweeps, ind && !p.rtg, p.half, p.fill), table);
         return out->kind == kKernelFusedWs;
     }
     if (r != 3 && r != 5 && r != 7) return false;

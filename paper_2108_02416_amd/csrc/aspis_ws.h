@@ -3,6 +3,8 @@
 // over several sources (aspis_ws_*.hip) that compile in parallel.
 #pragma once
 
+#include <type_traits>
+
 #include "aspis_device.h"
 
 namespace aspis {
@@ -19,11 +21,41 @@ namespace {
 constexpr int kWsThreads = 1024;   // threads of a warp-specialised workgroup
 constexpr int kWsFill = 512;       // threads of the streaming role (default split)
 
-// sweeps per burst of loads: as many as the streaming role's registers hold
-// next to the tile's keys (SW x 4 registers, or SW x 2 with half keys).  The
-// 36-sweep tile spills either way; one sweep per burst spills least
-template <int R, int SW>
-constexpr int ws_batch() { return R == 3 ? (SW > 32 ? 1 : SW > 12 ? 2 : 3) : 1; }
+// The streaming role's loads run in a ring of B sweeps: a sweep is processed,
+// its registers take the load of the sweep B further on (of the next tile
+// past the end of this one), so B sweeps of loads are in flight at any time,
+// over the hand-over between tiles too.  B divides the sweeps of a tile (a
+// sweep's ring place is then the same in every tile) and is as large as the
+// registers next to the tile's keys allow.  Measured:
+// the file-major single pass is as fast as with bursts of two sweeps (9.20
+// ms at 455 files, d = 11.2M, either way); three sweeps there spill 24
+// registers (9.32 ms).  Through a row table the ring, the byte offsets
+// (ws_offsets) and keys and addresses kept out of registers across sweeps
+// take the spills from 27 to none and the pass at 455 files, d = 3M, from
+// 2.78 to 2.51 ms (linear read 2.39 ms).
+template <int R, int SW, bool HALF>
+constexpr int ws_ring() {
+    if (R != 3) return SW < 24 ? 2 : 1;
+    if (SW > 32) return 1;
+    if (SW <= (HALF ? 16 : 8) && SW % 4 == 0) return 4;
+    return SW <= 24 && SW % 3 == 0 ? 3 : SW % 2 == 0 ? 2 : 1;
+}
+
+// Row tables in LDS hold byte offsets (8 bytes a row: a row's address is one
+// addition then, no 64-bit product a load) in half-key tiles of 32 columns
+// or more, row numbers (4 bytes) where that room would cost tile width.
+constexpr bool ws_offsets(int T, bool half) { return half && T >= 32; }
+
+// LDS words before the row table of the single pass: histograms and key tile,
+// and the per-file words (half keys: slot nibbles, and pair-difference
+// nibbles at r = 3 or words; full keys: two words a file); rounded up to an
+// even count
+__host__ __device__ constexpr int64_t ws_words_before_table(int64_t f, int r, int T, int sweeps,
+                                                            bool half, int fill) {
+    const int64_t w = half ? half_tile_words(sweeps, fill) + (f + 7) / 8 + (r == 3 ? (f + 7) / 8 : f)
+                           : hist_words(T) + f * (int64_t)T + 2 * f;
+    return (w + 1) & ~int64_t{1};
+}
 
 template <int T, int R, int SW, bool IND, bool HALF, int FILL, bool RTG = false>
 __global__ void __launch_bounds__(kWsThreads)
@@ -31,11 +63,12 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
                 const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
                 const int32_t *__restrict__ n_sel, int64_t ntiles,
                 uint32_t *__restrict__ pair_diff, float *__restrict__ out) {
-    extern __shared__ uint32_t smem[];
+    extern __shared__ __align__(16) uint32_t smem[];
     constexpr int G = (kWsThreads - FILL) / T;   // selection lanes per column
     constexpr int CPR = T / 4;           // float4 chunks per row segment
     constexpr int RPI = FILL / CPR;      // rows per sweep of the streaming role
-    constexpr int B = ws_batch<R, SW>(); // sweeps per burst of loads
+    constexpr int B = ws_ring<R, SW, HALF>();   // sweeps of loads in flight
+    static_assert(SW % B == 0, "the ring divides the tile");
     // key registers per sweep: 4 keys, or (HALF) 4 high halves packed in 2;
     // a half-key tile's rows are the files themselves
     constexpr int KW = HALF ? 2 : 4;
@@ -44,7 +77,7 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
     // a file's pair-difference bits fit a nibble only at r = 3 (3 bits)
     constexpr bool PDN = HALF && R == 3;
     const int n = *n_sel;
-    const int64_t hwords = HALF ? half_hist_words(T) : hist_words(T);
+    const int64_t hwords = HALF ? 0 : hist_words(T);   // full keys only
     const int64_t f8 = (f + 7) / 8;
     uint32_t *hist = smem;               // selection histograms
     uint32_t *tile = smem + hwords;
@@ -52,12 +85,18 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
     // (tile row << 3) | slot or -1.  Half keys (tile row = file): ps [f/8],
     // one nibble per file, 8 | slot or 0; pd [f/8] pair-difference nibbles
     // at r = 3, else pd [f] words
-    uint32_t *pd = tile + (HALF ? half_tile_words(f, T, FILL) : f * T);
+    uint32_t *pd = tile + (HALF ? half_tile_words(SW, FILL) : f * T);
     int32_t *ps = reinterpret_cast<int32_t *>(pd + (PDN ? f8 : f));
-    // [f*R] row table (IND): staged in LDS, or (RTG) read from global
+    // IND: the row table [f*R], staged in LDS, or (RTG) read from global
     // memory, where it stays cached, when LDS is needed for a wider tile
-    int32_t *rt_lds = ps + (HALF ? f8 : f);
-    const int32_t *rt = RTG ? row_of : rt_lds;
+    constexpr bool OFFS = ws_offsets(T, HALF);
+    uint32_t *rt_lds = smem + ws_words_before_table(f, R, T, SW, HALF, FILL);
+    // byte offset of the row of replica e = i*R + s
+    auto row_offset = [&](int e) __attribute__((always_inline)) -> int64_t {
+        if constexpr (RTG) return (int64_t)row_of[e] * d * 4;
+        if constexpr (OFFS) return reinterpret_cast<const int64_t *>(rt_lds)[e];
+        return (int64_t)(int32_t)rt_lds[e] * d * 4;
+    };
     const int tid = threadIdx.x;
     if constexpr (HALF) {
         for (int64_t w = tid; w < f8; w += kWsThreads) {
@@ -80,7 +119,12 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         return ((uint32_t)ps[i >> 3] >> ((i & 7) * 4)) & 15u;
     };
     if constexpr (IND && !RTG)
-        for (int64_t i = tid; i < f * R; i += kWsThreads) rt_lds[i] = row_of[i];
+        for (int64_t i = tid; i < f * R; i += kWsThreads) {
+            if constexpr (OFFS)
+                reinterpret_cast<int64_t *>(rt_lds)[i] = (int64_t)row_of[i] * d * 4;
+            else
+                rt_lds[i] = (uint32_t)row_of[i];
+        }
     for (int i = tid; i < hwords; i += kWsThreads) hist[i] = 0u;
     __syncthreads();
     // roles are whole waves: the first FILL/64 waves stream, the rest
@@ -112,13 +156,15 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         auto load_sweep = [&](int64_t t, int x) __attribute__((always_inline)) {
             const int64_t col = min(t * T + 4 * cq, d - 4);
             if constexpr (IND) {
-                int i = j0 + x * RPI;
+                int i = j0;
                 asm volatile("" : "+v"(i));   // row addresses recomputed per tile
+                i += x * RPI;
                 Chunks c;
                 if (i < f) {
 #pragma unroll
                     for (int s = 0; s < R; ++s)
-                        c.q[s] = load_stream(g + (int64_t)rt[i * R + s] * d + col);
+                        c.q[s] = load_stream(reinterpret_cast<const float *>(
+                            reinterpret_cast<const char *>(g + col) + row_offset(i * R + s)));
                 } else {
 #pragma unroll
                     for (int s = 0; s < R; ++s) c.q[s] = make_uint4(0u, 0u, 0u, 0u);
@@ -177,9 +223,12 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
                     if (s_sel == s) w = c.q[s];
                 if constexpr (HALF) {
                     if (q & 8) {
-                        keys[x][0] = pack_high(to_key(w.x), to_key(w.y));
-                        keys[x][1] = pack_high(to_key(w.z), to_key(w.w));
+                        keys[x][0] = pk_high_keys(pack_high(w.x, w.y));
+                        keys[x][1] = pk_high_keys(pack_high(w.z, w.w));
                     }
+                    // computed here: the compiler would sink it to the put
+                    // and hold the loaded words until then
+                    asm volatile("" : "+v"(keys[x][0]), "+v"(keys[x][1]));
                 } else {
                     keys[x][0] = to_key(w.x);
                     keys[x][1] = to_key(w.y);
@@ -188,41 +237,29 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
                 }
             }
         };
-        // sweep 0 of the next tile, loaded early: before the barrier and the
-        // hand-over, so that loads stay in flight meanwhile.  The 36-sweep
-        // tile, the row-table reads and r = 5 (five chunks a sweep) have no
-        // registers to spare for it and load it with their tile
-        constexpr bool kEarly0 = SW <= 32 && !IND && R == 3;
-        Chunks c0;
-        // tile t from its sweep 0 (already in c0, or loaded first); the
-        // other sweeps go in bursts of B, all loads of a burst issued first
-        auto stream_rest = [&](int64_t t) __attribute__((always_inline)) {
-            if constexpr (!kEarly0) c0 = load_sweep(t, 0);
-            proc_sweep(0, c0);
-            __builtin_amdgcn_sched_barrier(0);
+        Chunks c[B];
+        // tile t from the ring, refilled with t's later sweeps and then with
+        // the first ones of tile tn
+        auto stream_tile = [&](int64_t t, int64_t tn) __attribute__((always_inline)) {
 #pragma unroll
-            for (int xb = 1; xb < SW; xb += B) {
-                Chunks c[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) c[b] = load_sweep(t, xb + b);
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) proc_sweep(xb + b, c[b]);
-                // keep each burst's loads together: no scheduling across
-                // bursts, which would hold more loads in registers than fit
+            for (int x = 0; x < SW; ++x) {
+                proc_sweep(x, c[x % B]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (x + B < SW)
+                    c[x % B] = load_sweep(t, x + B);
+                else if (tn < ntiles)
+                    c[x % B] = load_sweep(tn, x + B - SW);
+                // no scheduling across sweeps, which would hold more loads in
+                // registers than fit
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
         auto put_tile = [&]() __attribute__((always_inline)) {
             if constexpr (HALF) {
-                // pair-rows j0 + k*RPI of the sweep pairs holding a file
-                int64_t fo = f;   // opaque: compared per tile, not held per pair
-                asm volatile("" : "+s"(fo));
+                // pair-rows j0 + k*RPI
 #pragma unroll
                 for (int k = 0; k < SW / 2; ++k)
-                    if (k * 2 * RPI < fo)
-                        put_pairs<T, G>(tile, j0 + k * RPI, cq, keys[2 * k], keys[2 * k + 1]);
+                    put_pairs<T, G>(tile, j0 + k * RPI, cq, keys[2 * k], keys[2 * k + 1]);
             } else {
 #pragma unroll
                 for (int x = 0; x < SW; ++x) {
@@ -236,16 +273,15 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         };
         int64_t t = blockIdx.x;
         if (t < ntiles) {
-            if constexpr (kEarly0) c0 = load_sweep(t, 0);
-            stream_rest(t);
+#pragma unroll
+            for (int x = 0; x < B; ++x) c[x] = load_sweep(t, x);
+            stream_tile(t, t + gridDim.x);
+            put_tile();
         }
-        if (kEarly0 && t + gridDim.x < ntiles) c0 = load_sweep(t + gridDim.x, 0);
-        if (t < ntiles) put_tile();
         __syncthreads();
         for (; t < ntiles; t += gridDim.x) {
             const int64_t tn = t + gridDim.x;
-            if (tn < ntiles) stream_rest(tn);
-            if (kEarly0 && tn + gridDim.x < ntiles) c0 = load_sweep(tn + gridDim.x, 0);
+            if (tn < ntiles) stream_tile(tn, tn + gridDim.x);
             __syncthreads();
             if (tn < ntiles) put_tile();
             __syncthreads();
@@ -271,10 +307,11 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
                     auto row = [&](int j) __attribute__((always_inline)) -> int64_t {
                         const uint32_t q = j < f ? nib(j) : 0u;
                         if (!(q & 8u)) return -1;
-                        return IND ? (int64_t)rt[j * R + (q & 7)] : (int64_t)j * R + (q & 7);
+                        if constexpr (IND) return row_offset(j * R + (int)(q & 7));
+                        return ((int64_t)j * R + (q & 7)) * d * 4;
                     };
-                    select_half_tile<T, G, RPI>(tile, hist, (int)half_pair_rows(f, T, FILL), n,
-                                                t * T, d, out, tid - FILL, g, row);
+                    select_half_tile<T, G, RPI, RPI / G * SW / 2>(
+                        tile, n, t * T, d, out, tid - FILL, g, row);
                 } else {
                     select_tile<T, G>(tile, hist, n, t * T, d, out, tid - FILL);
                 }
@@ -296,52 +333,71 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
 // list of the selection) into registers while waves 8-15 select on tile t.
 // Used by the two-pass path and after a wrong guess of the single pass.
 
-template <int SW>
-constexpr int mws_batch() { return SW >= 16 ? 4 : (SW < 6 ? SW : 6); }
+// the ring of the streaming role's loads (ws_ring), one 16-byte load a
+// sweep: six sweeps (10 measured 1 % slower at 455 kept files)
+template <int SW, bool HALF>
+constexpr int mws_ring() {
+    constexpr int cap = (128 - 28 - SW * (HALF ? 2 : 4)) / 4;
+    constexpr int most = HALF ? 6 : 4;
+    for (int b = cap < most ? cap : most; b > 1; --b)
+        if (SW % b == 0) return b;
+    return 1;
+}
 
 template <int T, int SW, bool HALF, int FILL>
 __global__ void __launch_bounds__(kWsThreads)
 median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restrict__ rows,
                  const int32_t *__restrict__ n_sel, int64_t ntiles, float *__restrict__ out,
                  TileMask mask) {
-    extern __shared__ uint32_t smem[];
+    extern __shared__ __align__(16) uint32_t smem[];
     constexpr int G = (kWsThreads - FILL) / T;   // selection lanes per column
     constexpr int CPR = T / 4;           // float4 chunks per row segment
     constexpr int RPI = FILL / CPR;      // rows per sweep of the streaming role
-    constexpr int B = mws_batch<SW>();   // sweeps per burst of loads
+    constexpr int B = mws_ring<SW, HALF>();   // sweeps of loads in flight
     // key registers per sweep: 4 keys, or (HALF) 4 high halves packed in 2
     constexpr int KW = HALF ? 2 : 4;
     static_assert(!HALF || (SW % 2 == 0 && RPI == half_rpi(T, FILL)), "half-key sweeps");
     const int n = *n_sel;
     if (n <= 0) return;                  // uniform: no workgroup reaches a barrier
-    const int64_t hwords = HALF ? half_hist_words(T) : hist_words(T);
+    const int64_t hwords = HALF ? 0 : hist_words(T);   // full keys only
     uint32_t *hist = smem;
     uint32_t *tile = smem + hwords;
-    int32_t *rl = reinterpret_cast<int32_t *>(tile + (HALF ? half_tile_words(n, T, FILL)
-                                                           : (int64_t)n * T));   // [n] kept rows
+    // [n] kept rows (ws_offsets; the words before them: an even count)
+    using Row = std::conditional_t<ws_offsets(T, HALF), int64_t, int32_t>;
+    constexpr bool OFFS = ws_offsets(T, HALF);
+    Row *rl = reinterpret_cast<Row *>(tile + (HALF ? half_tile_words(SW, FILL) : (int64_t)n * T));
+    auto row_offset = [&](int j) __attribute__((always_inline)) -> int64_t {
+        return OFFS ? (int64_t)rl[j] : (int64_t)rl[j] * d * 4;
+    };
     const int tid = threadIdx.x;
-    for (int i = tid; i < n; i += kWsThreads) rl[i] = rows[i];
+    for (int i = tid; i < n; i += kWsThreads) rl[i] = OFFS ? (Row)((int64_t)rows[i] * d * 4) : (Row)rows[i];
     for (int i = tid; i < hwords; i += kWsThreads) hist[i] = 0u;
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave < FILL / 64) {
         const int cq = tid % CPR, j0 = tid / CPR;
         uint32_t keys[SW][KW];
-        // one 16-byte chunk of kept row j (a lane past the last kept row
-        // re-reads row 0, which is never put; past the end of the rows it
-        // re-reads the row's last chunk, whose median is never written)
+        // one 16-byte chunk of a kept row (a lane past the last kept row
+        // re-reads that row, which is never put again; past the end of the
+        // rows it re-reads the row's last chunk, whose median is never
+        // written)
         auto load_row = [&](int64_t t, int x) __attribute__((always_inline)) {
             const int64_t col = min(t * T + 4 * cq, d - 4);
-            int j = j0 + x * RPI < n ? j0 + x * RPI : 0;
-            asm volatile("" : "+v"(j));   // row address recomputed per tile
-            return load_stream(g + (int64_t)rl[j] * d + col);
+            int j = j0;
+            asm volatile("" : "+v"(j));   // offsets read per tile, not held
+            j = min(j + x * RPI, n - 1);
+            return load_stream(reinterpret_cast<const float *>(
+                reinterpret_cast<const char *>(g + col) + row_offset(j)));
         };
         auto to_keys = [&](int x, uint4 q) __attribute__((always_inline)) {
             if constexpr (HALF) {
                 // high key halves; 0xFFFF past the last kept row
                 const bool keep = j0 + x * RPI < n;
-                keys[x][0] = keep ? pack_high(to_key(q.x), to_key(q.y)) : 0xFFFFFFFFu;
-                keys[x][1] = keep ? pack_high(to_key(q.z), to_key(q.w)) : 0xFFFFFFFFu;
+                keys[x][0] = keep ? pk_high_keys(pack_high(q.x, q.y)) : 0xFFFFFFFFu;
+                keys[x][1] = keep ? pk_high_keys(pack_high(q.z, q.w)) : 0xFFFFFFFFu;
+                // computed here: the compiler would sink it to the put and
+                // hold the four loaded words until then
+                asm volatile("" : "+v"(keys[x][0]), "+v"(keys[x][1]));
             } else {
                 keys[x][0] = to_key(q.x);
                 keys[x][1] = to_key(q.y);
@@ -349,34 +405,24 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
                 keys[x][3] = to_key(q.w);
             }
         };
-        uint4 c0;   // sweep 0 of the next tile, loaded early
-        auto stream_rest = [&](int64_t t) __attribute__((always_inline)) {
-            to_keys(0, c0);
-            __builtin_amdgcn_sched_barrier(0);
+        uint4 c[B];
+        auto stream_tile = [&](int64_t t, int64_t tn) __attribute__((always_inline)) {
 #pragma unroll
-            for (int xb = 1; xb < SW; xb += B) {
-                uint4 c[B];
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) c[b] = load_row(t, xb + b);
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (xb + b < SW) to_keys(xb + b, c[b]);
+            for (int x = 0; x < SW; ++x) {
+                to_keys(x, c[x % B]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (x + B < SW)
+                    c[x % B] = load_row(t, x + B);
+                else if (tn < ntiles)
+                    c[x % B] = load_row(tn, x + B - SW);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
         auto put_tile = [&]() __attribute__((always_inline)) {
             if constexpr (HALF) {
-                int no = n;   // opaque: compared per tile, not held per pair
-                asm volatile("" : "+s"(no));
 #pragma unroll
-                for (int k = 0; k < SW / 2; ++k) {
-                    int p = j0 + k * RPI;
-                    // opaque: the LDS addresses are recomputed per tile
-                    // instead of being held in registers for every pair
-                    asm volatile("" : "+v"(p));
-                    if (k * 2 * RPI < no) put_pairs<T, G>(tile, p, cq, keys[2 * k], keys[2 * k + 1]);
-                }
+                for (int k = 0; k < SW / 2; ++k)
+                    put_pairs<T, G>(tile, j0 + k * RPI, cq, keys[2 * k], keys[2 * k + 1]);
             } else {
 #pragma unroll
                 for (int x = 0; x < SW; ++x) {
@@ -386,21 +432,21 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
                 }
             }
         };
-        // the workgroup's tiles: t, then tn (whose sweep 0 is loaded early)
+        // the workgroup's tiles: t, then tn (whose first sweeps are loaded
+        // before the hand-over of t), then tnn
         const int64_t G0 = gridDim.x;
         int64_t t = mask.next(blockIdx.x, G0, ntiles);
         int64_t tn = mask.next(t + G0, G0, ntiles);
         if (t < ntiles) {
-            c0 = load_row(t, 0);
-            stream_rest(t);
+#pragma unroll
+            for (int x = 0; x < B; ++x) c[x] = load_row(t, x);
+            stream_tile(t, tn);
+            put_tile();
         }
-        if (tn < ntiles) c0 = load_row(tn, 0);
-        if (t < ntiles) put_tile();
         __syncthreads();
         while (t < ntiles) {
             const int64_t tnn = mask.next(tn + G0, G0, ntiles);
-            if (tn < ntiles) stream_rest(tn);
-            if (tnn < ntiles) c0 = load_row(tnn, 0);
+            if (tn < ntiles) stream_tile(tn, tnn);
             __syncthreads();
             if (tn < ntiles) put_tile();
             __syncthreads();
@@ -413,13 +459,10 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
              t = mask.next(t + gridDim.x, gridDim.x, ntiles)) {
             if constexpr (HALF) {
                 auto row = [&](int j) __attribute__((always_inline)) -> int64_t {
-                    return j < n ? (int64_t)rl[j] : -1;
+                    return j < n ? row_offset(j) : -1;
                 };
-                // FILL = 512: RPI = 4G, so every lane holds the same number of
-                // words, at most 2 SW
-                constexpr int REG = (FILL == kWsFill && RPI == 4 * G) ? 2 * SW : 0;
-                select_half_tile<T, G, RPI, REG>(tile, hist, (int)half_pair_rows(n, T, FILL), n,
-                                                 t * T, d, out, tid - FILL, g, row);
+                select_half_tile<T, G, RPI, RPI / G * SW / 2>(
+                    tile, n, t * T, d, out, tid - FILL, g, row);
             } else {
                 select_tile<T, G>(tile, hist, n, t * T, d, out, tid - FILL);
             }

@@ -10,12 +10,8 @@ MedianWsFn median_ws_fn(const WsPlan &p) {
     if (p.fill == kWsFillWide) {
         if (!p.half) return nullptr;
         switch (key) {
-            ASPIS_MWS(64, 16, true, kWsFillWide)
             ASPIS_MWS(64, 24, true, kWsFillWide)
-            ASPIS_MWS(64, 32, true, kWsFillWide)
-            ASPIS_MWS(32, 16, true, kWsFillWide)
             ASPIS_MWS(32, 24, true, kWsFillWide)
-            ASPIS_MWS(32, 32, true, kWsFillWide)
         default: return nullptr;
         }
     }
@@ -27,7 +23,9 @@ MedianWsFn median_ws_fn(const WsPlan &p) {
     ASPIS_MWS(TT, 12, false, kWsFill)
 #define ASPIS_MWS_HALF(TT)               \
     ASPIS_MWS(TT, 16, true, kWsFill)     \
+    ASPIS_MWS(TT, 20, true, kWsFill)     \
     ASPIS_MWS(TT, 24, true, kWsFill)     \
+    ASPIS_MWS(TT, 28, true, kWsFill)     \
     ASPIS_MWS(TT, 32, true, kWsFill)
         ASPIS_MWS_FULL(64)
         ASPIS_MWS(64, 16, false, kWsFill)
@@ -35,16 +33,16 @@ MedianWsFn median_ws_fn(const WsPlan &p) {
         ASPIS_MWS_FULL(16)
         ASPIS_MWS_FULL(8)
         ASPIS_MWS(128, 8, true, kWsFill)
-        ASPIS_MWS(128, 16, true, kWsFill)
-        ASPIS_MWS(128, 24, true, kWsFill)
-        ASPIS_MWS(128, 26, true, kWsFill)
-        ASPIS_MWS(128, 28, true, kWsFill)
+        ASPIS_MWS(128, 12, true, kWsFill)
         ASPIS_MWS(128, 30, true, kWsFill)
-        ASPIS_MWS(128, 32, true, kWsFill)
+        ASPIS_MWS_HALF(128)
         ASPIS_MWS_HALF(64)
         ASPIS_MWS_HALF(32)
         ASPIS_MWS(32, 36, true, kWsFill)
-        ASPIS_MWS_HALF(16)
+        ASPIS_MWS(16, 16, true, kWsFill)
+        ASPIS_MWS(16, 24, true, kWsFill)
+        ASPIS_MWS(16, 28, true, kWsFill)
+        ASPIS_MWS(16, 32, true, kWsFill)
 #undef ASPIS_MWS_HALF
 #undef ASPIS_MWS_FULL
     default: return nullptr;

@@ -13,9 +13,7 @@ FusedWsFn fused_ws_r3_table_fn(const WsPlan &p) {
     case ws_key(TT, SWW, true): return &fused_ws_kernel<TT, 3, SWW, true, true, kWsFillWide, true>;
         switch (ws_key(p.T, p.sweeps, p.half)) {
             W(64, 24)
-            W(64, 32)
             W(32, 24)
-            W(32, 32)
         default: return nullptr;
         }
 #undef W
@@ -32,23 +30,25 @@ FusedWsFn fused_ws_r3_table_fn(const WsPlan &p) {
     ASPIS_FWS(TT, 12, false)  \
     ASPIS_FWS(TT, 16, false)
 #define ASPIS_FWS_HALF(TT)    \
-    ASPIS_FWS(TT, 16, true)   \
+    ASPIS_FWS(TT, 20, true)   \
     ASPIS_FWS(TT, 24, true)   \
+    ASPIS_FWS(TT, 28, true)   \
     ASPIS_FWS(TT, 32, true)
         ASPIS_FWS_FULL(64)
         ASPIS_FWS_FULL(32)
         ASPIS_FWS_FULL(16)
         ASPIS_FWS_FULL(8)
         ASPIS_FWS(128, 8, true)
+        ASPIS_FWS(128, 12, true)
         ASPIS_FWS(128, 16, true)
-        ASPIS_FWS(128, 24, true)
-        ASPIS_FWS(128, 26, true)
-        ASPIS_FWS(128, 28, true)
         ASPIS_FWS(128, 30, true)
-        ASPIS_FWS(128, 32, true)
+        ASPIS_FWS_HALF(128)
         ASPIS_FWS_HALF(64)
         ASPIS_FWS_HALF(32)
-        ASPIS_FWS_HALF(16)
+        ASPIS_FWS(16, 16, true)
+        ASPIS_FWS(16, 24, true)
+        ASPIS_FWS(16, 28, true)
+        ASPIS_FWS(16, 32, true)
 #undef ASPIS_FWS_HALF
 #undef ASPIS_FWS_FULL
     default: return nullptr;

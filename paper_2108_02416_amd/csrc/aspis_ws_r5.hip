@@ -4,23 +4,17 @@
 namespace aspis {
 
 FusedWsFn fused_ws_r5_fn(const WsPlan &p) {
-    // half keys, even split
+    // half keys, even split; the sweeps of f = C(K,5), K = 10 to 15
     if (p.r != 5 || !p.half || p.fill != kWsFill || p.rtg) return nullptr;
     switch (ws_key(p.T, p.sweeps, p.half)) {
 #define ASPIS_FWS5(TT, SWW) \
     case ws_key(TT, SWW, true): return &fused_ws_kernel<TT, 5, SWW, false, true, kWsFill, false>;
         ASPIS_FWS5(128, 16)
         ASPIS_FWS5(128, 30)
-        ASPIS_FWS5(128, 32)
-        ASPIS_FWS5(64, 16)
-        ASPIS_FWS5(64, 24)
-        ASPIS_FWS5(64, 32)
-        ASPIS_FWS5(32, 16)
+        ASPIS_FWS5(64, 28)
         ASPIS_FWS5(32, 24)
         ASPIS_FWS5(32, 32)
-        ASPIS_FWS5(16, 16)
         ASPIS_FWS5(16, 24)
-        ASPIS_FWS5(16, 32)
 #undef ASPIS_FWS5
     default: return nullptr;
     }
