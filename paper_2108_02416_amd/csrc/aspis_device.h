@@ -215,7 +215,7 @@ __device__ __forceinline__ int compact(uint32_t *base, int cnt, F &&keep) {
 
 // Lower median (rank floor((n-1)/2)) of each of the T columns of the LDS key
 // tile holding n rows, found by the G lanes stid = c*G + g of each column c;
-// written to out[k0 + c] for k0 + c < d.  hist: the workgroup's histogram
+// written to out[k] where k = col(c), unless that is negative.  hist: the workgroup's histogram
 // block (hist_words(T) words, zero on entry; left zero on exit except for
 // the overflow buckets).
 //
@@ -232,9 +232,9 @@ __device__ __forceinline__ int compact(uint32_t *base, int cnt, F &&keep) {
 //  2. bitwise MSB radix select on the few survivors: split on the highest
 //     differing bit, keep the side holding the rank, until all are equal.
 // Lane g owns rows g, g+G, ...; its x-th candidate lives at base[x*STRIDE].
-template <int T, int G>
-__device__ __forceinline__ void select_tile(uint32_t *tile, uint32_t *hist, int n, int64_t k0,
-                                            int64_t d, float *out, int stid) {
+template <int T, int G, typename ColFn>
+__device__ __forceinline__ void select_tile(uint32_t *tile, uint32_t *hist, int n, float *out,
+                                            int stid, ColFn &&col) {
     constexpr int STRIDE = G * T;
     constexpr int BPL = kHistBuckets / G;   // buckets scanned per lane
     static_assert(BPL >= 2 && BPL % 2 == 0, "buckets per lane");
@@ -361,7 +361,10 @@ __device__ __forceinline__ void select_tile(uint32_t *tile, uint32_t *hist, int 
         and_or(a, o);
         varying = a ^ o;
     }
-    if (g == 0 && k0 + c < d) out[k0 + c] = __uint_as_float(from_key(a));
+    if (g == 0) {
+        const int64_t k = col(c);
+        if (k >= 0) out[k] = __uint_as_float(from_key(a));
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -420,9 +423,9 @@ __device__ __forceinline__ void put_pairs(uint32_t *tile, int p, int cq, const u
 // Lower median of each of the T columns of a half-key tile of NW*G pair-rows
 // (NW words per lane, a multiple of 4) holding nk kept values (1 <= nk,
 // 2*NW*G <= 65536), by the G lanes stid = c*G + g of column c, written to
-// out[k0 + c] for k0 + c < d.  row(j) gives the byte offset in g
-// of the replica row behind tile row j, or -1 for a padding row.  The tile
-// may be overwritten.
+// out[k] where k = col(c), unless that is negative.  row(j) gives the byte
+// offset in g of the replica row behind tile row j, or -1 for a padding row.
+// The tile may be overwritten.
 //
 //  1. the high byte of the sought key: the lane's high bytes, four to a
 //     register, then eight binary-search steps.  A step needs the number of
@@ -444,10 +447,10 @@ __device__ __forceinline__ void put_pairs(uint32_t *tile, int p, int cq, const u
 // about 14 VALU instructions a key, the tile read three times.  The LDS
 // histograms it replaces took about 28 and waited for their atomics in every
 // round.  SEL_MEASURED
-template <int T, int G, int RPI, int NW, typename RowFn>
-__device__ __forceinline__ void select_half_tile(uint32_t *tile, int nk, int64_t k0, int64_t d,
-                                                 float *out, int stid, const float *__restrict__ g,
-                                                 RowFn &&row) {
+template <int T, int G, int RPI, int NW, typename RowFn, typename ColFn>
+__device__ __forceinline__ void select_half_tile(uint32_t *tile, int nk, float *out, int stid,
+                                                 const float *__restrict__ g, RowFn &&row,
+                                                 ColFn &&column) {
     static_assert(RPI % (4 * G) == 0 && NW % 4 == 0, "whole blocks of four words per lane");
     constexpr int STRIDE = G * T;   // words between a lane's pair-rows
     const int gl = stid % G;
@@ -528,8 +531,8 @@ __device__ __forceinline__ void select_half_tile(uint32_t *tile, int nk, int64_t
             }
         }
     }
-    const bool valid = k0 + c < d;
-    const char *col = reinterpret_cast<const char *>(g + (valid ? k0 + c : 0));
+    const int64_t k = column(c);
+    const char *col = reinterpret_cast<const char *>(g + (k >= 0 ? k : 0));
     auto low_half = [&](int j) __attribute__((always_inline)) -> uint32_t {
         const int64_t off = row(j);
         // a padding row: the largest key
@@ -632,25 +635,26 @@ __device__ __forceinline__ void select_half_tile(uint32_t *tile, int nk, int64_t
             varying = a ^ o;
         }
     }
-    if (gl == 0 && valid) out[k0 + c] = __uint_as_float(from_key((H << 16) | a));
+    if (gl == 0 && k >= 0) out[k] = __uint_as_float(from_key((H << 16) | a));
 }
 
-// One 16-byte load (16-byte aligned) from a replica row that the pass
-// reads once: a non-temporal load, which streams past the caches instead of
-// filling them with lines nothing reads again (measured 3-6 % faster than a
-// plain load on the 61 GB single pass).
+// One 16-byte load from a replica row that the pass reads once: a
+// non-temporal load, which streams past the caches instead of filling them
+// with lines nothing reads again (measured 3-6 % faster than a plain load on
+// the 61 GB single pass).  Any 4-byte alignment: global memory takes a
+// 16-byte access at a dword boundary, so rows of any length are read this
+// way (455 files, d = 2.5M + 1: 2.50 ms, against 5.63 ms with one 4-byte load a
+// coordinate).
 __device__ __forceinline__ uint4 load_stream(const float *p) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4), aligned(4)));
     const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // Load four consecutive coordinates [k, k+4) of one row as bit patterns;
 // coordinates at or beyond kend read as 0.
-template <bool VEC>
-__device__ __forceinline__ void load4(const float *row, int64_t k, int64_t kend,
-                                      uint32_t v[4]) {
-    if (VEC && k + 3 < kend) {
+__device__ __forceinline__ void load4(const float *row, int64_t k, int64_t kend, uint32_t v[4]) {
+    if (k + 3 < kend) {
         const uint4 q = load_stream(row + k);
         v[0] = q.x;
         v[1] = q.y;
@@ -661,6 +665,15 @@ __device__ __forceinline__ void load4(const float *row, int64_t k, int64_t kend,
         for (int e = 0; e < 4; ++e)
             v[e] = (k + e < kend) ? __float_as_uint(row[k + e]) : 0u;
     }
+}
+
+// Column k0 + c of a tile whose lanes read whole 16-byte chunks: the chunk
+// holding the end of rows of d coordinates (d >= 4) is read four coordinates
+// before the end instead, so its tile columns hold those; -1 past the end.
+__device__ __forceinline__ int64_t chunk_start(int64_t k, int64_t d) { return k < d - 4 ? k : d - 4; }
+__device__ __forceinline__ int64_t chunk_col(int64_t k0, int c, int64_t d) {
+    const int64_t k = k0 + (c & ~3);
+    return k < d ? chunk_start(k, d) + (c & 3) : -1;
 }
 
 // Row of replica (i,s): i*R+s in the file-major tensor, or row_of[i*R+s]

@@ -713,7 +713,7 @@ aspis_status aspis_plan(int32_t K, int32_t r, int64_t d, int32_t worker_major, u
     aspis_status st = check_device_shape(K, r, d, &f);
     if (st != ASPIS_OK) return st;
     if (!single_pass || !median) return fail(ASPIS_ERR_INVALID_ARG, "aspis_plan: NULL output");
-    const bool vec = d % 4 == 0;
+    const bool vec = d >= 4;
     const bool full_keys = (flags & ASPIS_FLAG_FULL_KEYS) != 0;
     aspis::KernelPlan fused{}, med{};
     if (f <= aspis::kVoteRowsMaxFiles)
@@ -721,6 +721,10 @@ aspis_status aspis_plan(int32_t K, int32_t r, int64_t d, int32_t worker_major, u
     aspis::plan_median(f, vec, &med, full_keys);
     to_abi(fused, single_pass);
     to_abi(med, median);
+    // rows off 16-byte boundaries: the same kernel, reported as the single
+    // pass for any rows (aspis.h)
+    if (d % 4 != 0 && single_pass->kernel == ASPIS_KERNEL_FUSED_WS)
+        single_pass->kernel = ASPIS_KERNEL_FUSED;
     if (fused.kind == aspis::kKernelUnbuilt || med.kind == aspis::kKernelUnbuilt)
         return fail(ASPIS_ERR_INVALID_ARG, "aspis_plan: K=%d r=%d d=%lld: a planned kernel is not built",
                     K, r, (long long)d);

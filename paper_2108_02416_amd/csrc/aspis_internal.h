@@ -144,7 +144,7 @@ struct KernelPlan {
 };
 // Median over up to f kept rows (always has a kernel); single pass for f
 // files of r replicas (false: none, the step then takes two passes).  vec:
-// d % 4 == 0 and a 16-byte aligned tensor; ind: rows through a row table;
+// d >= 4, a row holds a 16-byte chunk; ind: rows through a row table;
 // full_keys: tiles of 32-bit keys only (no half-key plan, no read-back).
 bool plan_median(int64_t f, bool vec, KernelPlan *out, bool full_keys = false);
 bool plan_fused(int64_t f, int r, bool vec, bool ind, KernelPlan *out, bool full_keys = false);

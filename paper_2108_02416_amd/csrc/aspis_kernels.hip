@@ -33,8 +33,9 @@
 //                      high 16 bits of each key (select_half_tile), which
 //                      doubles the tile width; the low halves of the rows
 //                      that tie with the median's high half are read back.
-//   fused_kernel       agreement + median in one read for r = 5, 7 and
-//                      unaligned rows (load, then select, per tile).
+//   fused_kernel       agreement + median in one read, load then select per
+//                      tile, where no warp-specialised plan exists (r = 7,
+//                      small r = 5, rows of fewer than four coordinates).
 //   fused_mean_kernel  agreement + Case 1 mean in one read.
 //   mean_kernel        Algorithm 1 Case 1 mean, fp64 accumulation in file
 //                      order.
@@ -69,7 +70,7 @@ __global__ void fill_u64_kernel(uint64_t *p, int64_t n, uint64_t v) {
 constexpr int kAgreeUnroll = 4;                       // float4 per thread
 constexpr int64_t kAgreeChunk = (int64_t)kBlock * 4 * kAgreeUnroll;
 
-template <int R, bool VEC>
+template <int R>
 __global__ void __launch_bounds__(kBlock)
 agree_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
              int64_t d, int64_t kend, int64_t nchunks, uint32_t *__restrict__ pair_diff) {
@@ -88,7 +89,7 @@ agree_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
             if (k < kend) {
                 uint32_t v[R][4];
 #pragma unroll
-                for (int s = 0; s < R; ++s) load4<VEC>(rows[s], k, kend, v[s]);
+                for (int s = 0; s < R; ++s) load4(rows[s], k, kend, v[s]);
                 int p = 0;
 #pragma unroll
                 for (int s = 0; s < R; ++s)
@@ -118,7 +119,7 @@ agree_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
 // Agreement of one file per workgroup over coordinates [0,kend) (the
 // prefix probe of the single pass): the workgroup ORs its lanes' bits and
 // stores the file's word, so pair_diff needs no zero fill and no atomics.
-template <int R, bool VEC>
+template <int R>
 __global__ void __launch_bounds__(kBlock)
 agree_file_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
                   int64_t d, ProbeSet probe, uint32_t *__restrict__ pair_diff) {
@@ -144,7 +145,7 @@ agree_file_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_o
 #pragma unroll
                 for (int s = 0; s < R; ++s) {
                     if (k < kend)
-                        load4<VEC>(rows[s], k, kend, v[u][s]);
+                        load4(rows[s], k, kend, v[u][s]);
                     else
                         v[u][s][0] = v[u][s][1] = v[u][s][2] = v[u][s][3] = 0u;
                 }
@@ -326,7 +327,7 @@ select_kernel(const int32_t *__restrict__ subsets,
 
 constexpr int kMedianBatch = 8;   // row loads per thread issued as one burst
 
-template <int T, bool VEC>
+template <int T>
 __global__ void __launch_bounds__(tile_block<T>())
 median_kernel(const float *__restrict__ g, int64_t d,
               const int32_t *__restrict__ rows, const int32_t *__restrict__ n_sel,
@@ -346,12 +347,13 @@ median_kernel(const float *__restrict__ g, int64_t d,
     for (int64_t t = mask.next(blockIdx.x, gridDim.x, ntiles); t < ntiles;
          t = mask.next(t + gridDim.x, gridDim.x, ntiles)) {
         const int64_t k0 = t * T;
+        auto col = [&](int c) { return k0 + c < d ? k0 + c : (int64_t)-1; };
         for (int jb = 0; jb < n; jb += RPI * kMedianBatch) {
             uint32_t v[kMedianBatch][4];
 #pragma unroll
             for (int b = 0; b < kMedianBatch; ++b) {
                 const int j = jb + b * RPI + j0;
-                if (j < n) load4<VEC>(g + (int64_t)rows[j] * d, k0 + 4 * cq, d, v[b]);
+                if (j < n) load4(g + (int64_t)rows[j] * d, k0 + 4 * cq, d, v[b]);
             }
 #pragma unroll
             for (int b = 0; b < kMedianBatch; ++b) {
@@ -365,7 +367,7 @@ median_kernel(const float *__restrict__ g, int64_t d,
             }
         }
         __syncthreads();
-        select_tile<T, G>(tile, hist, n, k0, d, out, tid);
+        select_tile<T, G>(tile, hist, n, out, tid, col);
         __syncthreads();
     }
 }
@@ -376,7 +378,7 @@ median_kernel(const float *__restrict__ g, int64_t d,
 template <int R>
 constexpr int fused_batch() { return R == 3 ? 4 : (R == 5 ? 2 : 1); }
 
-template <int T, int R, bool VEC>
+template <int T, int R>
 __global__ void __launch_bounds__(tile_block<T>())
 fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f, int64_t d,
              const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
@@ -399,6 +401,7 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
     const int cq = tid % CPR, j0 = tid / CPR;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int64_t k0 = t * T;
+        auto col = [&](int c) { return k0 + c < d ? k0 + c : (int64_t)-1; };
         for (int64_t ib = 0; ib < f; ib += (int64_t)RPI * B) {
             uint32_t v[B][R][4];
 #pragma unroll
@@ -407,7 +410,7 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
                 if (i < f) {
 #pragma unroll
                     for (int s = 0; s < R; ++s)
-                        load4<VEC>(g + replica_row(row_of, i, R, s) * d, k0 + 4 * cq, d, v[b][s]);
+                        load4(g + replica_row(row_of, i, R, s) * d, k0 + 4 * cq, d, v[b][s]);
                 }
             }
 #pragma unroll
@@ -443,7 +446,7 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
             }
         }
         __syncthreads();
-        if (n > 0) select_tile<T, G>(tile, hist, n, k0, d, out, tid);
+        if (n > 0) select_tile<T, G>(tile, hist, n, out, tid, col);
         __syncthreads();
     }
     for (int64_t i = tid; i < f; i += BLOCK)
@@ -462,7 +465,7 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
 // 8 waves per SIMD (4 files: 74 VGPRs, 6 waves, 3.7 % slower at K=21, d=5M)
 constexpr int kMeanFiles = 3;
 
-template <int R, bool VEC>
+template <int R>
 __global__ void __launch_bounds__(kBlock)
 fused_mean_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
                   int64_t d, const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
@@ -489,7 +492,7 @@ fused_mean_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_o
                 if (i < f) {
 #pragma unroll
                     for (int s = 0; s < R; ++s)
-                        load4<VEC>(g + replica_row(row_of, i, R, s) * d, k, kend, v[b][s]);
+                        load4(g + replica_row(row_of, i, R, s) * d, k, kend, v[b][s]);
                 }
             }
 #pragma unroll
@@ -541,7 +544,6 @@ fused_mean_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_o
 constexpr int kMeanRows = 8;
 constexpr int64_t kMeanTileCols = kBlock * 4;   // coordinates per mean tile: four per thread
 
-template <bool VEC>
 __global__ void __launch_bounds__(kBlock)
 mean_kernel(const float *__restrict__ g, int64_t d,
             const int32_t *__restrict__ rows, const int32_t *__restrict__ n_sel,
@@ -560,7 +562,7 @@ mean_kernel(const float *__restrict__ g, int64_t d,
             uint32_t v[kMeanRows][4];
 #pragma unroll
             for (int b = 0; b < kMeanRows; ++b)
-                if (j0 + b < n) load4<VEC>(g + (int64_t)rows[j0 + b] * d, k, d, v[b]);
+                if (j0 + b < n) load4(g + (int64_t)rows[j0 + b] * d, k, d, v[b]);
 #pragma unroll
             for (int b = 0; b < kMeanRows; ++b)
                 if (j0 + b < n) {
@@ -791,7 +793,7 @@ constexpr int kDirtyBatch = 4;         // moved files per burst of loads
 // (b' + 1) << cshift), b' = 32w + b, when a listed pair differs there --
 // every bit when the kept files differ or more files moved than the list
 // holds.
-template <int R, bool VEC>
+template <int R>
 __global__ void __launch_bounds__(kBlock)
 dirty_tiles_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
                    int64_t d, int cshift, int64_t nbits,
@@ -852,8 +854,8 @@ dirty_tiles_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_
 #pragma unroll
                 for (int u = 0; u < kDirtyBatch; ++u) {
                     if (x0 + u < n) {
-                        load4<VEC>(g + (int64_t)moved[2 * (x0 + u)] * d, k, d, va[u]);
-                        load4<VEC>(g + (int64_t)moved[2 * (x0 + u) + 1] * d, k, d, vb[u]);
+                        load4(g + (int64_t)moved[2 * (x0 + u)] * d, k, d, va[u]);
+                        load4(g + (int64_t)moved[2 * (x0 + u) + 1] * d, k, d, vb[u]);
                     }
                 }
                 uint32_t diff = 0u;
@@ -912,8 +914,6 @@ int num_cus() {
     }
     return cus;
 }
-
-bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 int64_t grid_for(int64_t work, int64_t cap) { return work < cap ? (work < 1 ? 1 : work) : cap; }
 
@@ -986,12 +986,8 @@ hipError_t launch_agree(const float *g, const int32_t *row_of, int64_t f, int r,
     if (kend <= 0 || f <= 0) return hipSuccess;
     const int64_t nchunks = (kend + kAgreeChunk - 1) / kAgreeChunk;
     const unsigned grid = (unsigned)grid_for(f * nchunks, (int64_t)num_cus() * 16);
-    const bool vec = (d % 4 == 0) && aligned16(g);
-#define ASPIS_AGREE(RR)                                                              \
-    if (vec)                                                                         \
-        agree_kernel<RR, true><<<grid, kBlock, 0, s>>>(g, row_of, f, d, kend, nchunks, pair_diff); \
-    else                                                                             \
-        agree_kernel<RR, false><<<grid, kBlock, 0, s>>>(g, row_of, f, d, kend, nchunks, pair_diff);
+#define ASPIS_AGREE(RR) \
+    agree_kernel<RR><<<grid, kBlock, 0, s>>>(g, row_of, f, d, kend, nchunks, pair_diff);
     switch (r) {
     case 3: ASPIS_AGREE(3) break;
     case 5: ASPIS_AGREE(5) break;
@@ -1033,12 +1029,8 @@ hipError_t launch_agree_file(const float *g, const int32_t *row_of, int64_t f, i
     if (f <= 0) return hipSuccess;
     if (!probe_valid(probe, d)) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)grid_for(f, (int64_t)num_cus() * 8);
-    const bool vec = (d % 4 == 0) && aligned16(g);
-#define ASPIS_AGREE_FILE(RR)                                                                    \
-    if (vec)                                                                                    \
-        agree_file_kernel<RR, true><<<grid, kBlock, 0, s>>>(g, row_of, f, d, probe, pair_diff); \
-    else                                                                                        \
-        agree_file_kernel<RR, false><<<grid, kBlock, 0, s>>>(g, row_of, f, d, probe, pair_diff);
+#define ASPIS_AGREE_FILE(RR) \
+    agree_file_kernel<RR><<<grid, kBlock, 0, s>>>(g, row_of, f, d, probe, pair_diff);
     switch (r) {
     case 3: ASPIS_AGREE_FILE(3) break;
     case 5: ASPIS_AGREE_FILE(5) break;
@@ -1154,7 +1146,7 @@ int64_t ws_lds_bytes(int64_t f, int r, int T, int sweeps, bool table_in_lds, boo
            (table_in_lds ? f * r * (ws_offsets(T, half) ? 8 : 4) : 0);
 }
 
-// Warp-specialised single pass (16-byte aligned rows): plans as for the
+// Warp-specialised single pass (rows of four coordinates or more): plans as for the
 // median above (the wide split without a row table in LDS).  r = 5: half-key
 // tiles of the file-major tensor, even split (five 16-byte chunks a sweep
 // leave the streaming role no registers for more).
@@ -1273,7 +1265,7 @@ bool fused_supported(int64_t f, int r) {
 
 hipError_t launch_median(const float *g, int64_t d, const Workspace &ws, int64_t f,
                          float *out, hipStream_t s, TileUse *use, bool full_keys, bool repair) {
-    const bool vec = (d % 4 == 0) && aligned16(g);
+    const bool vec = d >= 4;
     KernelPlan k;
     if (!plan_median(f, vec, &k, full_keys)) return hipErrorInvalidValue;
     if (use) *use = TileUse{k.tile_cols, k.half_keys};
@@ -1301,12 +1293,7 @@ hipError_t launch_median(const float *g, int64_t d, const Workspace &ws, int64_t
     const size_t lds = (size_t)k.lds_bytes;
     const unsigned grid = (unsigned)tile_grid(ntiles, lds);
 #define ASPIS_MED(TT)                                                                        \
-    if (vec)                                                                                 \
-        median_kernel<TT, true><<<grid, tile_block<TT>(), lds, s>>>(g, d, ws.rows, ws.n_sel, \
-                                                                   ntiles, out, mask);       \
-    else                                                                                     \
-        median_kernel<TT, false><<<grid, tile_block<TT>(), lds, s>>>(g, d, ws.rows, ws.n_sel, \
-                                                                    ntiles, out, mask);
+    median_kernel<TT><<<grid, tile_block<TT>(), lds, s>>>(g, d, ws.rows, ws.n_sel, ntiles, out, mask);
     switch (T) {
     case 64: ASPIS_MED(64) break;
     case 32: ASPIS_MED(32) break;
@@ -1329,7 +1316,6 @@ hipError_t launch_save_sel(const Workspace &ws, int64_t f, hipStream_t s) {
 hipError_t launch_dirty_tiles(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
                               const Workspace &ws, const uint32_t *pair_diff, int tile_cols,
                               hipStream_t s) {
-    const bool vec = (d % 4 == 0) && aligned16(g);
     if (f <= 0 || d <= 0 || tile_cols < 4 || (tile_cols & (tile_cols - 1)) != 0)
         return hipErrorInvalidValue;
     const int64_t ntiles = (d + tile_cols - 1) / tile_cols;
@@ -1338,15 +1324,9 @@ hipError_t launch_dirty_tiles(const float *g, const int32_t *row_of, int64_t f, 
     int cshift = gshift;   // columns per bit: tile_cols << gshift
     for (int c = tile_cols; c > 1; c >>= 1) ++cshift;
     const unsigned grid = (unsigned)grid_for((nbits + 31) / 32, (int64_t)num_cus() * 8);
-#define ASPIS_DIRTY(RR)                                                                         \
-    if (vec)                                                                                    \
-        dirty_tiles_kernel<RR, true><<<grid, kBlock, 0, s>>>(g, row_of, f, d, cshift,          \
-                                                             nbits, ws.sel_prev, ws.sel,       \
-                                                             pair_diff, ws.dirty, ws.repair);  \
-    else                                                                                        \
-        dirty_tiles_kernel<RR, false><<<grid, kBlock, 0, s>>>(g, row_of, f, d, cshift,         \
-                                                              nbits, ws.sel_prev, ws.sel,      \
-                                                              pair_diff, ws.dirty, ws.repair);
+#define ASPIS_DIRTY(RR)                                                                       \
+    dirty_tiles_kernel<RR><<<grid, kBlock, 0, s>>>(g, row_of, f, d, cshift, nbits, ws.sel_prev, \
+                                                   ws.sel, pair_diff, ws.dirty, ws.repair);
     switch (r) {
     case 3: ASPIS_DIRTY(3) break;
     case 5: ASPIS_DIRTY(5) break;
@@ -1360,8 +1340,8 @@ hipError_t launch_dirty_tiles(const float *g, const int32_t *row_of, int64_t f, 
 hipError_t launch_fused(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
                         const Workspace &ws, uint32_t *pair_diff, float *out, hipStream_t s,
                         TileUse *use, bool full_keys) {
-    const bool vec = (d % 4 == 0) && aligned16(g);
     const bool ind = row_of != nullptr;
+    const bool vec = d >= 4;
     KernelPlan k;
     if (!plan_fused(f, r, vec, ind, &k, full_keys)) return hipErrorInvalidValue;
     if (use) *use = TileUse{k.tile_cols, k.half_keys};
@@ -1376,13 +1356,9 @@ hipError_t launch_fused(const float *g, const int32_t *row_of, int64_t f, int r,
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)tile_grid(ntiles, lds);
-#define ASPIS_FUSED(TT, RR)                                                                  \
-    if (vec)                                                                                 \
-        fused_kernel<TT, RR, true><<<grid, tile_block<TT>(), lds, s>>>(                      \
-            g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, ntiles, pair_diff, out);              \
-    else                                                                                     \
-        fused_kernel<TT, RR, false><<<grid, tile_block<TT>(), lds, s>>>(                     \
-            g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, ntiles, pair_diff, out);
+#define ASPIS_FUSED(TT, RR)                               \
+    fused_kernel<TT, RR><<<grid, tile_block<TT>(), lds, s>>>( \
+        g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, ntiles, pair_diff, out);
 #define ASPIS_FUSED_R(TT)                     \
     switch (r) {                              \
     case 3: ASPIS_FUSED(TT, 3) break;         \
@@ -1417,14 +1393,9 @@ hipError_t launch_fused_mean(const float *g, const int32_t *row_of, int64_t f, i
     // left K=21, d=5M 7 % slower)
     const unsigned grid = (unsigned)grid_for((nq + kBlock - 1) / kBlock, (int64_t)num_cus() * 8);
     const size_t lds = (size_t)f * 4;
-    const bool vec = (d % 4 == 0) && aligned16(g);
 #define ASPIS_FMEAN(RR)                                                                      \
-    if (vec)                                                                                 \
-        fused_mean_kernel<RR, true><<<grid, kBlock, lds, s>>>(g, row_of, f, d, ws.sel,       \
-                                                              ws.pos, ws.n_sel, pair_diff, out); \
-    else                                                                                     \
-        fused_mean_kernel<RR, false><<<grid, kBlock, lds, s>>>(g, row_of, f, d, ws.sel,      \
-                                                               ws.pos, ws.n_sel, pair_diff, out);
+    fused_mean_kernel<RR><<<grid, kBlock, lds, s>>>(g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, \
+                                                    pair_diff, out);
     switch (r) {
     case 3: ASPIS_FMEAN(3) break;
     case 5: ASPIS_FMEAN(5) break;
@@ -1445,17 +1416,14 @@ hipError_t launch_mean(const float *g, int64_t d, const Workspace &ws, float *ou
         mask.count = ws.repair;
         mask.gshift = dirty_gran_shift(ntiles);
     }
-    if ((d % 4 == 0) && aligned16(g))
-        mean_kernel<true><<<grid, kBlock, 0, s>>>(g, d, ws.rows, ws.n_sel, out, mask);
-    else
-        mean_kernel<false><<<grid, kBlock, 0, s>>>(g, d, ws.rows, ws.n_sel, out, mask);
+    mean_kernel<<<grid, kBlock, 0, s>>>(g, d, ws.rows, ws.n_sel, out, mask);
     return hipGetLastError();
 }
 
 int reduce_tile_cols(const float *g, int64_t f, int64_t d, bool mean, bool full_keys) {
     if (mean) return (int)kMeanTileCols;
+    const bool vec = d >= 4;
     KernelPlan k;
-    const bool vec = (d % 4 == 0) && aligned16(g);
     return plan_median(f, vec, &k, full_keys) ? k.tile_cols : 0;
 }
 

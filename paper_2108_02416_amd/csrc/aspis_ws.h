@@ -149,12 +149,12 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
             uint4 q[R];
         };
         // issue the row loads of sweep x of tile t.  Every load is in bounds:
-        // a lane past the end of the rows (tail tile; d % 4 == 0) reads the
-        // last chunk of its row instead (a repeated chunk changes neither
-        // the agreement bits nor any written median), and a lane past the
-        // last file loads nothing (proc_sweep ignores it).
+        // a lane at or past the end of the rows reads the last four
+        // coordinates of its row instead (chunk_col; repeated ones change
+        // neither the agreement bits nor any written median), and a lane past
+        // the last file loads nothing (proc_sweep ignores it).
         auto load_sweep = [&](int64_t t, int x) __attribute__((always_inline)) {
-            const int64_t col = min(t * T + 4 * cq, d - 4);
+            const int64_t col = chunk_start(t * T + 4 * cq, d);
             if constexpr (IND) {
                 int i = j0;
                 asm volatile("" : "+v"(i));   // row addresses recomputed per tile
@@ -301,6 +301,7 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
     } else {
         __syncthreads();
         for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+            auto col = [&](int c) __attribute__((always_inline)) { return chunk_col(t * T, c, d); };
             if (n > 0) {
                 if constexpr (HALF) {
                     // tile row j is file j: its guessed replica's row of g
@@ -310,10 +311,9 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
                         if constexpr (IND) return row_offset(j * R + (int)(q & 7));
                         return ((int64_t)j * R + (q & 7)) * d * 4;
                     };
-                    select_half_tile<T, G, RPI, RPI / G * SW / 2>(
-                        tile, n, t * T, d, out, tid - FILL, g, row);
+                    select_half_tile<T, G, RPI, RPI / G * SW / 2>(tile, n, out, tid - FILL, g, row, col);
                 } else {
-                    select_tile<T, G>(tile, hist, n, t * T, d, out, tid - FILL);
+                    select_tile<T, G>(tile, hist, n, out, tid - FILL, col);
                 }
             }
             __syncthreads();
@@ -382,7 +382,7 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
         // rows it re-reads the row's last chunk, whose median is never
         // written)
         auto load_row = [&](int64_t t, int x) __attribute__((always_inline)) {
-            const int64_t col = min(t * T + 4 * cq, d - 4);
+            const int64_t col = chunk_start(t * T + 4 * cq, d);
             int j = j0;
             asm volatile("" : "+v"(j));   // offsets read per tile, not held
             j = min(j + x * RPI, n - 1);
@@ -457,14 +457,14 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
         __syncthreads();
         for (int64_t t = mask.next(blockIdx.x, gridDim.x, ntiles); t < ntiles;
              t = mask.next(t + gridDim.x, gridDim.x, ntiles)) {
+            auto col = [&](int c) __attribute__((always_inline)) { return chunk_col(t * T, c, d); };
             if constexpr (HALF) {
                 auto row = [&](int j) __attribute__((always_inline)) -> int64_t {
                     return j < n ? row_offset(j) : -1;
                 };
-                select_half_tile<T, G, RPI, RPI / G * SW / 2>(
-                    tile, n, t * T, d, out, tid - FILL, g, row);
+                select_half_tile<T, G, RPI, RPI / G * SW / 2>(tile, n, out, tid - FILL, g, row, col);
             } else {
-                select_tile<T, G>(tile, hist, n, t * T, d, out, tid - FILL);
+                select_tile<T, G>(tile, hist, n, out, tid - FILL, col);
             }
             __syncthreads();
             __syncthreads();
