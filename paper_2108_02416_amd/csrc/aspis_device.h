@@ -641,13 +641,20 @@ __device__ __forceinline__ void select_half_tile(uint32_t *tile, int nk, float *
 // One 16-byte load from a replica row that the pass reads once: a
 // non-temporal load, which streams past the caches instead of filling them
 // with lines nothing reads again (measured 3-6 % faster than a plain load on
-// the 61 GB single pass).  Any 4-byte alignment: global memory takes a
-// 16-byte access at a dword boundary, so rows of any length are read this
-// way (455 files, d = 2.5M + 1: 2.50 ms, against 5.63 ms with one 4-byte load a
-// coordinate).
+// the 61 GB single pass), or (NT false) a plain load, where the lines a row
+// segment straddles are read by another workgroup of the XCD as well
+// (first_tile).  Any 4-byte alignment: global memory takes a 16-byte access
+// at a dword boundary, so rows of any length are read this way (455 files,
+// d = 2.5M + 1: 2.50 ms, against 5.63 ms with one 4-byte load a coordinate).
+template <bool NT = true>
 __device__ __forceinline__ uint4 load_stream(const float *p) {
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4), aligned(4)));
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    const u32x4 *q = reinterpret_cast<const u32x4 *>(p);
+    u32x4 v;
+    if constexpr (NT)
+        v = __builtin_nontemporal_load(q);
+    else
+        v = *q;
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
@@ -665,6 +672,25 @@ __device__ __forceinline__ void load4(const float *row, int64_t k, int64_t kend,
         for (int e = 0; e < 4; ++e)
             v[e] = (k + e < kend) ? __float_as_uint(row[k + e]) : 0u;
     }
+}
+
+// The first tile of a workgroup of a persistent grid of G (it takes every
+// G-th tile from there).  Workgroups go to the 8 XCDs, each with its own L2,
+// in turn, so in workgroup order neighbouring tiles are read by different
+// XCDs; by_xcd gives the workgroups of one XCD a run of neighbouring tiles
+// instead.  It pays where a row segment of a tile does
+// not cover whole 128-byte lines (rows off line boundaries, or tiles of
+// fewer than 32 columns): with plain loads the line two neighbouring tiles
+// share then comes from the XCD's L2 the second time.  1,330 files, d =
+// 1.25M (rows 64 bytes off every other time), 32 columns: 4.28 -> 3.34 ms
+// (with non-temporal loads 4.02 ms); 455 files, d = 2.5M + 1, 128 columns:
+// 2.50 -> 2.22 ms (2.37).  On whole lines it is slower: 455 files, d =
+// 11.2M, 9.21 -> 9.37 ms, and with plain loads 9.99 ms.
+__device__ __forceinline__ int64_t first_tile(bool by_xcd) {
+    const unsigned b = blockIdx.x, G = gridDim.x;
+    if (!by_xcd) return b;
+    const unsigned x = b % 8, rest = G % 8;
+    return x * (G / 8) + (x < rest ? x : rest) + b / 8;
 }
 
 // Column k0 + c of a tile whose lanes read whole 16-byte chunks: the chunk

@@ -915,6 +915,12 @@ int num_cus() {
     return cus;
 }
 
+// Row segments of T columns cover whole 128-byte lines: no line is shared by
+// neighbouring tiles.
+bool whole_lines(const float *g, int64_t d, int T) {
+    return (uintptr_t)g % 128 == 0 && d % 32 == 0 && T % 32 == 0;
+}
+
 int64_t grid_for(int64_t work, int64_t cap) { return work < cap ? (work < 1 ? 1 : work) : cap; }
 
 // widest tile T whose [rows x T] key block (plus extra bytes) fits in LDS
@@ -1280,7 +1286,8 @@ hipError_t launch_median(const float *g, int64_t d, const Workspace &ws, int64_t
     if (k.kind == kKernelMedianWs) {
         const unsigned grid = (unsigned)grid_for(ntiles, (int64_t)num_cus());
         const MedianWsFn fn = median_ws_fn(mws_plan(f, vec, full_keys));
-        fn<<<grid, kWsThreads, (size_t)k.lds_bytes, s>>>(g, d, ws.rows, ws.n_sel, ntiles, out, mask);
+        fn<<<grid, kWsThreads, (size_t)k.lds_bytes, s>>>(g, d, ws.rows, ws.n_sel, ntiles,
+                                                         !whole_lines(g, d, T), out, mask);
         return hipGetLastError();
     }
     if (k.kind == kKernelMedianRadix) {
@@ -1350,7 +1357,9 @@ hipError_t launch_fused(const float *g, const int32_t *row_of, int64_t f, int r,
     const size_t lds = (size_t)k.lds_bytes;
     if (k.kind == kKernelFusedWs) {
         const unsigned grid = (unsigned)grid_for(ntiles, (int64_t)num_cus());
-        const FusedWsFn fn = fused_ws_fn(ws_plan(f, r, vec, ind, full_keys), ind);
+        WsPlan p = ws_plan(f, r, vec, ind, full_keys);
+        p.lines = whole_lines(g, d, T);
+        const FusedWsFn fn = fused_ws_fn(p, ind);
         fn<<<grid, kWsThreads, lds, s>>>(g, ind ? row_of : nullptr, f, d, ws.sel, ws.pos, ws.n_sel,
                                          ntiles, pair_diff, out);
         return hipGetLastError();

@@ -57,7 +57,9 @@ __host__ __device__ constexpr int64_t ws_words_before_table(int64_t f, int r, in
     return (w + 1) & ~int64_t{1};
 }
 
-template <int T, int R, int SW, bool IND, bool HALF, int FILL, bool RTG = false>
+// NT: tiles of whole 128-byte lines, non-temporal loads, workgroup order;
+// else plain loads, each XCD a run of neighbouring tiles (first_tile).
+template <int T, int R, int SW, bool IND, bool HALF, int FILL, bool RTG, bool NT>
 __global__ void __launch_bounds__(kWsThreads)
 fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f, int64_t d,
                 const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
@@ -134,6 +136,7 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
     if (wave < FILL / 64) {
         const int cq = tid % CPR, j0 = tid / CPR;
         const int64_t sweep = (int64_t)RPI * R * d;   // elements between sweeps
+        const int f32 = (int)f;
         uint32_t keys[SW][KW];
         // pair-difference bits of the lane's files (sweep x: bits
         // NP*(x % PER) of word x / PER), ORed over every tile in registers
@@ -153,37 +156,30 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         // coordinates of its row instead (chunk_col; repeated ones change
         // neither the agreement bits nor any written median), and a lane past
         // the last file loads nothing (proc_sweep ignores it).
-        auto load_sweep = [&](int64_t t, int x) __attribute__((always_inline)) {
+        // the lane's chunk of tile t in row 0 (IND) or in its first file's
+        // first row
+        auto tile_base = [&](int64_t t) __attribute__((always_inline)) -> const float * {
             const int64_t col = chunk_start(t * T + 4 * cq, d);
-            if constexpr (IND) {
-                int i = j0;
-                asm volatile("" : "+v"(i));   // row addresses recomputed per tile
-                i += x * RPI;
-                Chunks c;
-                if (i < f) {
-#pragma unroll
-                    for (int s = 0; s < R; ++s)
-                        c.q[s] = load_stream(reinterpret_cast<const float *>(
-                            reinterpret_cast<const char *>(g + col) + row_offset(i * R + s)));
-                } else {
-#pragma unroll
-                    for (int s = 0; s < R; ++s) c.q[s] = make_uint4(0u, 0u, 0u, 0u);
-                }
-                return c;
-            }
-            const float *base = g + (int64_t)j0 * R * d + col;
-            int lim = (int)(f - j0);   // sweeps x with x * RPI < lim hold a file
-            // opaque copies of the tile's base address, the limit and the
-            // sweep stride: every row address and check below is recomputed
-            // from them, instead of the compiler carrying one pointer, one
-            // lane mask and one offset per sweep across tiles
+            return g + (IND ? col : (int64_t)j0 * R * d + col);
+        };
+        auto load_sweep = [&](const float *base, int x) __attribute__((always_inline)) {
+            // opaque copies of the lane's first file and the sweep stride:
+            // every row address and check below is recomputed from them,
+            // instead of the compiler carrying one pointer, one lane mask and
+            // one offset per sweep across tiles
+            int i = j0;
             int64_t stride = sweep;
-            asm volatile("" : "+v"(base), "+v"(lim), "+s"(stride));
+            asm volatile("" : "+v"(i), "+s"(stride));
+            i += x * RPI;
             Chunks c;
-            if (x * RPI < lim) {
+            if (i < f32) {
                 const float *rows = base + x * stride;
 #pragma unroll
-                for (int s = 0; s < R; ++s) c.q[s] = load_stream(rows + s * d);
+                for (int s = 0; s < R; ++s)
+                    c.q[s] = load_stream<NT>(
+                        IND ? reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) +
+                                                              row_offset(i * R + s))
+                            : rows + s * d);
             } else {
 #pragma unroll
                 for (int s = 0; s < R; ++s) c.q[s] = make_uint4(0u, 0u, 0u, 0u);
@@ -194,12 +190,12 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         // (HALF: its high key halves, packed two to a register, 0xFFFF for a
         // file past the last or dropped)
         auto proc_sweep = [&](int x, Chunks c) __attribute__((always_inline)) {
-            const int i = j0 + x * RPI;   // f <= C(64,3) here
+            const int i = j0 + x * RPI;
             if constexpr (HALF) {
                 keys[x][0] = 0xFFFFFFFFu;
                 keys[x][1] = 0xFFFFFFFFu;
             }
-            if (i < f) {
+            if (i < f32) {
                 uint32_t diff = 0u;
                 int p = 0;
 #pragma unroll
@@ -241,14 +237,13 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         // tile t from the ring, refilled with t's later sweeps and then with
         // the first ones of tile tn
         auto stream_tile = [&](int64_t t, int64_t tn) __attribute__((always_inline)) {
+            const float *base = tile_base(t);
 #pragma unroll
             for (int x = 0; x < SW; ++x) {
                 proc_sweep(x, c[x % B]);
                 __builtin_amdgcn_sched_barrier(0);
-                if (x + B < SW)
-                    c[x % B] = load_sweep(t, x + B);
-                else if (tn < ntiles)
-                    c[x % B] = load_sweep(tn, x + B - SW);
+                if (x == SW - B) base = tile_base(tn);
+                if (x + B < SW || tn < ntiles) c[x % B] = load_sweep(base, (x + B) % SW);
                 // no scheduling across sweeps, which would hold more loads in
                 // registers than fit
                 __builtin_amdgcn_sched_barrier(0);
@@ -271,10 +266,10 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
                 }
             }
         };
-        int64_t t = blockIdx.x;
+        int64_t t = first_tile(!NT);
         if (t < ntiles) {
 #pragma unroll
-            for (int x = 0; x < B; ++x) c[x] = load_sweep(t, x);
+            for (int x = 0; x < B; ++x) c[x] = load_sweep(tile_base(t), x);
             stream_tile(t, t + gridDim.x);
             put_tile();
         }
@@ -300,7 +295,7 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         }
     } else {
         __syncthreads();
-        for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        for (int64_t t = first_tile(!NT); t < ntiles; t += gridDim.x) {
             auto col = [&](int c) __attribute__((always_inline)) { return chunk_col(t * T, c, d); };
             if (n > 0) {
                 if constexpr (HALF) {
@@ -332,6 +327,8 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
 // stream the kept rows of tile t+1 (one row per kept file, through the row
 // list of the selection) into registers while waves 8-15 select on tile t.
 // Used by the two-pass path and after a wrong guess of the single pass.
+// Its loads are plain ones: 455 kept files, d = 1.5M, 625 us, against 641 with
+// non-temporal ones; by_xcd as in the single pass (first_tile).
 
 // the ring of the streaming role's loads (ws_ring), one 16-byte load a
 // sweep: six sweeps (10 measured 1 % slower at 455 kept files)
@@ -347,8 +344,8 @@ constexpr int mws_ring() {
 template <int T, int SW, bool HALF, int FILL>
 __global__ void __launch_bounds__(kWsThreads)
 median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restrict__ rows,
-                 const int32_t *__restrict__ n_sel, int64_t ntiles, float *__restrict__ out,
-                 TileMask mask) {
+                 const int32_t *__restrict__ n_sel, int64_t ntiles, bool by_xcd,
+                 float *__restrict__ out, TileMask mask) {
     extern __shared__ __align__(16) uint32_t smem[];
     constexpr int G = (kWsThreads - FILL) / T;   // selection lanes per column
     constexpr int CPR = T / 4;           // float4 chunks per row segment
@@ -386,7 +383,7 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
             int j = j0;
             asm volatile("" : "+v"(j));   // offsets read per tile, not held
             j = min(j + x * RPI, n - 1);
-            return load_stream(reinterpret_cast<const float *>(
+            return load_stream<false>(reinterpret_cast<const float *>(
                 reinterpret_cast<const char *>(g + col) + row_offset(j)));
         };
         auto to_keys = [&](int x, uint4 q) __attribute__((always_inline)) {
@@ -435,7 +432,7 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
         // the workgroup's tiles: t, then tn (whose first sweeps are loaded
         // before the hand-over of t), then tnn
         const int64_t G0 = gridDim.x;
-        int64_t t = mask.next(blockIdx.x, G0, ntiles);
+        int64_t t = mask.next(first_tile(by_xcd), G0, ntiles);
         int64_t tn = mask.next(t + G0, G0, ntiles);
         if (t < ntiles) {
 #pragma unroll
@@ -455,7 +452,7 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
         }
     } else {
         __syncthreads();
-        for (int64_t t = mask.next(blockIdx.x, gridDim.x, ntiles); t < ntiles;
+        for (int64_t t = mask.next(first_tile(by_xcd), gridDim.x, ntiles); t < ntiles;
              t = mask.next(t + gridDim.x, gridDim.x, ntiles)) {
             auto col = [&](int c) __attribute__((always_inline)) { return chunk_col(t * T, c, d); };
             if constexpr (HALF) {
@@ -491,6 +488,8 @@ struct WsPlan {
     bool half = false;
     int fill = kWsFill;
     bool rtg = false;   // row table read from global memory (not in LDS)
+    // row segments of whole 128-byte lines (the single pass's NT)
+    bool lines = true;
 };
 
 constexpr int kWsFillWide = 768;
@@ -503,10 +502,13 @@ constexpr int kWsFillWide = 768;
 // a plan's kernel in the tables: tile columns, sweeps, half keys
 constexpr int ws_key(int T, int sweeps, bool half) { return T * 1000 + sweeps * 10 + (half ? 1 : 0); }
 
+// the kernel of plan p for tiles of whole 128-byte lines or not
+#define ASPIS_NT(kernel, ...) (p.lines ? &kernel<__VA_ARGS__, true> : &kernel<__VA_ARGS__, false>)
+
 using FusedWsFn = void (*)(const float *, const int32_t *, int64_t, int64_t, const int32_t *,
                            const int32_t *, const int32_t *, int64_t, uint32_t *, float *);
 using MedianWsFn = void (*)(const float *, int64_t, const int32_t *, const int32_t *, int64_t,
-                            float *, TileMask);
+                            bool, float *, TileMask);
 
 // nullptr: not built.  fused_ws_fn looks in the family of the plan.
 FusedWsFn fused_ws_fn(const WsPlan &p, bool ind);

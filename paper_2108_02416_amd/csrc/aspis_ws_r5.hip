@@ -8,13 +8,13 @@ FusedWsFn fused_ws_r5_fn(const WsPlan &p) {
     if (p.r != 5 || !p.half || p.fill != kWsFill || p.rtg) return nullptr;
     switch (ws_key(p.T, p.sweeps, p.half)) {
 #define ASPIS_FWS5(TT, SWW) \
-    case ws_key(TT, SWW, true): return &fused_ws_kernel<TT, 5, SWW, false, true, kWsFill, false>;
+    case ws_key(TT, SWW, true): return ASPIS_NT(fused_ws_kernel, TT, 5, SWW, false, true, kWsFill, false);
         ASPIS_FWS5(128, 16)
         ASPIS_FWS5(128, 30)
         ASPIS_FWS5(64, 28)
         ASPIS_FWS5(32, 24)
         ASPIS_FWS5(32, 32)
-        ASPIS_FWS5(16, 24)
+    case ws_key(16, 24, true): return &fused_ws_kernel<16, 5, 24, false, true, kWsFill, false, false>;
 #undef ASPIS_FWS5
     default: return nullptr;
     }

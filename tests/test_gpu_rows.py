@@ -1,7 +1,8 @@
 """Rows of any length: the kernels read 16-byte chunks at 4-byte boundaries,
 and the chunk holding a row's end is read four coordinates before it.  Every
 remainder of the row length by four and by the tile, in the persistent grid's
-steady state, against the oracle."""
+steady state, against the oracle.  Row lengths that keep rows on 128-byte
+lines and others take different kernels (the tile order and the loads)."""
 import numpy as np
 import pytest
 
@@ -30,6 +31,12 @@ pytestmark = pytest.mark.gpu
     (10, 7, 2, "file", 0, 20, 1),
     (15, 3, 4, "file", 0, 0, 5),
     (15, 3, 4, "file", 0, 0, 7),
+    # rows on 128-byte lines, the last tile ragged
+    (15, 3, 4, "file", 0, 2 * CUS + 3, 32),
+    (15, 3, 4, "worker", 0, CUS + 3, 96),
+    (21, 3, 5, "file", 0, 2 * CUS // 4 + 1, 32),
+    (25, 3, 6, "file", 0, CUS // 4 + 1, 64),
+    (11, 5, 3, "file", 0, CUS + 1, 64),
 ])
 def test_any_row_length(K, r, q, layout, flags, tiles, extra):
     d = 128 * tiles + extra
