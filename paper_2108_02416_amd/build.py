@@ -24,7 +24,8 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
 SOURCES = ["aspis_host.cpp", "aspis_sim.cpp", "aspis_kernels.hip", "aspis_ws_r3.hip",
-           "aspis_ws_r3_table.hip", "aspis_ws_r5.hip", "aspis_ws_median.hip"]
+           "aspis_ws_r3_table.hip", "aspis_ws_r5.hip", "aspis_ws_r7.hip",
+           "aspis_ws_median.hip"]
 
 
 def _run(cmd: list[str]) -> list[str]:

@@ -1092,6 +1092,10 @@ int round_sweeps(int64_t sw, bool half, int T, int fill) {
 // split only: with the even split the streaming role would hold the
 // table's addresses next to its keys (the kernels built for a global
 // table are wide-split ones).
+// r = 7: at most 16 sweeps of 64 or 128 columns, 28 of 32 or 16 (seven chunks
+// a sweep; the keys of more sweeps spill): 330 files, d = 0.4M, 64 columns of
+// 12 sweeps 0.58 ms, 128 of 24 0.66 ms; 792 files, d = 0.2M, 32 of 16 0.71,
+// 64 of 28 0.88 ms; 1,716 files, d = 0.1M, 32 of 28 0.87, 16 of 16 0.91 ms.
 template <typename LdsFn>
 WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r = 3) {
     WsPlan p;
@@ -1103,7 +1107,10 @@ WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r
             if (rtg && fill != kWsFillWide) continue;
             const int64_t rpi = half_rpi(T, fill);
             const int64_t sw = (f + rpi - 1) / rpi;
-            const int64_t max_sw = fill == kWsFillWide ? 24 : (ind || r != 3) ? 32 : max_half_sweeps(T, fill);
+            const int64_t max_sw = fill == kWsFillWide ? 24
+                                   : r == 7            ? (T > 32 ? 16 : 28)
+                                   : (ind || r != 3)   ? 32
+                                                       : max_half_sweeps(T, fill);
             if (sw > max_sw) continue;
             const int sweeps = round_sweeps(sw, true, T, fill);
             if (lds(T, sweeps, fill) > kLdsBytes) continue;
@@ -1153,21 +1160,27 @@ int64_t ws_lds_bytes(int64_t f, int r, int T, int sweeps, bool table_in_lds, boo
 }
 
 // Warp-specialised single pass (rows of four coordinates or more): plans as for the
-// median above (the wide split without a row table in LDS).  r = 5: half-key
-// tiles of the file-major tensor, even split (five 16-byte chunks a sweep
-// leave the streaming role no registers for more).
+// median above (the wide split without a row table in LDS).  r = 5 and 7: the
+// even split.
 WsPlan ws_plan(int64_t f, int r, bool vec, bool ind, bool full_keys = false) {
     WsPlan p;
     if (!vec) return p;
-    if (r == 5 && !ind && !full_keys) {
-        p.r = 5;
-        WsPlan h = half_plan(f, 0, false, false, [&](int T, int sweeps, int fill) {
-            return ws_lds_bytes(f, r, T, sweeps, false, true, fill);
-        }, 5);
-        h.r = 5;
-        return h.T != 0 ? h : WsPlan{};
+    p.r = r;
+    if (r != 3) {
+        // full keys: 64 columns and up to four sweeps (128 files), what the
+        // registers hold next to five or seven chunks a sweep; half keys
+        // beyond
+        if (ws_lds_bytes(f, r, 64, 0, ind, false, kWsFill) <= kLdsBytes && f <= 4 * kWsFill / 16) {
+            p.T = 64;
+            p.sweeps = f <= 2 * kWsFill / 16 ? 2 : 4;
+        }
+        if (full_keys) return p;
+        WsPlan h = half_plan(f, p.T, ind, false, [&](int T, int sweeps, int fill) {
+            return ws_lds_bytes(f, r, T, sweeps, ind, true, fill);
+        }, r);
+        h.r = r;
+        return h.T != 0 ? h : p;
     }
-    if (r != 3) return p;
     for (int T : {64, 32, 16, 8}) {
         if (ws_lds_bytes(f, r, T, 0, ind, false, kWsFill) > kLdsBytes) continue;
         const int64_t rpi = kWsFill / (T / 4);
@@ -1199,7 +1212,7 @@ WsPlan ws_plan(int64_t f, int r, bool vec, bool ind, bool full_keys = false) {
 }  // namespace
 
 FusedWsFn fused_ws_fn(const WsPlan &p, bool ind) {
-    if (p.r == 5) return ind ? nullptr : fused_ws_r5_fn(p);
+    if (p.r != 3) return p.r == 5 ? fused_ws_r5_fn(p, ind) : fused_ws_r7_fn(p, ind);
     return ind ? fused_ws_r3_table_fn(p) : fused_ws_r3_fn(p);
 }
 

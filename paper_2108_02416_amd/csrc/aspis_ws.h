@@ -35,7 +35,7 @@ constexpr int kWsFill = 512;       // threads of the streaming role (default spl
 // 2.78 to 2.51 ms (linear read 2.39 ms).
 template <int R, int SW, bool HALF>
 constexpr int ws_ring() {
-    if (R != 3) return SW < 24 ? 2 : 1;
+    if (R != 3) return R == 5 && SW < 24 && SW % 2 == 0 ? 2 : 1;
     if (SW > 32) return 1;
     if (SW <= (HALF ? 16 : 8) && SW % 4 == 0) return 4;
     return SW <= 24 && SW % 3 == 0 ? 3 : SW % 2 == 0 ? 2 : 1;
@@ -138,14 +138,18 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         const int64_t sweep = (int64_t)RPI * R * d;   // elements between sweeps
         const int f32 = (int)f;
         uint32_t keys[SW][KW];
-        // pair-difference bits of the lane's files (sweep x: bits
-        // NP*(x % PER) of word x / PER), ORed over every tile in registers
-        // and merged into LDS once at the end
+        // pair-difference bits of the lane's files.  r = 3 and 5: sweep x's
+        // in bits NP*(x % PER) of word x / PER, ORed over every tile in
+        // registers and merged into LDS once at the end.  r = 7 (21 bits a
+        // file) has no registers for that and adds new bits to the files'
+        // LDS words (at r = 5 that is 3 % slower: 462 files, d = 1M, 1.447
+        // against 1.400 ms)
         constexpr int NPB = R * (R - 1) / 2;
         constexpr int PER = 32 / NPB;
-        uint32_t pdacc[(SW + PER - 1) / PER];
+        uint32_t pdacc[R <= 5 ? (SW + PER - 1) / PER : 1];
+        if constexpr (R <= 5)
 #pragma unroll
-        for (int a = 0; a < (SW + PER - 1) / PER; ++a) pdacc[a] = 0u;
+            for (int a = 0; a < (SW + PER - 1) / PER; ++a) pdacc[a] = 0u;
         // the r replica chunks of one sweep, kept in registers (a value
         // type, so that no per-lane indexing can turn it into memory)
         struct Chunks {
@@ -207,7 +211,11 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
                         diff |= (y != 0u ? 1u : 0u) << p;
                         ++p;
                     }
-                pdacc[x / PER] |= diff << (NPB * (x % PER));
+                if constexpr (R <= 5) {
+                    pdacc[x / PER] |= diff << (NPB * (x % PER));
+                } else {
+                    if (diff & ~pd[i]) atomicOr(&pd[i], diff);
+                }
                 // HALF: file i's nibble, word (j0 >> 3) + x*RPI/8 (RPI is a
                 // multiple of 8), shift (j0 & 7) * 4 in every sweep
                 const int w8 = (j0 >> 3) + x * (RPI / 8), sh = (j0 & 7) * 4;
@@ -282,17 +290,18 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
             __syncthreads();
         }
         // the lane's pair-difference bits into the workgroup's words
+        if constexpr (R <= 5)
 #pragma unroll
-        for (int x = 0; x < SW; ++x) {
-            const int i = j0 + x * RPI;
-            const uint32_t b = (pdacc[x / PER] >> (NPB * (x % PER))) & ((1u << NPB) - 1u);
-            if (i < f && b) {
-                if constexpr (PDN)
-                    atomicOr(&pd[i >> 3], b << ((i & 7) * 4));
-                else
-                    atomicOr(&pd[i], b);
+            for (int x = 0; x < SW; ++x) {
+                const int i = j0 + x * RPI;
+                const uint32_t b = (pdacc[x / PER] >> (NPB * (x % PER))) & ((1u << NPB) - 1u);
+                if (i < f && b) {
+                    if constexpr (PDN)
+                        atomicOr(&pd[i >> 3], b << ((i & 7) * 4));
+                    else
+                        atomicOr(&pd[i], b);
+                }
             }
-        }
     } else {
         __syncthreads();
         for (int64_t t = first_tile(!NT); t < ntiles; t += gridDim.x) {
@@ -512,7 +521,8 @@ using MedianWsFn = void (*)(const float *, int64_t, const int32_t *, const int32
 
 // nullptr: not built.  fused_ws_fn looks in the family of the plan.
 FusedWsFn fused_ws_fn(const WsPlan &p, bool ind);
-FusedWsFn fused_ws_r5_fn(const WsPlan &p);                 // r = 5
+FusedWsFn fused_ws_r5_fn(const WsPlan &p, bool ind);       // r = 5
+FusedWsFn fused_ws_r7_fn(const WsPlan &p, bool ind);       // r = 7
 FusedWsFn fused_ws_r3_fn(const WsPlan &p);                 // r = 3, file-major
 FusedWsFn fused_ws_r3_table_fn(const WsPlan &p);           // r = 3, row table
 MedianWsFn median_ws_fn(const WsPlan &p);

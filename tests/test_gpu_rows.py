@@ -31,6 +31,14 @@ pytestmark = pytest.mark.gpu
     (10, 7, 2, "file", 0, 20, 1),
     (15, 3, 4, "file", 0, 0, 5),
     (15, 3, 4, "file", 0, 0, 7),
+    # r = 5 and 7: full keys, half keys, the row table
+    (9, 5, 2, "file", 0, CUS + 1, 4),
+    (9, 5, 2, "worker", 0, CUS + 1, 1),
+    (11, 5, 3, "worker", 0, CUS + 1, 36),
+    (9, 7, 2, "worker", 0, CUS + 1, 32),
+    (11, 7, 2, "file", 0, CUS // 2 + 1, 32),
+    (11, 7, 2, "worker", 0, CUS // 2 + 1, 3),
+    (12, 7, 2, "file", 0, 10, 7),
     # rows on 128-byte lines, the last tile ragged
     (15, 3, 4, "file", 0, 2 * CUS + 3, 32),
     (15, 3, 4, "worker", 0, CUS + 3, 96),
