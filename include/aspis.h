@@ -172,7 +172,7 @@ typedef struct {
     int32_t fused;             /* 1 if the single-pass kernel ran           */
     int32_t speculation_hit;   /* 1 if the probe's guess was confirmed      */
     int64_t probe_coords;      /* coordinates the guess was taken from      */
-    float ms_probe;            /* agreement pass over the probe             */
+    float ms_probe;            /* agreement over the probe, and the guess   */
     float ms_main;             /* main pass (fused, or detect + reduce)     */
     float ms_fallback;         /* repair or rerun after a wrong guess       */
     float ms_total;            /* first kernel to result, host steps incl.  */
@@ -230,8 +230,9 @@ typedef struct {
  * Errors as aspis_aggregate's, except that on NO_FILES `out` holds no
  * result rather than being untouched: the single pass may have written it
  * with the guessed selection before the final one kept no file.
- * Synchronises the stream: twice on the single pass (the probe's graph and
- * the full graph), once more before returning. */
+ * The guess is made on the device, so the single pass synchronises the stream
+ * once, for the full graph, when the guess held, and once more after a repair
+ * or rerun; with more than 4,096 files, once more for the probe's graph. */
 aspis_status aspis_detect_aggregate(const float *grads, int32_t K, int32_t r,
                                     int32_t q, int64_t d,
                                     const int32_t *subsets_dev,

@@ -162,17 +162,6 @@ bool use_mean(aspis_reduce mode, const aspis_clique_result *res) {
     return mode == ASPIS_REDUCE_MEAN || (mode == ASPIS_REDUCE_PAPER && res->success);
 }
 
-// Full-key tiles when on average over the probed coordinates at least this
-// many files share the high 16-bit key half of the median.  The half-key
-// tiles read back the low half of every such file, so their extra time
-// follows the mean count: 28 files tied with the median (ALIE colluders
-// sending the honest mean, K = 15) cost the half-key single pass about as
-// much as the full-key tiles cost, and data tied on a fraction x of the
-// coordinates (455 files each there) costs about x times the fully tied
-// case.  The mean, unlike a typical coordinate's count, sees ties that
-// cover less than half of the coordinates.
-constexpr uint32_t kTieFullKeys = 16;
-
 // The tie estimate: the mean, rounded up, over the probed coordinates of
 // the number of files tied with the median's high key half
 // (launch_tie_probe).
@@ -441,7 +430,7 @@ aspis_status detect_aggregate_impl(const float *grads, bool worker_major, int32_
         const uint32_t t = tie_estimate(
             reinterpret_cast<const uint32_t *>(staged_words + aspis::kStageTie), n_tie);
         local.tie_rows = (int32_t)t;
-        full_keys = t >= kTieFullKeys;
+        full_keys = t >= aspis::kTieFullKeys;
     };
     // the two-pass path: the disagreement rows and the tie counts, one sync
     uint64_t rows[aspis::kStageWords] = {};
@@ -455,12 +444,10 @@ aspis_status detect_aggregate_impl(const float *grads, bool worker_major, int32_
         decide_keys(rows);
         return aspis_clique(rows, K, q, out_res);
     };
-    // the row of every replica in a worker-major upload, in the workspace,
-    // and the repair's group count copied back.  The host memory must
-    // outlive the asynchronous copies: the guard, declared after it and so
-    // destroyed before it, waits for the stream on every return once armed
-    // (a no-op after the synchronisations of a normal return)
-    std::vector<int32_t> host_rows;
+    // the repair's group count, copied back.  The host memory must outlive
+    // the asynchronous copy: the guard, declared after it and so destroyed
+    // before it, waits for the stream on every return once armed (a no-op
+    // after the synchronisations of a normal return)
     int32_t groups = -1;
     struct DrainStream {
         hipStream_t s;
@@ -469,13 +456,10 @@ aspis_status detect_aggregate_impl(const float *grads, bool worker_major, int32_
             if (armed) (void)hipStreamSynchronize(s);
         }
     } drain{s};
+    // the row of every replica in a worker-major upload, in the workspace
     const int32_t *row_of = nullptr;
     if (worker_major) {
-        drain.armed = true;
-        host_rows.resize((size_t)f * r);
-        worker_row_table(K, r, host_rows.data());
-        ASPIS_HIP(hipMemcpyAsync(ws.row_of, host_rows.data(), host_rows.size() * sizeof(int32_t),
-                                 hipMemcpyHostToDevice, s));
+        ASPIS_HIP(aspis::launch_worker_rows(K, r, f, ws.row_of, s));
         row_of = ws.row_of;
     }
 
@@ -492,42 +476,101 @@ aspis_status detect_aggregate_impl(const float *grads, bool worker_major, int32_
             return aspis_clique(staged, K, q, out_res);
         };
         // 1) agreement on the probed coordinates -> provisional clique and
-        //    selection; the tie probe rides on the same copy to the host
+        //    selection; the tie probe rides along.  2) one pass: agreement on
+        //    every coordinate + the reduction with the guessed selection.
         local.probe_coords = probe.coords();
-        if (timing) ASPIS_HIP(hipEventRecord(ev[0], s));
-        ASPIS_HIP(aspis::launch_agree_file(grads, row_of, f, r, d, probe, det->pair_diff, s));
-        ASPIS_HIP(aspis::launch_vote_rows(det->pair_diff, subsets_dev, f, r, K, det->vote,
-                                          det->has_majority, det->disagree, ws.stage, s));
-        if (tie_probe)
-            ASPIS_HIP(aspis::launch_tie_probe(grads, row_of, f, r, d, probe, tie_dev, s));
-        if (timing) ASPIS_HIP(hipEventRecord(ev[1], s));
         aspis_clique_result guess{};
-        if ((st = staged_clique(&guess, tie_probe ? aspis::kStageWords : 65)) != ASPIS_OK)
-            return st;
-        decide_keys(staged);
-        // the reduction the guess calls for: the median (Case 2, or MEDIAN
-        // mode) or the mean (Case 1 in PAPER mode, or MEAN mode)
-        const bool guess_mean = use_mean(mode, &guess);
-        if (guess_mean ? aspis::fused_mean_supported(f, r) : aspis::fused_supported(f, r)) {
-            local.fused = 1;
-            aspis::TileUse fused_tile{};   // stays empty for the mean
-            // the guessed selection; the same launch zeroes pair_diff for
-            // the main pass
-            ASPIS_HIP(aspis::launch_select(subsets_dev, det->vote, f, r, guess.success,
-                                           honest_mask(&guess), row_of, ws, nullptr,
-                                           det->pair_diff, f, s));
-            // 2) one pass: agreement on every coordinate + the reduction with
-            //    the guessed selection
+        bool guess_mean = false, ran = false;
+        aspis::TileUse fused_tile{};   // stays empty for the mean
+        const bool may_median = mode != ASPIS_REDUCE_MEAN, may_mean = mode != ASPIS_REDUCE_MEDIAN;
+        if (f <= aspis::kDirtyWords && (!may_median || aspis::fused_supported(f, r)) &&
+            (!may_mean || aspis::fused_mean_supported(f, r))) {
+            // every reduction the guess may call for has a single pass: the
+            // guess stays on the device, and each candidate kernel runs or
+            // returns at once as it says (an empty launch costs a few
+            // microseconds, the host's part in the guess cost about 30)
+            if (timing) ASPIS_HIP(hipEventRecord(ev[0], s));
+            int split = 1;
+            ASPIS_HIP(aspis::launch_probe(grads, row_of, f, r, d, probe, ws, tie_probe ? n_tie : 0,
+                                          &split, s));
+            // half- or full-key tiles: two candidates when the tie probe
+            // decides and the plan has half keys
+            aspis::KernelPlan plan{};
+            if (may_median) aspis::plan_single_pass(f, r, d, row_of != nullptr, &plan, false);
+            const bool two = tie_probe && plan.half_keys;
+            const int keys = two         ? aspis::kKeysProbe
+                             : full_keys ? aspis::kKeysFull
+                                         : aspis::kKeysHalf;
+            ASPIS_HIP(aspis::launch_guess(subsets_dev, row_of, f, r, K, q, (int)mode, keys, n_tie,
+                                          split, det->vote, det->has_majority, det->disagree,
+                                          det->pair_diff, ws, s));
+            if (timing) ASPIS_HIP(hipEventRecord(ev[1], s));
             if (timing) ASPIS_HIP(hipEventRecord(ev[2], s));
-            if (guess_mean)
-                ASPIS_HIP(aspis::launch_fused_mean(grads, row_of, f, r, d, ws, det->pair_diff, out, s));
-            else
-                ASPIS_HIP(aspis::launch_fused(grads, row_of, f, r, d, ws, det->pair_diff, out, s,
-                                              &fused_tile, full_keys));
+            aspis::TileUse half_tile{}, full_tile{};
+            auto gate = [&](int want) {
+                return aspis::PathGate{(may_mean && may_median) || two ? ws.n_sel + 1 : nullptr,
+                                       want};
+            };
+            if (may_median) {
+                if (two || !full_keys)
+                    ASPIS_HIP(aspis::launch_fused_if(grads, row_of, f, r, d, ws, det->pair_diff, out,
+                                                     s, &half_tile, false,
+                                                     gate(aspis::kPathHalfKeys)));
+                if (two || full_keys)
+                    ASPIS_HIP(aspis::launch_fused_if(grads, row_of, f, r, d, ws, det->pair_diff, out,
+                                                     s, &full_tile, true,
+                                                     gate(aspis::kPathFullKeys)));
+                if (!two) half_tile = full_tile = full_keys ? full_tile : half_tile;
+            }
+            if (may_mean)
+                ASPIS_HIP(aspis::launch_fused_mean_if(grads, row_of, f, r, d, ws, det->pair_diff, out,
+                                                      s, gate(aspis::kPathMean)));
             if (timing) ASPIS_HIP(hipEventRecord(ev[3], s));
+            ASPIS_HIP(aspis::launch_finish(det->pair_diff, subsets_dev, f, r, K, det->vote,
+                                           det->has_majority, det->disagree, ws, sel_out, s));
+            if ((st = staged_clique(res, aspis::kStageWords)) != ASPIS_OK) return st;
+            decide_keys(staged);
+            guess.success = (int32_t)(staged[aspis::kStageGuess] & 1u);
+            guess.honest[0] = staged[aspis::kStageGuess + 1];
+            guess_mean = (int)(staged[aspis::kStageGuess] >> 8) == aspis::kPathMean;
+            if (!guess_mean) fused_tile = full_keys ? full_tile : half_tile;
+            ran = true;
+        } else {
+            if (timing) ASPIS_HIP(hipEventRecord(ev[0], s));
+            ASPIS_HIP(aspis::launch_agree_file(grads, row_of, f, r, d, probe, det->pair_diff, s));
             ASPIS_HIP(aspis::launch_vote_rows(det->pair_diff, subsets_dev, f, r, K, det->vote,
                                               det->has_majority, det->disagree, ws.stage, s));
-            if ((st = staged_clique(res, 65)) != ASPIS_OK) return st;
+            if (tie_probe)
+                ASPIS_HIP(aspis::launch_tie_probe(grads, row_of, f, r, d, probe, tie_dev, s));
+            if (timing) ASPIS_HIP(hipEventRecord(ev[1], s));
+            if ((st = staged_clique(&guess, tie_probe ? aspis::kStageWords : 65)) != ASPIS_OK)
+                return st;
+            decide_keys(staged);
+            // the reduction the guess calls for: the median (Case 2, or MEDIAN
+            // mode) or the mean (Case 1 in PAPER mode, or MEAN mode)
+            guess_mean = use_mean(mode, &guess);
+            if (guess_mean ? aspis::fused_mean_supported(f, r) : aspis::fused_supported(f, r)) {
+                // the guessed selection; the same launch zeroes pair_diff for
+                // the main pass
+                ASPIS_HIP(aspis::launch_select(subsets_dev, det->vote, f, r, guess.success,
+                                               honest_mask(&guess), row_of, ws, nullptr,
+                                               det->pair_diff, f, s));
+                if (timing) ASPIS_HIP(hipEventRecord(ev[2], s));
+                if (guess_mean)
+                    ASPIS_HIP(aspis::launch_fused_mean(grads, row_of, f, r, d, ws, det->pair_diff,
+                                                       out, s));
+                else
+                    ASPIS_HIP(aspis::launch_fused(grads, row_of, f, r, d, ws, det->pair_diff, out, s,
+                                                  &fused_tile, full_keys));
+                if (timing) ASPIS_HIP(hipEventRecord(ev[3], s));
+                ASPIS_HIP(aspis::launch_finish(det->pair_diff, subsets_dev, f, r, K, det->vote,
+                                               det->has_majority, det->disagree, ws, sel_out, s));
+                if ((st = staged_clique(res, 65)) != ASPIS_OK) return st;
+                ran = true;
+            }
+        }
+        if (ran) {
+            local.fused = 1;
             const bool vote_changed = staged[64] != 0;
             // 3) the final selection.  The guess selected the same replica of
             //    every file iff both detections took the same case and
@@ -548,14 +591,14 @@ aspis_status detect_aggregate_impl(const float *grads, bool worker_major, int32_
             const bool final_mean = use_mean(mode, res);
             const bool repair = !hit && guess_mean == final_mean;
             if (timing) ASPIS_HIP(hipEventRecord(ev[4], s));
+            // a right guess left the final selection in the workspace and in
+            // sel_out; else the workspace describes the final selection from
+            // here on (the rows and positions a rerun of the reduction reads)
             if (repair) ASPIS_HIP(aspis::launch_save_sel(ws, f, s));
-            // the workspace describes the final selection from here on (the
-            // rows and positions a rerun of the reduction reads)
-            if (!hit || sel_out)
+            if (!hit) {
                 ASPIS_HIP(aspis::launch_select(subsets_dev, det->vote, f, r, res->success,
                                                honest_mask(res), row_of, ws, sel_out, nullptr, 0,
                                                s));
-            if (!hit) {
                 fused_tile = aspis::TileUse{};
                 if (repair) {
                     const int cols = aspis::reduce_tile_cols(grads, f, d, final_mean, full_keys);
@@ -578,7 +621,7 @@ aspis_status detect_aggregate_impl(const float *grads, bool worker_major, int32_
             local.tile_cols = fused_tile.cols;
             local.half_keys = fused_tile.half;
             if (timing) ASPIS_HIP(hipEventRecord(ev[5], s));
-            ASPIS_HIP(hipStreamSynchronize(s));
+            if (!hit || timing) ASPIS_HIP(hipStreamSynchronize(s));
             local.repair_groups = groups;
             if (timing) {
                 ASPIS_HIP(hipEventElapsedTime(&local.ms_probe, ev[0], ev[1]));
@@ -717,7 +760,7 @@ aspis_status aspis_plan(int32_t K, int32_t r, int64_t d, int32_t worker_major, u
     const bool full_keys = (flags & ASPIS_FLAG_FULL_KEYS) != 0;
     aspis::KernelPlan fused{}, med{};
     if (f <= aspis::kVoteRowsMaxFiles)
-        aspis::plan_fused(f, r, vec, worker_major != 0, &fused, full_keys);
+        aspis::plan_single_pass(f, r, d, worker_major != 0, &fused, full_keys);
     aspis::plan_median(f, vec, &med, full_keys);
     to_abi(fused, single_pass);
     to_abi(med, median);

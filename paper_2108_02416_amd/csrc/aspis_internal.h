@@ -36,6 +36,7 @@ struct Workspace {
 // Tile-group bits of the repair after a wrong guess: bit b covers tiles
 // [b << s, (b + 1) << s), s the least that fits every tile in these bits.
 constexpr int64_t kDirtyWords = 4096;
+constexpr int kStageGuess = 65;    // first stage word of the guess (guess_kernel)
 constexpr int kStageTie = 72;      // first stage word of the tie counts
 constexpr int kStageWords = 104;   // stage words the host reads back
 size_t workspace_bytes(int64_t f, int r);
@@ -142,12 +143,10 @@ struct KernelPlan {
     int32_t block = 0;            // threads per workgroup
     int64_t lds_bytes = 0;        // dynamic LDS per workgroup
 };
-// Median over up to f kept rows (always has a kernel); single pass for f
-// files of r replicas (false: none, the step then takes two passes).  vec:
-// d >= 4, a row holds a 16-byte chunk; ind: rows through a row table;
-// full_keys: tiles of 32-bit keys only (no half-key plan, no read-back).
+// Median over up to f kept rows (always has a kernel).  vec: d >= 4, a row
+// holds a 16-byte chunk; full_keys: tiles of 32-bit keys only (no half-key
+// plan, no read-back).
 bool plan_median(int64_t f, bool vec, KernelPlan *out, bool full_keys = false);
-bool plan_fused(int64_t f, int r, bool vec, bool ind, KernelPlan *out, bool full_keys = false);
 
 // Coordinate-wise lower median / fp64 mean of the kept rows.  With repair,
 // only the tiles of the groups ws.dirty marks (launch_dirty_tiles with the
@@ -178,6 +177,70 @@ bool fused_mean_supported(int64_t f, int r);
 // up on the first call per device (the calling thread's current device).
 constexpr size_t kScratchBytes = (size_t)2 << 20;
 hipError_t scratch_ptr(void **out);
+
+// ---- the single pass without a host step before its main kernel ----
+//
+// launch_probe, launch_guess, one main kernel per reduction the guess may call
+// for (each gated on the device's choice), launch_finish; one copy of the
+// stage words then tells the host whether the guess held.  The names below
+// are weak: a build of the host sources alone has no device code, and
+// fused_supported tells it so.
+#define ASPIS_DEVICE __attribute__((weak))
+
+// The reduction the guess calls for.
+constexpr int kPathHalfKeys = 0, kPathFullKeys = 1, kPathMean = 2;
+// aspis_reduce and the key choice, for the device
+constexpr int kModeMedian = 0, kModeMean = 1, kModePaper = 2;
+constexpr int kKeysHalf = 0, kKeysFull = 1, kKeysProbe = 2;
+
+// Full-key tiles when on average over the probed coordinates at least this
+// many files share the high 16-bit key half of the median.  The half-key
+// tiles read back the low half of every such file, so their extra time
+// follows the mean count: 28 files tied with the median (ALIE colluders
+// sending the honest mean, K = 15) cost the half-key single pass about as
+// much as the full-key tiles cost, and data tied on a fraction x of the
+// coordinates (455 files each there) costs about x times the fully tied
+// case.  The mean, unlike a typical coordinate's count, sees ties that
+// cover less than half of the coordinates.
+constexpr uint32_t kTieFullKeys = 16;
+
+// A main kernel's condition: it runs when *path is want (or without a path).
+struct PathGate {
+    const int32_t *path = nullptr;
+    int32_t want = 0;
+    __device__ bool closed() const { return path != nullptr && *path != want; }
+};
+
+// Single pass for f files of r replicas of d coordinates (false: none, the step
+// then takes two passes); ind: rows through a row table; full_keys as above.
+ASPIS_DEVICE bool plan_single_pass(int64_t f, int r, int64_t d, bool ind, KernelPlan *out,
+                        bool full_keys);
+// Agreement over the probe, each file's blocks over *split workgroups (the
+// words in ws.dirty), and n_tie (0: none) tie counts, in one launch.
+// f <= kDirtyWords.
+ASPIS_DEVICE hipError_t launch_probe(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
+                        const ProbeSet &probe, const Workspace &ws, int n_tie, int *split,
+                        hipStream_t s);
+// Votes, disagreement rows, clique search and selection of the probe into
+// vote, has_majority, disagree and the workspace; zeroes pair_diff; the
+// reduction to ws.n_sel[1] (kPath...).
+ASPIS_DEVICE hipError_t launch_guess(const int32_t *subsets, const int32_t *row_of, int64_t f, int r,
+                        int K, int q, int mode, int keys, int n_tie, int split, int8_t *vote,
+                        uint8_t *has_majority, uint64_t *disagree, uint32_t *pair_diff,
+                        const Workspace &ws, hipStream_t s);
+ASPIS_DEVICE hipError_t launch_fused_if(const float *g, const int32_t *row_of, int64_t f, int r,
+                        int64_t d, const Workspace &ws, uint32_t *pair_diff, float *out,
+                        hipStream_t s, TileUse *use, bool full_keys, PathGate gate);
+ASPIS_DEVICE hipError_t launch_fused_mean_if(const float *g, const int32_t *row_of, int64_t f, int r,
+                        int64_t d, const Workspace &ws, uint32_t *pair_diff, float *out,
+                        hipStream_t s, PathGate gate);
+// launch_vote_rows on the full agreement, and the guessed selection to
+// sel_out when it is not NULL.
+ASPIS_DEVICE hipError_t launch_finish(const uint32_t *pair_diff, const int32_t *subsets, int64_t f,
+                        int r, int K, int8_t *vote, uint8_t *has_majority, uint64_t *disagree,
+                        const Workspace &ws, int32_t *sel_out, hipStream_t s);
+// The row table of a worker-major upload (aspis_worker_rows).
+ASPIS_DEVICE hipError_t launch_worker_rows(int K, int r, int64_t f, int32_t *row_of, hipStream_t s);
 
 // Tie probe over the probed coordinates: for min(kTieCols, probe.coords())
 // coordinates spread over them, out[j] = the number of files whose value

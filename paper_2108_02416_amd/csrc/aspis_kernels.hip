@@ -116,67 +116,76 @@ agree_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
     }
 }
 
-// Agreement of one file per workgroup over coordinates [0,kend) (the
-// prefix probe of the single pass): the workgroup ORs its lanes' bits and
-// stores the file's word, so pair_diff needs no zero fill and no atomics.
+// Agreement of file i over blocks first, first + step, ... of the probe, by
+// one workgroup: returns the file's bits there to thread 0.
+template <int R>
+__device__ __forceinline__ uint32_t probe_agreement(const float *g, const int32_t *row_of, int64_t i,
+                                                    int64_t d, const ProbeSet &probe, int64_t first,
+                                                    int64_t step) {
+    static_assert(kProbeBlockCols == kBlock * 4, "one float4 per thread and probe block");
+    __shared__ uint32_t wave_bits[kBlock / 64];
+    constexpr int P = R * (R - 1) / 2;
+    const float *rows[R];
+#pragma unroll
+    for (int s = 0; s < R; ++s) rows[s] = g + replica_row(row_of, i, R, s) * d;
+    uint32_t diff = 0u;
+    for (int64_t j0 = first; j0 < probe.nb; j0 += kAgreeUnroll * step) {
+        uint32_t v[kAgreeUnroll][R][4];
+#pragma unroll
+        for (int u = 0; u < kAgreeUnroll; ++u) {
+            // block j0 + u*step: the thread's four coordinates (none past its end)
+            int64_t k = 0, kend = 0;
+            if (j0 + u * step < probe.nb) {
+                const int64_t b = probe.block_start(j0 + u * step);
+                k = b + (int64_t)threadIdx.x * 4;
+                kend = probe.block_end(b);
+            }
+#pragma unroll
+            for (int s = 0; s < R; ++s) {
+                if (k < kend)
+                    load4(rows[s], k, kend, v[u][s]);
+                else
+                    v[u][s][0] = v[u][s][1] = v[u][s][2] = v[u][s][3] = 0u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kAgreeUnroll; ++u) {
+            int p = 0;
+#pragma unroll
+            for (int s = 0; s < R; ++s)
+#pragma unroll
+                for (int t = s + 1; t < R; ++t) {
+                    const uint32_t x = (v[u][s][0] ^ v[u][t][0]) | (v[u][s][1] ^ v[u][t][1]) |
+                                       (v[u][s][2] ^ v[u][t][2]) | (v[u][s][3] ^ v[u][t][3]);
+                    diff |= (x != 0u ? 1u : 0u) << p;
+                    ++p;
+                }
+        }
+    }
+    uint32_t wdiff = 0u;
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (__ballot((diff >> p) & 1u)) wdiff |= 1u << p;
+    if ((threadIdx.x & 63) == 0) wave_bits[threadIdx.x >> 6] = wdiff;
+    __syncthreads();
+    uint32_t bits = 0u;
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) bits |= wave_bits[w];
+    }
+    __syncthreads();
+    return bits;
+}
+
+// Agreement over the probed coordinates, one file per workgroup: stores the
+// file's word, so pair_diff needs no zero fill and no atomics.
 template <int R>
 __global__ void __launch_bounds__(kBlock)
 agree_file_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
                   int64_t d, ProbeSet probe, uint32_t *__restrict__ pair_diff) {
-    static_assert(kProbeBlockCols == kBlock * 4, "one float4 per thread and probe block");
-    __shared__ uint32_t wave_bits[kBlock / 64];
-    constexpr int P = R * (R - 1) / 2;
     for (int64_t i = blockIdx.x; i < f; i += gridDim.x) {
-        const float *rows[R];
-#pragma unroll
-        for (int s = 0; s < R; ++s) rows[s] = g + replica_row(row_of, i, R, s) * d;
-        uint32_t diff = 0u;
-        for (int64_t j0 = 0; j0 < probe.nb; j0 += kAgreeUnroll) {
-            uint32_t v[kAgreeUnroll][R][4];
-#pragma unroll
-            for (int u = 0; u < kAgreeUnroll; ++u) {
-                // block j0+u: the thread's four coordinates (none past its end)
-                int64_t k = 0, kend = 0;
-                if (j0 + u < probe.nb) {
-                    const int64_t b = probe.block_start(j0 + u);
-                    k = b + (int64_t)threadIdx.x * 4;
-                    kend = probe.block_end(b);
-                }
-#pragma unroll
-                for (int s = 0; s < R; ++s) {
-                    if (k < kend)
-                        load4(rows[s], k, kend, v[u][s]);
-                    else
-                        v[u][s][0] = v[u][s][1] = v[u][s][2] = v[u][s][3] = 0u;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kAgreeUnroll; ++u) {
-                int p = 0;
-#pragma unroll
-                for (int s = 0; s < R; ++s)
-#pragma unroll
-                    for (int t = s + 1; t < R; ++t) {
-                        const uint32_t x = (v[u][s][0] ^ v[u][t][0]) | (v[u][s][1] ^ v[u][t][1]) |
-                                           (v[u][s][2] ^ v[u][t][2]) | (v[u][s][3] ^ v[u][t][3]);
-                        diff |= (x != 0u ? 1u : 0u) << p;
-                        ++p;
-                    }
-            }
-        }
-        uint32_t wdiff = 0u;
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-            if (__ballot((diff >> p) & 1u)) wdiff |= 1u << p;
-        if ((threadIdx.x & 63) == 0) wave_bits[threadIdx.x >> 6] = wdiff;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t b = 0u;
-#pragma unroll
-            for (int w = 0; w < kBlock / 64; ++w) b |= wave_bits[w];
-            pair_diff[i] = b;
-        }
-        __syncthreads();
+        const uint32_t b = probe_agreement<R>(g, row_of, i, d, probe, 0, 1);
+        if (threadIdx.x == 0) pair_diff[i] = b;
     }
 }
 
@@ -186,15 +195,18 @@ agree_file_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_o
 // Eq. (3) for one file from its pair-difference word: the lowest slot of the
 // largest class of bitwise-equal replicas and that class's size.  Calls
 // differ(s, t) for every slot pair whose replicas differ.
-template <typename DiffFn>
-__device__ __forceinline__ void file_vote(uint32_t pd, int r, int *vote_slot, int *class_size,
+template <int R, typename DiffFn>
+__device__ __forceinline__ void file_vote(uint32_t pd, int *vote_slot, int *class_size,
                                           DiffFn differ) {
     // same[s] = bitmask of slots whose replica equals slot s's
-    uint32_t same[8];
-    for (int s = 0; s < r; ++s) same[s] = 1u << s;
+    uint32_t same[R];
+#pragma unroll
+    for (int s = 0; s < R; ++s) same[s] = 1u << s;
     int p = 0;
-    for (int s = 0; s < r; ++s)
-        for (int t = s + 1; t < r; ++t, ++p) {
+#pragma unroll
+    for (int s = 0; s < R; ++s)
+#pragma unroll
+        for (int t = s + 1; t < R; ++t, ++p) {
             if (pd >> p & 1u) {
                 differ(s, t);
             } else {
@@ -203,7 +215,8 @@ __device__ __forceinline__ void file_vote(uint32_t pd, int r, int *vote_slot, in
             }
         }
     int best = 0, best_n = 0;
-    for (int s = 0; s < r; ++s) {
+#pragma unroll
+    for (int s = 0; s < R; ++s) {
         const int c = __popc(same[s]);
         if (c > best_n) {
             best_n = c;
@@ -214,33 +227,38 @@ __device__ __forceinline__ void file_vote(uint32_t pd, int r, int *vote_slot, in
     *class_size = best_n;
 }
 
+template <int R>
 __global__ void vote_kernel(const uint32_t *__restrict__ pair_diff,
                             const int32_t *__restrict__ subsets, int64_t f,
-                            int r, int8_t *__restrict__ vote,
+                            int8_t *__restrict__ vote,
                             uint8_t *__restrict__ has_majority,
                             uint64_t *__restrict__ disagree) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < f;
          i += (int64_t)gridDim.x * blockDim.x) {
         int best = 0, best_n = 0;
-        file_vote(pair_diff[i], r, &best, &best_n, [&](int s, int t) {
-            const int us = subsets[i * r + s], ut = subsets[i * r + t];
+        file_vote<R>(pair_diff[i], &best, &best_n, [&](int s, int t) {
+            const int us = subsets[i * R + s], ut = subsets[i * R + t];
             atomicOr((unsigned long long *)&disagree[us], 1ull << ut);
             atomicOr((unsigned long long *)&disagree[ut], 1ull << us);
         });
         vote[i] = (int8_t)best;
-        has_majority[i] = (uint8_t)(best_n >= (r + 1) / 2);
+        has_majority[i] = (uint8_t)(best_n >= (R + 1) / 2);
     }
 }
 
 // The same in one workgroup, for the single pass (f is at most a few
 // thousand there): the K rows are built in LDS and stored whole (no zero
 // fill), and a copy goes to stage[0..K) for the host, with stage[64] = 1 if
-// any file's vote differs from the one vote[] held before the call.
+// any file's vote differs from the one vote[] held before the call.  sel_out,
+// when not NULL, receives a copy of sel (the guessed selection, which the
+// host finds to be the final one in nearly every step).
+template <int R>
 __global__ void __launch_bounds__(1024)
 vote_rows_kernel(const uint32_t *__restrict__ pair_diff, const int32_t *__restrict__ subsets,
-                 int64_t f, int r, int K, int8_t *__restrict__ vote,
+                 int64_t f, int K, int8_t *__restrict__ vote,
                  uint8_t *__restrict__ has_majority, uint64_t *__restrict__ disagree,
-                 uint64_t *__restrict__ stage) {
+                 uint64_t *__restrict__ stage, const int32_t *__restrict__ sel,
+                 int32_t *__restrict__ sel_out) {
     __shared__ unsigned long long rows[64];
     __shared__ int changed;
     const int tid = threadIdx.x;
@@ -249,14 +267,15 @@ vote_rows_kernel(const uint32_t *__restrict__ pair_diff, const int32_t *__restri
     __syncthreads();
     for (int64_t i = tid; i < f; i += blockDim.x) {
         int best = 0, best_n = 0;
-        file_vote(pair_diff[i], r, &best, &best_n, [&](int s, int t) {
-            const int us = subsets[i * r + s], ut = subsets[i * r + t];
+        file_vote<R>(pair_diff[i], &best, &best_n, [&](int s, int t) {
+            const int us = subsets[i * R + s], ut = subsets[i * R + t];
             atomicOr(&rows[us], 1ull << ut);
             atomicOr(&rows[ut], 1ull << us);
         });
+        if (sel_out) sel_out[i] = sel[i];
         if (vote[i] != (int8_t)best) changed = 1;
         vote[i] = (int8_t)best;
-        has_majority[i] = (uint8_t)(best_n >= (r + 1) / 2);
+        has_majority[i] = (uint8_t)(best_n >= (R + 1) / 2);
     }
     __syncthreads();
     if (tid < K) {
@@ -269,18 +288,13 @@ vote_rows_kernel(const uint32_t *__restrict__ pair_diff, const int32_t *__restri
 // ---------------------------------------------------------------------------
 // selection (one workgroup of 1024 threads; f is at most a few thousand)
 
-__global__ void __launch_bounds__(1024)
-select_kernel(const int32_t *__restrict__ subsets,
-              const int8_t *__restrict__ vote, int64_t f, int r,
-              int success, uint64_t honest, const int32_t *__restrict__ row_of,
-              int32_t *__restrict__ sel, int32_t *__restrict__ pos, int32_t *__restrict__ rows,
-              int32_t *__restrict__ n_sel, int32_t *__restrict__ sel_out,
-              uint32_t *__restrict__ zero, int64_t n_zero) {
+__device__ __forceinline__ void select_files(const int32_t *subsets, const int8_t *vote, int64_t f,
+                                             int r, int success, uint64_t honest,
+                                             const int32_t *row_of, int32_t *sel, int32_t *pos,
+                                             int32_t *rows, int32_t *n_sel, int32_t *sel_out) {
     __shared__ int wave_tot[16];
     __shared__ int carry;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (zero)
-        for (int64_t i = tid; i < n_zero; i += 1024) zero[i] = 0u;
     if (tid == 0) carry = 0;
     __syncthreads();
     for (int64_t b = 0; b < f; b += 1024) {
@@ -320,6 +334,196 @@ select_kernel(const int32_t *__restrict__ subsets,
         __syncthreads();
     }
     if (tid == 0) *n_sel = carry;
+}
+
+__global__ void __launch_bounds__(1024)
+select_kernel(const int32_t *__restrict__ subsets,
+              const int8_t *__restrict__ vote, int64_t f, int r,
+              int success, uint64_t honest, const int32_t *__restrict__ row_of,
+              int32_t *__restrict__ sel, int32_t *__restrict__ pos, int32_t *__restrict__ rows,
+              int32_t *__restrict__ n_sel, int32_t *__restrict__ sel_out,
+              uint32_t *__restrict__ zero, int64_t n_zero) {
+    if (zero)
+        for (int64_t i = threadIdx.x; i < n_zero; i += 1024) zero[i] = 0u;
+    select_files(subsets, vote, f, r, success, honest, row_of, sel, pos, rows, n_sel, sel_out);
+}
+
+// ---------------------------------------------------------------------------
+// the guess of the single pass, on the device: the host's clique search
+// would cost the step a copy, a synchronisation and a launch before its main
+// kernel can start
+
+// Whether the detection graph has exactly one maximum clique and it holds at
+// least `need` workers, as the host's aspis_clique decides it; by one wave,
+// which all run in step.  nbr (LDS): neighbour masks, lane u's in nbr[u], 0
+// from K on.  Bron-Kerbosch with Tomita's pivot, bounded below by need and
+// the largest clique found (branches that cannot reach it are cut); at most
+// kGuessSteps branches, then it gives up and answers no (a wrong guess costs
+// time, never the result).
+constexpr int kGuessSteps = 1024;
+struct GuessStack {
+    uint64_t P[65], X[65], R[65], todo[65];
+};
+__device__ __forceinline__ bool guess_clique(const unsigned long long *nbr, int K, int need,
+                                             volatile GuessStack *st, uint64_t *honest) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t mine = nbr[lane];
+    int best = need, count = 0, depth = 0;
+    uint64_t found = 0ull;
+    // the candidates not adjacent to the pivot, the vertex of P or X adjacent
+    // to most of P
+    auto branch = [&](uint64_t P, uint64_t X) {
+        const bool in = ((P | X) >> lane) & 1ull;
+        const uint32_t deg = in ? (uint32_t)__popcll(P & mine) + 1u : 0u;
+        const uint32_t top = group_reduce<64, Op::Max>(deg);
+        const int pivot = __ffsll((unsigned long long)__ballot(in && deg == top)) - 1;
+        return P & ~nbr[pivot];
+    };
+    const uint64_t all = K == 64 ? ~0ull : (1ull << K) - 1ull;
+    st->P[0] = all;
+    st->X[0] = 0ull;
+    st->R[0] = 0ull;
+    st->todo[0] = branch(all, 0ull);
+    for (int step = 0; depth >= 0; ++step) {
+        if (step >= kGuessSteps) return false;
+        const uint64_t todo = st->todo[depth];
+        if (todo == 0ull) {
+            --depth;
+            continue;
+        }
+        const int v = __ffsll((unsigned long long)todo) - 1;
+        const uint64_t bit = 1ull << v, nv = nbr[v];
+        const uint64_t P = st->P[depth], X = st->X[depth];
+        const uint64_t P2 = P & nv, X2 = X & nv, R2 = st->R[depth] | bit;
+        st->todo[depth] = todo & ~bit;
+        st->P[depth] = P & ~bit;
+        st->X[depth] = X | bit;
+        const int size = __popcll(R2);
+        if (P2 == 0ull) {
+            if (X2 == 0ull && size >= best) {
+                if (size > best) count = 0;
+                best = size;
+                if (count++ == 0) found = R2;
+            }
+        } else if (size + __popcll(P2) >= best) {
+            ++depth;
+            st->P[depth] = P2;
+            st->X[depth] = X2;
+            st->R[depth] = R2;
+            st->todo[depth] = branch(P2, X2);
+        }
+    }
+    *honest = found;
+    return count == 1;
+}
+
+// The probe's outcome in one workgroup: votes and disagreement rows from the
+// files' partial words (split: how many a file has, file i's at part[s*f +
+// i]), the clique search, the guessed selection into the workspace, the
+// reduction the guess calls for (path_out, GuessPath), and pair_diff zeroed
+// for the main pass.  stage: as vote_rows_kernel's, without the flag;
+// stage[kStageGuess] = success | path << 8, stage[kStageGuess + 1] = the
+// honest mask.
+template <int R>
+__global__ void __launch_bounds__(1024)
+guess_kernel(const uint32_t *__restrict__ part, int split, const int32_t *__restrict__ subsets,
+             int64_t f, int K, int need, int mode, int keys,
+             const uint32_t *__restrict__ tie_counts, int n_tie,
+             const int32_t *__restrict__ row_of, int8_t *__restrict__ vote,
+             uint8_t *__restrict__ has_majority, uint64_t *__restrict__ disagree,
+             uint64_t *__restrict__ stage, uint32_t *__restrict__ pair_diff,
+             int32_t *__restrict__ sel, int32_t *__restrict__ pos, int32_t *__restrict__ rows,
+             int32_t *__restrict__ n_sel, int32_t *__restrict__ path_out) {
+    __shared__ unsigned long long nbr[64];
+    __shared__ GuessStack stack;
+    __shared__ int success;
+    __shared__ uint64_t honest;
+    const int tid = threadIdx.x;
+    if (tid < 64) nbr[tid] = 0ull;   // disagreement rows, then neighbours
+    __syncthreads();
+    for (int64_t i = tid; i < f; i += 1024) {
+        uint32_t pd = 0u;
+        for (int s = 0; s < split; ++s) pd |= part[(int64_t)s * f + i];
+        int best = 0, best_n = 0;
+        file_vote<R>(pd, &best, &best_n, [&](int s, int t) {
+            const int us = subsets[i * R + s], ut = subsets[i * R + t];
+            atomicOr(&nbr[us], 1ull << ut);
+            atomicOr(&nbr[ut], 1ull << us);
+        });
+        vote[i] = (int8_t)best;
+        has_majority[i] = (uint8_t)(best_n >= (R + 1) / 2);
+        pair_diff[i] = 0u;
+    }
+    __syncthreads();
+    if (tid < 64) {
+        const uint64_t all = K == 64 ? ~0ull : (1ull << K) - 1ull;
+        const uint64_t dis = nbr[tid];
+        if (tid < K) {
+            disagree[tid] = dis;
+            stage[tid] = dis;
+        }
+        nbr[tid] = tid < K ? all & ~dis & ~(1ull << tid) : 0ull;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        uint64_t h = 0ull;
+        const bool ok = guess_clique(nbr, K, need, &stack, &h);
+        // the tie estimate: the mean count, rounded up
+        uint32_t full = keys == kKeysFull ? 1u : 0u;
+        if (keys == kKeysProbe) {
+            const uint32_t sum = group_reduce<64, Op::Add>(tid < n_tie ? tie_counts[tid] : 0u);
+            full = (sum + (uint32_t)n_tie - 1u) / (uint32_t)n_tie >= kTieFullKeys ? 1u : 0u;
+        }
+        const bool mean = mode == kModeMean || (mode == kModePaper && ok);
+        const int path = mean ? kPathMean : full ? kPathFullKeys : kPathHalfKeys;
+        if (tid == 0) {
+            success = ok ? 1 : 0;
+            honest = h;
+            *path_out = path;
+            stage[kStageGuess] = (uint64_t)(ok ? 1 : 0) | (uint64_t)path << 8;
+            stage[kStageGuess + 1] = h;
+        }
+    }
+    __syncthreads();
+    select_files(subsets, vote, f, R, success, honest, row_of, sel, pos, rows, n_sel, nullptr);
+}
+
+// Row of every replica in a worker-major upload: replica (i,s) is row u*l + k
+// of worker u = slot s's worker, i the k-th file of u.  The files holding u,
+// u taken out, are the (r-1)-subsets of the K-1 others in lexicographic
+// order, so k is the rank of file i's other workers among those.
+__global__ void __launch_bounds__(kBlock)
+worker_rows_kernel(int K, int r, int64_t f, int32_t *__restrict__ row_of) {
+    __shared__ uint32_t binom[64][8];   // C(n, k); C(63, 7) fits 32 bits
+    for (int e = threadIdx.x; e < 64 * 8; e += kBlock) {
+        const int n = e / 8, k = e % 8;
+        uint64_t v = k <= n ? 1u : 0u;
+        for (int j = 0; j < k && k <= n; ++j) v = v * (uint64_t)(n - j) / (uint64_t)(j + 1);
+        binom[n][k] = (uint32_t)v;
+    }
+    __syncthreads();
+    const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
+    if (i >= f) return;
+    // file i's workers: the subset of rank i
+    int c[8];
+    int64_t rest = i;
+    int u = 0;
+    for (int s = 0; s < r; ++s, ++u) {
+        // subsets whose next worker is u
+        for (; rest >= (int64_t)binom[K - 1 - u][r - 1 - s]; ++u) rest -= binom[K - 1 - u][r - 1 - s];
+        c[s] = u;
+    }
+    const int64_t l = binom[K - 1][r - 1];
+    for (int s = 0; s < r; ++s) {
+        int64_t k = 0;
+        int next = 0;   // the least label the next worker may have
+        for (int t = 0, m = 0; t < r; ++t) {
+            if (t == s) continue;
+            const int w = c[t] - (t > s ? 1 : 0);   // label without worker c[s]
+            for (int x = next; x < w; ++x) k += binom[K - 2 - x][r - 2 - m];
+            next = w + 1;
+            ++m;
+        }
+        row_of[i * r + s] = (int32_t)(c[s] * l + k);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -383,7 +587,8 @@ __global__ void __launch_bounds__(tile_block<T>())
 fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f, int64_t d,
              const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
              const int32_t *__restrict__ n_sel, int64_t ntiles,
-             uint32_t *__restrict__ pair_diff, float *__restrict__ out) {
+             uint32_t *__restrict__ pair_diff, float *__restrict__ out, PathGate gate) {
+    if (gate.closed()) return;
     extern __shared__ __align__(16) uint32_t smem[];
     constexpr int BLOCK = tile_block<T>();
     constexpr int G = BLOCK / T;
@@ -470,7 +675,8 @@ __global__ void __launch_bounds__(kBlock)
 fused_mean_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
                   int64_t d, const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
                   const int32_t *__restrict__ n_sel, uint32_t *__restrict__ pair_diff,
-                  float *__restrict__ out) {
+                  float *__restrict__ out, PathGate gate) {
+    if (gate.closed()) return;
     extern __shared__ uint32_t pdw[];   // [f]
     const int tid = threadIdx.x;
     for (int64_t i = tid; i < f; i += kBlock) pdw[i] = 0u;
@@ -697,15 +903,14 @@ constexpr int kTieMaxFiles = 4096;   // files looked at per coordinate (the firs
 static_assert(kTieThreads == 256, "one histogram bucket per thread");
 
 template <int R>
-__global__ void __launch_bounds__(kTieThreads)
-tie_probe_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
-                 int64_t d, ProbeSet probe, uint32_t *__restrict__ out) {
+__device__ __forceinline__ void tie_count(const float *g, const int32_t *row_of, int64_t f, int64_t d,
+                                          const ProbeSet &probe, int coord, uint32_t *out) {
     __shared__ uint16_t h[kTieMaxFiles];
     __shared__ uint32_t hist[256];
     __shared__ uint32_t wsum[kTieThreads / 64];
     __shared__ uint32_t pick[2];   // bucket, rank within it
     const int tid = threadIdx.x;
-    const int64_t k = tie_coord(probe, blockIdx.x);
+    const int64_t k = tie_coord(probe, coord);
     const int n = (int)(f < kTieMaxFiles ? f : kTieMaxFiles);
     for (int i = tid; i < n; i += kTieThreads) {
         uint32_t v[R];
@@ -764,9 +969,35 @@ tie_probe_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of
             hi = b;
             rank = pick[1];
         } else if (tid == 0) {
-            out[blockIdx.x] = hist[b];
+            out[coord] = hist[b];
         }
         __syncthreads();
+    }
+}
+
+template <int R>
+__global__ void __launch_bounds__(kTieThreads)
+tie_probe_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
+                 int64_t d, ProbeSet probe, uint32_t *__restrict__ out) {
+    tie_count<R>(g, row_of, f, d, probe, (int)blockIdx.x, out);
+}
+
+// The whole probe in one launch: workgroups [0, f*split) compare file b % f
+// over every split-th block of the probe (from block b / f on) into part[b],
+// the rest run the tie probe.  A file alone leaves a small cluster's probe to
+// a few workgroups: K = 7, d = 0.1M, 29 us
+// without the split, 18 us with it and the guess (guess_kernel).
+template <int R>
+__global__ void __launch_bounds__(kBlock)
+probe_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f, int split,
+             int64_t d, ProbeSet probe, uint32_t *__restrict__ part, uint32_t *__restrict__ tie_out) {
+    static_assert(kTieThreads == kBlock, "one workgroup size");
+    const int64_t b = blockIdx.x, n = f * split;
+    if (b < n) {
+        const uint32_t bits = probe_agreement<R>(g, row_of, b % f, d, probe, b / f, split);
+        if (threadIdx.x == 0) part[b] = bits;
+    } else {
+        tie_count<R>(g, row_of, f, d, probe, (int)(b - n), tie_out);
     }
 }
 
@@ -1007,18 +1238,43 @@ hipError_t launch_agree(const float *g, const int32_t *row_of, int64_t f, int r,
 hipError_t launch_vote(const uint32_t *pair_diff, const int32_t *subsets, int64_t f,
                        int r, int8_t *vote, uint8_t *has_majority, uint64_t *disagree,
                        hipStream_t s) {
-    vote_kernel<<<(unsigned)grid_for((f + 255) / 256, 64), 256, 0, s>>>(
-        pair_diff, subsets, f, r, vote, has_majority, disagree);
+    const unsigned grid = (unsigned)grid_for((f + 255) / 256, 64);
+#define ASPIS_VOTE(RR) \
+    vote_kernel<RR><<<grid, 256, 0, s>>>(pair_diff, subsets, f, vote, has_majority, disagree);
+    switch (r) {
+    case 3: ASPIS_VOTE(3) break;
+    case 5: ASPIS_VOTE(5) break;
+    case 7: ASPIS_VOTE(7) break;
+    default: return hipErrorInvalidValue;
+    }
+#undef ASPIS_VOTE
     return hipGetLastError();
 }
+
+namespace {
+hipError_t vote_rows(const uint32_t *pair_diff, const int32_t *subsets, int64_t f, int r, int K,
+                     int8_t *vote, uint8_t *has_majority, uint64_t *disagree, uint64_t *stage,
+                     const int32_t *sel, int32_t *sel_out, hipStream_t s) {
+#define ASPIS_VOTE(RR)                                                                           \
+    vote_rows_kernel<RR><<<1, 1024, 0, s>>>(pair_diff, subsets, f, K, vote, has_majority, disagree, \
+                                            stage, sel, sel_out);
+    switch (r) {
+    case 3: ASPIS_VOTE(3) break;
+    case 5: ASPIS_VOTE(5) break;
+    case 7: ASPIS_VOTE(7) break;
+    default: return hipErrorInvalidValue;
+    }
+#undef ASPIS_VOTE
+    return hipGetLastError();
+}
+}  // namespace
 
 hipError_t launch_vote_rows(const uint32_t *pair_diff, const int32_t *subsets, int64_t f,
                             int r, int K, int8_t *vote, uint8_t *has_majority,
                             uint64_t *disagree, uint64_t *stage, hipStream_t s) {
     if (f > kVoteRowsMaxFiles || K < 1 || K > 64) return hipErrorInvalidValue;
-    vote_rows_kernel<<<1, 1024, 0, s>>>(pair_diff, subsets, f, r, K, vote, has_majority,
-                                        disagree, stage);
-    return hipGetLastError();
+    return vote_rows(pair_diff, subsets, f, r, K, vote, has_majority, disagree, stage, nullptr,
+                     nullptr, s);
 }
 
 // Every probed coordinate inside [0, d), the blocks within their count.
@@ -1058,6 +1314,13 @@ hipError_t launch_select(const int32_t *subsets, const int8_t *vote, int64_t f, 
 namespace {
 
 constexpr int64_t kHalfMinRows = 128;
+// The single pass at r = 3 takes half-key tiles of 128 columns from 24 files
+// on where the vector gives every CU one (256 CUs): their selection costs a
+// quarter of the full keys' a column, K = 7 (35 files) d = 1M 133 against
+// 203 us, d = 0.1M 26 against 32 us, K = 10 (120 files) d = 1M 237 against 336 us;
+// shorter vectors spread over more CUs in tiles of 64 columns (K = 7, d =
+// 7,850: 13.1 against 10.6 us).
+constexpr int64_t kHalfFewRows = 24, kHalfFewCols = 128 * 256;
 constexpr int64_t kHalfMaxRows = 60000;   // row numbers (with padding) fit 16 bits
 
 // Most sweeps a half-key plan may take: 32, and 36 for the 32-column tile
@@ -1077,7 +1340,7 @@ int round_sweeps(int64_t sw, bool half, int T, int fill) {
         if (fill == kWsFillWide) return 24;
         if (T == 128 && (sw == 29 || sw == 30)) return 30;
         if (T == 16 && sw > 16 && sw <= 24) return 24;
-        return sw <= 8 ? 8 : (int)((sw + 3) / 4 * 4);
+        return (int)((sw + 3) / 4 * 4);
     }
     return sw <= 2 ? 2 : sw <= 4 ? 4 : sw <= 8 ? 8 : sw <= 12 ? 12 : 16;
 }
@@ -1097,9 +1360,10 @@ int round_sweeps(int64_t sw, bool half, int T, int fill) {
 // 12 sweeps 0.58 ms, 128 of 24 0.66 ms; 792 files, d = 0.2M, 32 of 16 0.71,
 // 64 of 28 0.88 ms; 1,716 files, d = 0.1M, 32 of 28 0.87, 16 of 16 0.91 ms.
 template <typename LdsFn>
-WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r = 3) {
+WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r = 3,
+                 int64_t min_rows = kHalfMinRows) {
     WsPlan p;
-    if (f < kHalfMinRows || f > kHalfMaxRows) return p;
+    if (f < min_rows || f > kHalfMaxRows) return p;
     for (int T : {128, 64, 32, 16}) {
         if (T <= narrower) break;
         for (int fill : {kWsFill, kWsFillWide}) {
@@ -1162,9 +1426,9 @@ int64_t ws_lds_bytes(int64_t f, int r, int T, int sweeps, bool table_in_lds, boo
 // Warp-specialised single pass (rows of four coordinates or more): plans as for the
 // median above (the wide split without a row table in LDS).  r = 5 and 7: the
 // even split.
-WsPlan ws_plan(int64_t f, int r, bool vec, bool ind, bool full_keys = false) {
+WsPlan ws_plan(int64_t f, int r, int64_t d, bool ind, bool full_keys = false) {
     WsPlan p;
-    if (!vec) return p;
+    if (d < 4) return p;
     p.r = r;
     if (r != 3) {
         // full keys: 64 columns and up to four sweeps (128 files), what the
@@ -1193,7 +1457,7 @@ WsPlan ws_plan(int64_t f, int r, bool vec, bool ind, bool full_keys = false) {
     if (full_keys) return p;
     const WsPlan h = half_plan(f, p.T, ind, false, [&](int T, int sweeps, int fill) {
         return ws_lds_bytes(f, r, T, sweeps, ind, true, fill);
-    });
+    }, 3, d > kHalfFewCols ? kHalfFewRows : kHalfMinRows);
     WsPlan best = h.T != 0 ? h : p;
     if (ind) {
         // a 32-column tile when the row table, read from global memory (where
@@ -1257,9 +1521,9 @@ bool plan_median(int64_t f, bool vec, KernelPlan *out, bool full_keys) {
     return true;
 }
 
-bool plan_fused(int64_t f, int r, bool vec, bool ind, KernelPlan *out, bool full_keys) {
+bool plan_single_pass(int64_t f, int r, int64_t d, bool ind, KernelPlan *out, bool full_keys) {
     *out = KernelPlan{};
-    const WsPlan p = ws_plan(f, r, vec, ind, full_keys);
+    const WsPlan p = ws_plan(f, r, d, ind, full_keys);
     if (p.T != 0) {
         const int table = ind ? (p.rtg ? 2 : 1) : 0;
         *out = ws_kernel_plan(fused_ws_fn(p, ind) ? kKernelFusedWs : kKernelUnbuilt, p,
@@ -1279,7 +1543,7 @@ bool plan_fused(int64_t f, int r, bool vec, bool ind, KernelPlan *out, bool full
 
 bool fused_supported(int64_t f, int r) {
     KernelPlan k;
-    return plan_fused(f, r, true, false, &k) || plan_fused(f, r, false, false, &k);
+    return plan_single_pass(f, r, 4, false, &k, false) || plan_single_pass(f, r, 1, false, &k, false);
 }
 
 hipError_t launch_median(const float *g, int64_t d, const Workspace &ws, int64_t f,
@@ -1360,27 +1624,32 @@ hipError_t launch_dirty_tiles(const float *g, const int32_t *row_of, int64_t f, 
 hipError_t launch_fused(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
                         const Workspace &ws, uint32_t *pair_diff, float *out, hipStream_t s,
                         TileUse *use, bool full_keys) {
+    return launch_fused_if(g, row_of, f, r, d, ws, pair_diff, out, s, use, full_keys, PathGate{});
+}
+
+hipError_t launch_fused_if(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
+                           const Workspace &ws, uint32_t *pair_diff, float *out, hipStream_t s,
+                           TileUse *use, bool full_keys, PathGate gate) {
     const bool ind = row_of != nullptr;
-    const bool vec = d >= 4;
     KernelPlan k;
-    if (!plan_fused(f, r, vec, ind, &k, full_keys)) return hipErrorInvalidValue;
+    if (!plan_single_pass(f, r, d, ind, &k, full_keys)) return hipErrorInvalidValue;
     if (use) *use = TileUse{k.tile_cols, k.half_keys};
     const int T = k.tile_cols;
     const int64_t ntiles = (d + T - 1) / T;
     const size_t lds = (size_t)k.lds_bytes;
     if (k.kind == kKernelFusedWs) {
         const unsigned grid = (unsigned)grid_for(ntiles, (int64_t)num_cus());
-        WsPlan p = ws_plan(f, r, vec, ind, full_keys);
+        WsPlan p = ws_plan(f, r, d, ind, full_keys);
         p.lines = whole_lines(g, d, T);
         const FusedWsFn fn = fused_ws_fn(p, ind);
         fn<<<grid, kWsThreads, lds, s>>>(g, ind ? row_of : nullptr, f, d, ws.sel, ws.pos, ws.n_sel,
-                                         ntiles, pair_diff, out);
+                                         ntiles, pair_diff, out, gate);
         return hipGetLastError();
     }
     const unsigned grid = (unsigned)tile_grid(ntiles, lds);
 #define ASPIS_FUSED(TT, RR)                               \
     fused_kernel<TT, RR><<<grid, tile_block<TT>(), lds, s>>>( \
-        g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, ntiles, pair_diff, out);
+        g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, ntiles, pair_diff, out, gate);
 #define ASPIS_FUSED_R(TT)                     \
     switch (r) {                              \
     case 3: ASPIS_FUSED(TT, 3) break;         \
@@ -1408,6 +1677,12 @@ bool fused_mean_supported(int64_t f, int r) {
 hipError_t launch_fused_mean(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
                              const Workspace &ws, uint32_t *pair_diff, float *out,
                              hipStream_t s) {
+    return launch_fused_mean_if(g, row_of, f, r, d, ws, pair_diff, out, s, PathGate{});
+}
+
+hipError_t launch_fused_mean_if(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
+                                const Workspace &ws, uint32_t *pair_diff, float *out, hipStream_t s,
+                                PathGate gate) {
     if (!fused_mean_supported(f, r)) return hipErrorInvalidValue;
     const int64_t nq = (d + 3) / 4;
     // up to 8 workgroups per CU: each wave's loads follow one another file
@@ -1417,7 +1692,7 @@ hipError_t launch_fused_mean(const float *g, const int32_t *row_of, int64_t f, i
     const size_t lds = (size_t)f * 4;
 #define ASPIS_FMEAN(RR)                                                                      \
     fused_mean_kernel<RR><<<grid, kBlock, lds, s>>>(g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, \
-                                                    pair_diff, out);
+                                                    pair_diff, out, gate);
     switch (r) {
     case 3: ASPIS_FMEAN(3) break;
     case 5: ASPIS_FMEAN(5) break;
@@ -1486,6 +1761,67 @@ hipError_t launch_tie_probe(const float *g, const int32_t *row_of, int64_t f, in
     case 7: tie_probe_kernel<7><<<grid, kTieThreads, 0, s>>>(g, row_of, f, d, probe, out); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_probe(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
+                        const ProbeSet &probe, const Workspace &ws, int n_tie, int *split,
+                        hipStream_t s) {
+    // the partial words share the workspace of the repair's tile-group bits,
+    // which are written after them
+    if (f <= 0 || f > kDirtyWords || !probe_valid(probe, d) || n_tie < 0 || n_tie > kTieCols ||
+        n_tie > probe.coords())
+        return hipErrorInvalidValue;
+    int64_t most = kDirtyWords / f;
+    const int64_t bursts = (probe.nb + kAgreeUnroll - 1) / kAgreeUnroll;
+    if (most > bursts) most = bursts;
+    *split = (int)(most > 8 ? 8 : most);
+    const unsigned grid = (unsigned)(f * *split + n_tie);
+    uint32_t *tie_out = reinterpret_cast<uint32_t *>(ws.stage + kStageTie);
+#define ASPIS_PROBE(RR) \
+    probe_kernel<RR><<<grid, kBlock, 0, s>>>(g, row_of, f, *split, d, probe, ws.dirty, tie_out);
+    switch (r) {
+    case 3: ASPIS_PROBE(3) break;
+    case 5: ASPIS_PROBE(5) break;
+    case 7: ASPIS_PROBE(7) break;
+    default: return hipErrorInvalidValue;
+    }
+#undef ASPIS_PROBE
+    return hipGetLastError();
+}
+
+hipError_t launch_guess(const int32_t *subsets, const int32_t *row_of, int64_t f, int r, int K, int q,
+                        int mode, int keys, int n_tie, int split, int8_t *vote,
+                        uint8_t *has_majority, uint64_t *disagree, uint32_t *pair_diff,
+                        const Workspace &ws, hipStream_t s) {
+    if (f <= 0 || f > kDirtyWords || K < 1 || K > 64 || (keys == kKeysProbe && n_tie < 1))
+        return hipErrorInvalidValue;
+    const uint32_t *ties = reinterpret_cast<const uint32_t *>(ws.stage + kStageTie);
+#define ASPIS_GUESS(RR)                                                                          \
+    guess_kernel<RR><<<1, 1024, 0, s>>>(ws.dirty, split, subsets, f, K, K - q, mode, keys, ties,  \
+                                        n_tie, row_of, vote, has_majority, disagree, ws.stage,   \
+                                        pair_diff, ws.sel, ws.pos, ws.rows, ws.n_sel, ws.n_sel + 1);
+    switch (r) {
+    case 3: ASPIS_GUESS(3) break;
+    case 5: ASPIS_GUESS(5) break;
+    case 7: ASPIS_GUESS(7) break;
+    default: return hipErrorInvalidValue;
+    }
+#undef ASPIS_GUESS
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const uint32_t *pair_diff, const int32_t *subsets, int64_t f, int r, int K,
+                         int8_t *vote, uint8_t *has_majority, uint64_t *disagree,
+                         const Workspace &ws, int32_t *sel_out, hipStream_t s) {
+    if (f > kVoteRowsMaxFiles || K < 1 || K > 64) return hipErrorInvalidValue;
+    return vote_rows(pair_diff, subsets, f, r, K, vote, has_majority, disagree, ws.stage, ws.sel,
+                     sel_out, s);
+}
+
+hipError_t launch_worker_rows(int K, int r, int64_t f, int32_t *row_of, hipStream_t s) {
+    if (K < 2 || K > 64 || r < 2 || r > 7 || f <= 0) return hipErrorInvalidValue;
+    worker_rows_kernel<<<(unsigned)((f + kBlock - 1) / kBlock), kBlock, 0, s>>>(K, r, f, row_of);
     return hipGetLastError();
 }
 

@@ -64,7 +64,8 @@ __global__ void __launch_bounds__(kWsThreads)
 fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f, int64_t d,
                 const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
                 const int32_t *__restrict__ n_sel, int64_t ntiles,
-                uint32_t *__restrict__ pair_diff, float *__restrict__ out) {
+                uint32_t *__restrict__ pair_diff, float *__restrict__ out, PathGate gate) {
+    if (gate.closed()) return;
     extern __shared__ __align__(16) uint32_t smem[];
     constexpr int G = (kWsThreads - FILL) / T;   // selection lanes per column
     constexpr int CPR = T / 4;           // float4 chunks per row segment
@@ -515,7 +516,8 @@ constexpr int ws_key(int T, int sweeps, bool half) { return T * 1000 + sweeps * 
 #define ASPIS_NT(kernel, ...) (p.lines ? &kernel<__VA_ARGS__, true> : &kernel<__VA_ARGS__, false>)
 
 using FusedWsFn = void (*)(const float *, const int32_t *, int64_t, int64_t, const int32_t *,
-                           const int32_t *, const int32_t *, int64_t, uint32_t *, float *);
+                           const int32_t *, const int32_t *, int64_t, uint32_t *, float *,
+                           PathGate);
 using MedianWsFn = void (*)(const float *, int64_t, const int32_t *, const int32_t *, int64_t,
                             bool, float *, TileMask);
 

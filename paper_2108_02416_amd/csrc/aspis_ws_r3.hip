@@ -43,6 +43,7 @@ FusedWsFn fused_ws_r3_fn(const WsPlan &p) {
         ASPIS_FWS_NARROW(8, 8, false)
         ASPIS_FWS_NARROW(8, 12, false)
         ASPIS_FWS_NARROW(8, 16, false)
+        ASPIS_FWS(128, 4, true)
         ASPIS_FWS(128, 8, true)
         ASPIS_FWS(128, 12, true)
         ASPIS_FWS(128, 16, true)

@@ -1,0 +1,66 @@
+"""The guess of the single pass is made on the device (clique search, choice of
+the reduction and the key tiles, selection, row table of a worker-major
+upload): every outcome against the oracle, and the guess right where the
+probe covers the vector."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from paper_2108_02416_amd import aspis
+
+from test_gpu_steady import _compare, _oracle, _run
+
+pytestmark = pytest.mark.gpu
+
+
+def _honest(K, r, d):
+    wl = synth.Workload(0, K, r, 0, d, synth.DIST_NORMAL, "weak", "reversed", "fixed")
+    s = oracle.assign(K, r)
+    g, _ = synth.generate(wl, s, d=d)
+    return g, s
+
+
+@pytest.mark.parametrize("K,r,q,pairs", [
+    (7, 3, 3, []),                                  # complete graph
+    (9, 3, 2, [(0, 8)]),                            # two maximum cliques
+    (10, 3, 4, [(0, 1), (0, 2), (0, 3)]),           # one maximum clique
+    (10, 3, 1, [(0, 1), (2, 3)]),                   # none large enough
+    (12, 5, 3, [(0, 11), (1, 11), (2, 11)]),
+    (24, 3, 11, [(2 * j, 2 * j + 1) for j in range(12)]),   # 4,096 of them: the search gives up
+])
+@pytest.mark.parametrize("mode", ["median", "paper"])
+def test_guess_of_planted_graphs(K, r, q, pairs, mode):
+    """Worker v's replica differs from worker u's in every common file."""
+    d = 40
+    g, s = _honest(K, r, d)
+    for u, v in pairs:
+        for i in np.flatnonzero((s == u).any(axis=1) & (s == v).any(axis=1)):
+            g[i, int(np.flatnonzero(s[i] == v)[0]), (u * K + v) % d] += np.float32(1.0)
+    ref = _oracle(g, K, r, q, mode)
+    for layout in ("file", "worker"):
+        got = _run(g, K, r, q, mode, 0, layout)
+        _compare(got, ref, K, mode)
+        assert got["stats"]["fused"] == 1 and got["stats"]["speculation_hit"] == 1
+
+
+@pytest.mark.parametrize("K,r", [(41, 3), (64, 3), (14, 7), (19, 5)])
+def test_row_table_of_many_workers(K, r):
+    g, _ = _honest(K, r, 4)
+    got = _run(g, K, r, 2, "mean", 0, "worker")
+    _compare(got, _oracle(g, K, r, 2, "mean"), K, "mean")
+
+
+@pytest.mark.parametrize("d", [128 * 256, 128 * 256 + 4, 128 * 256 + 133])
+def test_few_files_either_side_of_the_half_key_line(d):
+    """35 files take half-key tiles from 32,769 coordinates on."""
+    K, r, q = 7, 3, 2
+    wl = synth.Workload(0, K, r, q, d, synth.DIST_NORMAL, "weak", "reversed", "fixed")
+    g, _ = synth.generate(wl, oracle.assign(K, r), d=d)
+    got = _run(g, K, r, q)
+    _compare(got, _oracle(g, K, r, q, "median"), K, "median")
+    assert (got["stats"]["tile_cols"], got["stats"]["half_keys"]) == \
+        ((128, 1) if d > 128 * 256 else (64, 0))
+    full = _run(g, K, r, q, flags=aspis.FLAG_FULL_KEYS)
+    assert full["stats"]["half_keys"] == 0
+    assert (full["out"] == got["out"]).all()
