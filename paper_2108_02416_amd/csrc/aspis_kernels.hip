@@ -666,13 +666,115 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
 // one row per load.  The pair-difference bits of a wave are combined with
 // ballots into per-workgroup LDS words, merged into pair_diff at the end.
 
-// files per burst of loads (R rows each): 3 keeps the kernel at 62 VGPRs,
-// 8 waves per SIMD (4 files: 74 VGPRs, 6 waves, 3.7 % slower at K=21, d=5M)
+// Bound by HBM.  A lane's loads run in a ring of B files (a file is processed,
+// its registers take the load of the file B further on), so that few waves
+// keep the memory busy: 455 files, d = 1M 0.97 -> 0.85 ms, d = 0.2M 0.71 ->
+// 0.20 ms (linear reads 0.77 and 0.17); 462 files at r = 5, d = 4M 6.83 -> 5.82
+// ms; 120 files at r = 7, d = 0.4M 0.55 -> 0.23 ms, all against bursts of
+// loads waited for together.  At r = 3 those bursts (62 registers, 8
+// workgroups per CU) stay where the vector gives each CU more than 4 and at
+// most 8 workgroups, which then run as one full round: 455 files, d = 2M, 1.67
+// against 1.72 ms.
+constexpr int64_t kMeanBurstMin = 4, kMeanBurstMax = 8;   // workgroups per CU
+
+// IND: rows through the table row_of.  SHORT: rows of fewer than four
+// coordinates.
+template <int R, int B, bool IND, bool SHORT>
+__global__ void __launch_bounds__(kBlock)
+fused_mean_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
+                  int64_t d, const int32_t *__restrict__ sel, const int32_t *__restrict__ n_sel,
+                  uint32_t *__restrict__ pair_diff, float *__restrict__ out, PathGate gate) {
+    if (gate.closed()) return;
+    extern __shared__ uint32_t pdw[];   // [f]
+    const int tid = threadIdx.x;
+    const int nf = (int)f;
+    for (int i = tid; i < nf; i += kBlock) pdw[i] = 0u;
+    __syncthreads();
+    const int n = *n_sel;
+    const int64_t nq = (d + 3) / 4;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    // every lane of a workgroup runs the same iterations (the ballots need
+    // whole waves); a lane at or past the end of the rows reads their last
+    // four coordinates
+    for (int64_t q0 = (int64_t)blockIdx.x * kBlock; q0 < nq; q0 += stride) {
+        const int64_t k = (q0 + tid) * 4;
+        const int64_t col = SHORT ? 0 : chunk_start(k, d);
+        const float *at = g + col;
+        struct Chunks {
+            uint4 q[R];
+        };
+        auto load_file = [&](int i) __attribute__((always_inline)) {
+            Chunks c;
+#pragma unroll
+            for (int s = 0; s < R; ++s) {
+                const float *row = at + (IND ? (int64_t)row_of[i * R + s] : (int64_t)i * R + s) * d;
+                if constexpr (SHORT) {
+                    uint32_t v[4];
+                    load4(row, 0, d, v);
+                    c.q[s] = make_uint4(v[0], v[1], v[2], v[3]);
+                } else {
+                    c.q[s] = load_stream(row);
+                }
+            }
+            return c;
+        };
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        Chunks c[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (b < nf) c[b] = load_file(b);
+        for (int ib = 0; ib < nf; ib += B) {
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int i = ib + b;
+                if (i >= nf) break;
+                uint32_t wdiff = 0u;   // of the wave
+                int p = 0;
+#pragma unroll
+                for (int s = 0; s < R; ++s)
+#pragma unroll
+                    for (int u = s + 1; u < R; ++u) {
+                        const uint4 x = c[b].q[s], y = c[b].q[u];
+                        const uint32_t z = (x.x ^ y.x) | (x.y ^ y.y) | (x.z ^ y.z) | (x.w ^ y.w);
+                        if (__ballot(z != 0u)) wdiff |= 1u << p;
+                        ++p;
+                    }
+                if ((tid & 63) == 0 && wdiff) atomicOr(&pdw[i], wdiff);
+                const int s_sel = sel[i];
+                if (s_sel >= 0) {
+                    uint4 w = c[b].q[0];
+#pragma unroll
+                    for (int s = 1; s < R; ++s)
+                        if (s_sel == s) w = c[b].q[s];
+                    acc[0] += (double)__uint_as_float(w.x);
+                    acc[1] += (double)__uint_as_float(w.y);
+                    acc[2] += (double)__uint_as_float(w.z);
+                    acc[3] += (double)__uint_as_float(w.w);
+                }
+                // each ring place refilled before the next file is processed
+                __builtin_amdgcn_sched_barrier(0);
+                if (i + B < nf) c[b] = load_file(i + B);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (k < d && n > 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + e < d) out[col + e] = (float)(acc[e] / (double)n);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < nf; i += kBlock)
+        if (pdw[i]) atomicOr(&pair_diff[i], pdw[i]);
+}
+
+// The same at r = 3 in bursts of three files (R rows each), all loads of a burst
+// issued first: 62 VGPRs, 8 workgroups per CU.
 constexpr int kMeanFiles = 3;
 
 template <int R>
 __global__ void __launch_bounds__(kBlock)
-fused_mean_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
+fused_mean_burst_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f,
                   int64_t d, const int32_t *__restrict__ sel, const int32_t *__restrict__ pos,
                   const int32_t *__restrict__ n_sel, uint32_t *__restrict__ pair_diff,
                   float *__restrict__ out, PathGate gate) {
@@ -1690,15 +1792,34 @@ hipError_t launch_fused_mean_if(const float *g, const int32_t *row_of, int64_t f
     // left K=21, d=5M 7 % slower)
     const unsigned grid = (unsigned)grid_for((nq + kBlock - 1) / kBlock, (int64_t)num_cus() * 8);
     const size_t lds = (size_t)f * 4;
-#define ASPIS_FMEAN(RR)                                                                      \
-    fused_mean_kernel<RR><<<grid, kBlock, lds, s>>>(g, row_of, f, d, ws.sel, ws.pos, ws.n_sel, \
-                                                    pair_diff, out, gate);
+#define ASPIS_FMEAN_(RR, BB, IND, SHORT)                                            \
+    fused_mean_kernel<RR, BB, IND, SHORT><<<grid, kBlock, lds, s>>>(                \
+        g, row_of, f, d, ws.sel, ws.n_sel, pair_diff, out, gate);
+#define ASPIS_FMEAN(RR, BB)                   \
+    if (d < 4 && row_of) {                    \
+        ASPIS_FMEAN_(RR, 1, true, true)       \
+    } else if (d < 4) {                       \
+        ASPIS_FMEAN_(RR, 1, false, true)      \
+    } else if (row_of) {                      \
+        ASPIS_FMEAN_(RR, BB, true, false)     \
+    } else {                                  \
+        ASPIS_FMEAN_(RR, BB, false, false)    \
+    }
+    const int64_t blocks = (nq + kBlock - 1) / kBlock;
     switch (r) {
-    case 3: ASPIS_FMEAN(3) break;
-    case 5: ASPIS_FMEAN(5) break;
-    case 7: ASPIS_FMEAN(7) break;
+    case 3:
+        if (blocks > kMeanBurstMin * num_cus() && blocks <= kMeanBurstMax * num_cus()) {
+            fused_mean_burst_kernel<3><<<grid, kBlock, lds, s>>>(g, row_of, f, d, ws.sel, ws.pos,
+                                                                 ws.n_sel, pair_diff, out, gate);
+        } else {
+            ASPIS_FMEAN(3, 6)
+        }
+        break;
+    case 5: ASPIS_FMEAN(5, 3) break;
+    case 7: ASPIS_FMEAN(7, 3) break;
     default: return hipErrorInvalidValue;
     }
+#undef ASPIS_FMEAN_
 #undef ASPIS_FMEAN
     return hipGetLastError();
 }

@@ -55,9 +55,20 @@ def test_any_row_length(K, r, q, layout, flags, tiles, extra):
     _compare(got, _oracle(g, K, r, q, "median"), K, "median")
 
 
-@pytest.mark.parametrize("mode", ["mean", "paper"])
-def test_any_row_length_mean(mode):
-    K, r, q, d = 10, 3, 2, 4 * 256 * 11 + 3
+@pytest.mark.parametrize("mode,K,r,q,d", [
+    ("mean", 10, 3, 2, 4 * 256 * 11 + 3),
+    ("paper", 10, 3, 2, 4 * 256 * 11 + 3),
+    ("mean", 5, 3, 1, 1024 * 4 * CUS),          # either side of the line to bursts
+    ("mean", 5, 3, 1, 1024 * 4 * CUS + 1),
+    ("mean", 5, 3, 1, 1024 * 8 * CUS + 5),      # and back, two rounds of the grid
+    ("mean", 8, 5, 2, 1024 * 3 + 2),
+    ("mean", 8, 7, 2, 1024 * 3 + 1),
+    ("mean", 7, 3, 2, 3),                       # rows shorter than a chunk
+    ("mean", 7, 5, 2, 2),
+    ("mean", 8, 7, 2, 1),
+    ("mean", 7, 3, 2, 4),
+])
+def test_any_row_length_mean(mode, K, r, q, d):
     wl = synth.Workload(0, K, r, q, d, synth.DIST_NORMAL, "weak", "reversed", "fixed")
     g, _ = synth.generate(wl, oracle.assign(K, r), d=d)
     for layout in ("file", "worker"):
