@@ -10,8 +10,10 @@
 //
 //   agree_kernel       Eq. (4): per file, OR over coordinates of "slot pair p
 //                      differs"; one coalesced stream over the r rows.
-//   agree_file_kernel  the same over a coordinate prefix, one workgroup per
-//                      file (the probe of the single pass).
+//   probe_kernel       the same over the probe's blocks, with the tie probe
+//                      (agree_file_kernel and tie_probe_kernel: each alone).
+//   guess_kernel       the probe's votes, clique search and selection, and
+//                      the reduction it calls for, in one workgroup.
 //   vote_kernel        Eq. (3) majority per file and the K x K disagreement
 //                      rows (Section 4: edge iff the pair agrees on all
 //                      common files).
