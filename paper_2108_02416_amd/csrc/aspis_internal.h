@@ -182,10 +182,7 @@ hipError_t scratch_ptr(void **out);
 //
 // launch_probe, launch_guess, one main kernel per reduction the guess may call
 // for (each gated on the device's choice), launch_finish; one copy of the
-// stage words then tells the host whether the guess held.  The names below
-// are weak: a build of the host sources alone has no device code, and
-// fused_supported tells it so.
-#define ASPIS_DEVICE __attribute__((weak))
+// stage words then tells the host whether the guess held.
 
 // The reduction the guess calls for.
 constexpr int kPathHalfKeys = 0, kPathFullKeys = 1, kPathMean = 2;
@@ -213,34 +210,33 @@ struct PathGate {
 
 // Single pass for f files of r replicas of d coordinates (false: none, the step
 // then takes two passes); ind: rows through a row table; full_keys as above.
-ASPIS_DEVICE bool plan_single_pass(int64_t f, int r, int64_t d, bool ind, KernelPlan *out,
-                        bool full_keys);
+bool plan_single_pass(int64_t f, int r, int64_t d, bool ind, KernelPlan *out, bool full_keys);
 // Agreement over the probe, each file's blocks over *split workgroups (the
 // words in ws.dirty), and n_tie (0: none) tie counts, in one launch.
 // f <= kDirtyWords.
-ASPIS_DEVICE hipError_t launch_probe(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
+hipError_t launch_probe(const float *g, const int32_t *row_of, int64_t f, int r, int64_t d,
                         const ProbeSet &probe, const Workspace &ws, int n_tie, int *split,
                         hipStream_t s);
 // Votes, disagreement rows, clique search and selection of the probe into
 // vote, has_majority, disagree and the workspace; zeroes pair_diff; the
 // reduction to ws.n_sel[1] (kPath...).
-ASPIS_DEVICE hipError_t launch_guess(const int32_t *subsets, const int32_t *row_of, int64_t f, int r,
+hipError_t launch_guess(const int32_t *subsets, const int32_t *row_of, int64_t f, int r,
                         int K, int q, int mode, int keys, int n_tie, int split, int8_t *vote,
                         uint8_t *has_majority, uint64_t *disagree, uint32_t *pair_diff,
                         const Workspace &ws, hipStream_t s);
-ASPIS_DEVICE hipError_t launch_fused_if(const float *g, const int32_t *row_of, int64_t f, int r,
-                        int64_t d, const Workspace &ws, uint32_t *pair_diff, float *out,
-                        hipStream_t s, TileUse *use, bool full_keys, PathGate gate);
-ASPIS_DEVICE hipError_t launch_fused_mean_if(const float *g, const int32_t *row_of, int64_t f, int r,
-                        int64_t d, const Workspace &ws, uint32_t *pair_diff, float *out,
-                        hipStream_t s, PathGate gate);
+hipError_t launch_fused_if(const float *g, const int32_t *row_of, int64_t f, int r,
+                           int64_t d, const Workspace &ws, uint32_t *pair_diff, float *out,
+                           hipStream_t s, TileUse *use, bool full_keys, PathGate gate);
+hipError_t launch_fused_mean_if(const float *g, const int32_t *row_of, int64_t f, int r,
+                                int64_t d, const Workspace &ws, uint32_t *pair_diff, float *out,
+                                hipStream_t s, PathGate gate);
 // launch_vote_rows on the full agreement, and the guessed selection to
 // sel_out when it is not NULL.
-ASPIS_DEVICE hipError_t launch_finish(const uint32_t *pair_diff, const int32_t *subsets, int64_t f,
-                        int r, int K, int8_t *vote, uint8_t *has_majority, uint64_t *disagree,
-                        const Workspace &ws, int32_t *sel_out, hipStream_t s);
+hipError_t launch_finish(const uint32_t *pair_diff, const int32_t *subsets, int64_t f,
+                         int r, int K, int8_t *vote, uint8_t *has_majority, uint64_t *disagree,
+                         const Workspace &ws, int32_t *sel_out, hipStream_t s);
 // The row table of a worker-major upload (aspis_worker_rows).
-ASPIS_DEVICE hipError_t launch_worker_rows(int K, int r, int64_t f, int32_t *row_of, hipStream_t s);
+hipError_t launch_worker_rows(int K, int r, int64_t f, int32_t *row_of, hipStream_t s);
 
 // Tie probe over the probed coordinates: for min(kTieCols, probe.coords())
 // coordinates spread over them, out[j] = the number of files whose value

@@ -10,7 +10,11 @@ namespace aspis {
 size_t workspace_bytes(int64_t f, int r) {
     return (size_t)f * 12 + 256 + 1024 + (size_t)f * r * 4 + 1024 + (size_t)f + kDirtyWords * 4 + 256;
 }
-Workspace carve_workspace(void *, int64_t, int) { return Workspace{}; }
+Workspace carve_workspace(void *base, int64_t, int) {
+    Workspace w{};
+    w.stage = static_cast<uint64_t *>(base);   // the host offsets it
+    return w;
+}
 hipError_t launch_fill_u32(uint32_t *, int64_t, uint32_t, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_fill_u64(uint64_t *, int64_t, uint64_t, hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_agree(const float *, const int32_t *, int64_t, int, int64_t, int64_t, uint32_t *,
@@ -39,7 +43,7 @@ bool plan_median(int64_t, bool, KernelPlan *out, bool) {
     out->kind = kKernelMedianRadix;
     return true;
 }
-bool plan_fused(int64_t, int, bool, bool, KernelPlan *out, bool) {
+bool plan_single_pass(int64_t, int, int64_t, bool, KernelPlan *out, bool) {
     *out = KernelPlan{};
     return false;
 }
@@ -71,6 +75,27 @@ hipError_t launch_dirty_tiles(const float *, const int32_t *, int64_t, int, int6
     return hipErrorInvalidValue;
 }
 int reduce_tile_cols(const float *, int64_t, int64_t, bool, bool) { return 0; }
+hipError_t launch_probe(const float *, const int32_t *, int64_t, int, int64_t, const ProbeSet &,
+                        const Workspace &, int, int *, hipStream_t) {
+    return hipErrorInvalidValue;
+}
+hipError_t launch_guess(const int32_t *, const int32_t *, int64_t, int, int, int, int, int, int, int,
+                        int8_t *, uint8_t *, uint64_t *, uint32_t *, const Workspace &, hipStream_t) {
+    return hipErrorInvalidValue;
+}
+hipError_t launch_fused_if(const float *, const int32_t *, int64_t, int, int64_t, const Workspace &,
+                           uint32_t *, float *, hipStream_t, TileUse *, bool, PathGate) {
+    return hipErrorInvalidValue;
+}
+hipError_t launch_fused_mean_if(const float *, const int32_t *, int64_t, int, int64_t,
+                                const Workspace &, uint32_t *, float *, hipStream_t, PathGate) {
+    return hipErrorInvalidValue;
+}
+hipError_t launch_finish(const uint32_t *, const int32_t *, int64_t, int, int, int8_t *, uint8_t *,
+                         uint64_t *, const Workspace &, int32_t *, hipStream_t) {
+    return hipErrorInvalidValue;
+}
+hipError_t launch_worker_rows(int, int, int64_t, int32_t *, hipStream_t) { return hipErrorInvalidValue; }
 size_t read_probe_sink_words() { return 0; }
 hipError_t launch_read_probe(const void *, size_t, uint32_t *, hipStream_t) {
     return hipErrorInvalidValue;

@@ -91,6 +91,27 @@ int main() {
     aspis_detect_out det{(uint32_t *)16, (int8_t *)16, (uint8_t *)16, (uint64_t *)16};
     CHECK(aspis_detect((const float *)16, 7, 4, 10, (const int32_t *)16, &det, nullptr) == ASPIS_ERR_INVALID_ARG);
     CHECK(aspis_detect(nullptr, 7, 3, 10, (const int32_t *)16, &det, nullptr) == ASPIS_ERR_INVALID_ARG);
+    // ... and report a launcher that fails; the plans come from the planners
+    {
+        const int32_t K = 7, r = 3;
+        const int64_t d = 40;
+        const size_t bytes = aspis_aggregate_workspace(K, r, d);
+        CHECK(bytes > 0);
+        void *ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+        CHECK(ws != nullptr);
+        aspis_clique_result cr;
+        int64_t kept = 0;
+        CHECK(aspis_detect_aggregate_wm((const float *)16, K, r, 2, d, (const int32_t *)16, &det,
+                                        ASPIS_REDUCE_MEDIAN, (float *)16, nullptr, &cr, &kept, ws, bytes,
+                                        0, nullptr, nullptr) == ASPIS_ERR_DEVICE);
+        CHECK(aspis_detect_aggregate((const float *)16, K, r, 2, d, (const int32_t *)16, &det,
+                                     ASPIS_REDUCE_MEDIAN, (float *)16, nullptr, &cr, &kept, ws, bytes,
+                                     0, nullptr, nullptr) == ASPIS_ERR_DEVICE);
+        std::free(ws);
+        aspis_kernel_plan sp, med;
+        CHECK(aspis_plan(K, r, d, 1, 0, &sp, &med) == ASPIS_OK);
+        CHECK(sp.kernel == ASPIS_KERNEL_NONE && med.kernel == ASPIS_KERNEL_MEDIAN_RADIX);
+    }
     // the oracle's median and mean on a small case
     const int64_t f = 5, r = 3, n = 4;
     std::vector<float> g((size_t)f * r * n);
