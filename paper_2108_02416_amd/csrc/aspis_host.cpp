@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../../include/aspis.h"
+#include "aspis_guess.h"
 #include "aspis_internal.h"
 
 namespace {
@@ -483,7 +484,8 @@ aspis_status detect_aggregate_impl(const float *grads, bool worker_major, int32_
         bool guess_mean = false, ran = false;
         aspis::TileUse fused_tile{};   // stays empty for the mean
         const bool may_median = mode != ASPIS_REDUCE_MEAN, may_mean = mode != ASPIS_REDUCE_MEDIAN;
-        if (f <= aspis::kDirtyWords && (!may_median || aspis::fused_supported(f, r)) &&
+        if (f <= aspis::kDirtyWords && K <= aspis::kGuessMaxK &&
+            (!may_median || aspis::fused_supported(f, r)) &&
             (!may_mean || aspis::fused_mean_supported(f, r))) {
             // every reduction the guess may call for has a single pass: the
             // guess stays on the device, and each candidate kernel runs or

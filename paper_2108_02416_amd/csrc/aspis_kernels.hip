@@ -46,6 +46,7 @@
 #include <atomic>
 #include <cstdint>
 
+#include "aspis_guess.h"
 #include "aspis_ws.h"
 
 namespace aspis {
@@ -355,74 +356,32 @@ select_kernel(const int32_t *__restrict__ subsets,
 // would cost the step a copy, a synchronisation and a launch before its main
 // kernel can start
 
-// Whether the detection graph has exactly one maximum clique and it holds at
-// least `need` workers, as the host's aspis_clique decides it; by one wave,
-// which all run in step.  nbr (LDS): neighbour masks, lane u's in nbr[u], 0
-// from K on.  Bron-Kerbosch with Tomita's pivot, bounded below by need and
-// the largest clique found (branches that cannot reach it are cut); at most
-// kGuessSteps branches, then it gives up and answers no (a wrong guess costs
-// time, never the result).
-constexpr int kGuessSteps = 1024;
-struct GuessStack {
-    uint64_t P[65], X[65], R[65], todo[65];
-};
-__device__ __forceinline__ bool guess_clique(const unsigned long long *nbr, int K, int need,
-                                             volatile GuessStack *st, uint64_t *honest) {
-    const int lane = threadIdx.x & 63;
-    const uint64_t mine = nbr[lane];
-    int best = need, count = 0, depth = 0;
-    uint64_t found = 0ull;
-    // the candidates not adjacent to the pivot, the vertex of P or X adjacent
-    // to most of P
-    auto branch = [&](uint64_t P, uint64_t X) {
-        const bool in = ((P | X) >> lane) & 1ull;
-        const uint32_t deg = in ? (uint32_t)__popcll(P & mine) + 1u : 0u;
-        const uint32_t top = group_reduce<64, Op::Max>(deg);
-        const int pivot = __ffsll((unsigned long long)__ballot(in && deg == top)) - 1;
-        return P & ~nbr[pivot];
-    };
-    const uint64_t all = K == 64 ? ~0ull : (1ull << K) - 1ull;
-    st->P[0] = all;
-    st->X[0] = 0ull;
-    st->R[0] = 0ull;
-    st->todo[0] = branch(all, 0ull);
-    for (int step = 0; depth >= 0; ++step) {
-        if (step >= kGuessSteps) return false;
-        const uint64_t todo = st->todo[depth];
-        if (todo == 0ull) {
-            --depth;
-            continue;
-        }
-        const int v = __ffsll((unsigned long long)todo) - 1;
-        const uint64_t bit = 1ull << v, nv = nbr[v];
-        const uint64_t P = st->P[depth], X = st->X[depth];
-        const uint64_t P2 = P & nv, X2 = X & nv, R2 = st->R[depth] | bit;
-        st->todo[depth] = todo & ~bit;
-        st->P[depth] = P & ~bit;
-        st->X[depth] = X | bit;
-        const int size = __popcll(R2);
-        if (P2 == 0ull) {
-            if (X2 == 0ull && size >= best) {
-                if (size > best) count = 0;
-                best = size;
-                if (count++ == 0) found = R2;
-            }
-        } else if (size + __popcll(P2) >= best) {
-            ++depth;
-            st->P[depth] = P2;
-            st->X[depth] = X2;
-            st->R[depth] = R2;
-            st->todo[depth] = branch(P2, X2);
-        }
+// The operations of guess_clique by one wave, whose 64 lanes all run in step:
+// lane u holds the workers that disagree with worker u (0 from K on) and, at
+// lane d, the open branch of depth d.  Everything else is the same in every
+// lane, so it stays in scalar registers.
+struct GuessWave {
+    uint32_t dis, stack, lane;
+    __device__ void pairs(uint32_t C, uint32_t bits[5]) const {
+        const uint32_t n = (C >> (lane & 31u)) & 1u ? (uint32_t)__popc(C & dis) : 0u;
+#pragma unroll
+        for (int b = 0; b < 5; ++b) bits[b] = (uint32_t)__ballot((n >> b) & 1u);
     }
-    *honest = found;
-    return count == 1;
-}
+    __device__ uint32_t against(int v) const {
+        return (uint32_t)__builtin_amdgcn_readlane((int)dis, v);
+    }
+    __device__ void push(int depth, uint32_t C) {
+        stack = lane == (uint32_t)depth ? C : stack;
+    }
+    __device__ uint32_t pop(int depth) const {
+        return (uint32_t)__builtin_amdgcn_readlane((int)stack, depth);
+    }
+};
 
 // The probe's outcome in one workgroup: votes and disagreement rows from the
 // files' partial words (split: how many a file has, file i's at part[s*f +
 // i]), the clique search, the guessed selection into the workspace, the
-// reduction the guess calls for (path_out, GuessPath), and pair_diff zeroed
+// reduction the guess calls for (path_out, a kPath value), and pair_diff zeroed
 // for the main pass.  stage: as vote_rows_kernel's, without the flag;
 // stage[kStageGuess] = success | path << 8, stage[kStageGuess + 1] = the
 // honest mask.
@@ -436,12 +395,11 @@ guess_kernel(const uint32_t *__restrict__ part, int split, const int32_t *__rest
              uint64_t *__restrict__ stage, uint32_t *__restrict__ pair_diff,
              int32_t *__restrict__ sel, int32_t *__restrict__ pos, int32_t *__restrict__ rows,
              int32_t *__restrict__ n_sel, int32_t *__restrict__ path_out) {
-    __shared__ unsigned long long nbr[64];
-    __shared__ GuessStack stack;
+    __shared__ unsigned long long dis_rows[64];
     __shared__ int success;
     __shared__ uint64_t honest;
     const int tid = threadIdx.x;
-    if (tid < 64) nbr[tid] = 0ull;   // disagreement rows, then neighbours
+    if (tid < 64) dis_rows[tid] = 0ull;
     __syncthreads();
     for (int64_t i = tid; i < f; i += 1024) {
         uint32_t pd = 0u;
@@ -449,8 +407,8 @@ guess_kernel(const uint32_t *__restrict__ part, int split, const int32_t *__rest
         int best = 0, best_n = 0;
         file_vote<R>(pd, &best, &best_n, [&](int s, int t) {
             const int us = subsets[i * R + s], ut = subsets[i * R + t];
-            atomicOr(&nbr[us], 1ull << ut);
-            atomicOr(&nbr[ut], 1ull << us);
+            atomicOr(&dis_rows[us], 1ull << ut);
+            atomicOr(&dis_rows[ut], 1ull << us);
         });
         vote[i] = (int8_t)best;
         has_majority[i] = (uint8_t)(best_n >= (R + 1) / 2);
@@ -458,16 +416,14 @@ guess_kernel(const uint32_t *__restrict__ part, int split, const int32_t *__rest
     }
     __syncthreads();
     if (tid < 64) {
-        const uint64_t all = K == 64 ? ~0ull : (1ull << K) - 1ull;
-        const uint64_t dis = nbr[tid];
+        const uint64_t dis = dis_rows[tid];
         if (tid < K) {
             disagree[tid] = dis;
             stage[tid] = dis;
         }
-        nbr[tid] = tid < K ? all & ~dis & ~(1ull << tid) : 0ull;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        uint64_t h = 0ull;
-        const bool ok = guess_clique(nbr, K, need, &stack, &h);
+        GuessWave wave{tid < K ? (uint32_t)dis : 0u, 0u, (uint32_t)tid};
+        uint32_t h = 0u;
+        const bool ok = guess_clique(wave, K, need, &h);
         // the tie estimate: the mean count, rounded up
         uint32_t full = keys == kKeysFull ? 1u : 0u;
         if (keys == kKeysProbe) {
@@ -1917,7 +1873,8 @@ hipError_t launch_guess(const int32_t *subsets, const int32_t *row_of, int64_t f
                         int mode, int keys, int n_tie, int split, int8_t *vote,
                         uint8_t *has_majority, uint64_t *disagree, uint32_t *pair_diff,
                         const Workspace &ws, hipStream_t s) {
-    if (f <= 0 || f > kDirtyWords || K < 1 || K > 64 || (keys == kKeysProbe && n_tie < 1))
+    if (f <= 0 || f > kDirtyWords || K < 1 || K > kGuessMaxK || q < 0 || q >= K ||
+        (keys == kKeysProbe && n_tie < 1))
         return hipErrorInvalidValue;
     const uint32_t *ties = reinterpret_cast<const uint32_t *>(ws.stage + kStageTie);
 #define ASPIS_GUESS(RR)                                                                          \

@@ -1,6 +1,7 @@
 // Exercises the host entry points of libaspis and the oracle under
 // AddressSanitizer / UndefinedBehaviorSanitizer: assignment, worker row
 // tables, clique enumeration on random and structured graphs up to K = 128,
+// the device guess's clique search over host operations against it,
 // the distortion-fraction simulator (multithreaded) and DETOX, the argument
 // checks of the device entry points, and the oracle's C functions.  Prints
 // "ok" and exits 0 when every check holds.
@@ -8,9 +9,11 @@
 #include <cstdio>
 #include <cstdlib>
 #include <random>
+#include <utility>
 #include <vector>
 
 #include "../../include/aspis.h"
+#include "../../paper_2108_02416_amd/csrc/aspis_guess.h"
 
 extern "C" {
 #include "../../oracle/oracle.h"
@@ -23,6 +26,46 @@ extern "C" {
             std::exit(1);                                               \
         }                                                               \
     } while (0)
+
+// guess_clique's wave operations, one worker after another
+struct HostWave {
+    const std::vector<uint64_t> &rows;
+    std::vector<uint32_t> open;
+    int nodes = 0;
+    void pairs(uint32_t C, uint32_t bits[5]) {
+        ++nodes;
+        for (int b = 0; b < 5; ++b) bits[b] = 0;
+        for (size_t u = 0; u < rows.size(); ++u) {
+            const int n = C >> u & 1u ? __builtin_popcount(C & (uint32_t)rows[u]) : 0;
+            for (int b = 0; b < 5; ++b) bits[b] |= (uint32_t)(n >> b & 1) << u;
+        }
+    }
+    uint32_t against(int v) const { return (uint32_t)rows[(size_t)v]; }
+    void push(int depth, uint32_t C) {
+        CHECK(depth >= 0 && depth < 64);
+        open.resize((size_t)depth + 1);
+        open[(size_t)depth] = C;
+    }
+    uint32_t pop(int depth) const { return open.at((size_t)depth); }
+};
+
+// the guess's clique search against the host's, on K workers and pairs that
+// disagree
+void check_guess(int K, int q, const std::vector<std::pair<int, int>> &pairs) {
+    std::vector<uint64_t> rows((size_t)K, 0);
+    for (auto [u, v] : pairs) {
+        rows[(size_t)u] |= 1ull << v;
+        rows[(size_t)v] |= 1ull << u;
+    }
+    aspis_clique_result ref;
+    CHECK(aspis_clique(rows.data(), K, q, &ref) == ASPIS_OK);
+    HostWave wave{rows, {}};
+    uint32_t honest = 0;
+    const bool ok = aspis::guess_clique(wave, K, K - q, &honest);
+    CHECK(ok == (ref.success != 0));
+    CHECK(!ok || honest == ref.honest[0]);
+    CHECK(wave.nodes <= 1596);
+}
 
 int main() {
     // assignment and worker rows against the oracle's assignment
@@ -71,6 +114,36 @@ int main() {
         CHECK(oracle_cliques(adj.data(), K, 0, &ref) == 0);
         CHECK(res.omega == ref.omega && res.n_maximum == ref.n_maximum);
         CHECK(res.n_maximal == ref.n_maximal);
+    }
+    // the device guess's clique search: random graphs of every density, few
+    // disagreements among many workers (where it branches most), the attacks
+    for (int trial = 0; trial < 3000; ++trial) {
+        const int K = 3 + (int)(rng() % 18), q = (int)(rng() % (uint64_t)((K + 1) / 2));
+        const uint64_t density = rng() % 60;
+        std::vector<std::pair<int, int>> pairs;
+        for (int u = 0; u < K; ++u)
+            for (int v = u + 1; v < K; ++v)
+                if (rng() % 100 < density) pairs.emplace_back(u, v);
+        check_guess(K, q, pairs);
+    }
+    for (int trial = 0; trial < 40; ++trial)
+        for (int K : {25, 27, 30}) {
+            // each adversary disagrees with `deg` honest workers
+            const int q = (K - 1) / 2 - (int)(rng() % 3), deg = 2 + (int)(rng() % 4);
+            std::vector<std::pair<int, int>> pairs;
+            for (int a = 0; a < q; ++a)
+                for (int j = 0; j < deg; ++j) pairs.emplace_back(a, q + (int)(rng() % (uint64_t)(K - q)));
+            check_guess(K, q, pairs);
+        }
+    for (int K : {3, 7, 24, 30}) {
+        const int q = (K - 1) / 2;
+        std::vector<std::pair<int, int>> none, weak, hidden, matched;
+        for (int a = 0; a < q; ++a) {
+            for (int u = q; u < K; ++u) weak.emplace_back(a, u);
+            for (int u = q; u < 2 * q; ++u) hidden.emplace_back(a, u);
+            matched.emplace_back(a, q + a);
+        }
+        for (const auto *p : {&none, &weak, &hidden, &matched}) check_guess(K, q, *p);
     }
     // simulator and DETOX, including a threaded K=60 run and bad arguments
     aspis_sim_result sr;

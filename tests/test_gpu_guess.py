@@ -2,6 +2,8 @@
 the reduction and the key tiles, selection, row table of a worker-major
 upload): every outcome against the oracle, and the guess right where the
 probe covers the vector."""
+import random
+
 import numpy as np
 import pytest
 
@@ -27,11 +29,12 @@ def _honest(K, r, d):
     (10, 3, 4, [(0, 1), (0, 2), (0, 3)]),           # one maximum clique
     (10, 3, 1, [(0, 1), (2, 3)]),                   # none large enough
     (12, 5, 3, [(0, 11), (1, 11), (2, 11)]),
-    (24, 3, 11, [(2 * j, 2 * j + 1) for j in range(12)]),   # 4,096 of them: the search gives up
+    (24, 3, 11, [(2 * j, 2 * j + 1) for j in range(12)]),   # the even workers: one too few
 ])
 @pytest.mark.parametrize("mode", ["median", "paper"])
 def test_guess_of_planted_graphs(K, r, q, pairs, mode):
-    """Worker v's replica differs from worker u's in every common file."""
+    """Worker v's replica differs from every other one of each file that it
+    shares with worker u."""
     d = 40
     g, s = _honest(K, r, d)
     for u, v in pairs:
@@ -42,6 +45,30 @@ def test_guess_of_planted_graphs(K, r, q, pairs, mode):
         got = _run(g, K, r, q, mode, 0, layout)
         _compare(got, ref, K, mode)
         assert got["stats"]["fused"] == 1 and got["stats"]["speculation_hit"] == 1
+
+
+@pytest.mark.parametrize("K,q,deg,seed", [
+    (30, 14, 3, 6), (30, 14, 3, 5), (30, 14, 3, 0), (27, 13, 3, 8), (30, 14, 2, 3), (25, 12, 3, 5),
+])
+@pytest.mark.parametrize("mode,layout", [("median", "file"), ("paper", "file"), ("paper", "worker"),
+                                         ("median", "worker")])
+def test_guess_of_sparse_disagreement(K, q, deg, seed, mode, layout):
+    """Every adversary disagrees with `deg` honest workers only, so the graph
+    has up to thousands of maximal cliques (1,935, 1,770, 690, 1,145, 2,576
+    and 561 here): the guess has to decide it all the same, both where one
+    clique is the largest and where several are."""
+    r, d = 3, 64
+    g, s = _honest(K, r, d)
+    rng = random.Random(seed)
+    against = [rng.sample(range(q, K), deg) for _ in range(q)]
+    for i, (a, u, v) in enumerate(s):
+        if a < q <= u and u in against[a] and v in against[a]:
+            g[i, 0, (int(a) * 7) % d] += np.float32(1.0)
+    ref = _oracle(g, K, r, q, mode)
+    assert ref["clique"]["success"] == ((deg, seed) not in ((3, 0), (2, 3)))
+    got = _run(g, K, r, q, mode, 0, layout)
+    _compare(got, ref, K, mode)
+    assert got["stats"]["fused"] == 1 and got["stats"]["speculation_hit"] == 1
 
 
 @pytest.mark.parametrize("K,r", [(41, 3), (64, 3), (14, 7), (19, 5)])
