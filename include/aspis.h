@@ -308,12 +308,8 @@ aspis_status aspis_detect_aggregate_wm(const float *grads_wm, int32_t K, int32_t
  * Errors: INVALID_ARG for an invalid shape (as aspis_detect) or when a
  * planned kernel is not built (the launch would fail the same way). */
 #define ASPIS_KERNEL_NONE 0          /* no kernel: the step takes two passes    */
-#define ASPIS_KERNEL_FUSED_WS 1      /* single pass, warp-specialised: r = 3, or
-                                        r = 5 on half-key tiles of a file-major
-                                        tensor; d a multiple of four            */
-#define ASPIS_KERNEL_FUSED 2         /* single pass on other shapes: warp-specialised
-                                        too when stream_threads > 0, else load
-                                        then select per tile                    */
+#define ASPIS_KERNEL_FUSED_WS 1      /* single pass, warp-specialised           */
+#define ASPIS_KERNEL_FUSED 2         /* single pass, load then select per tile  */
 #define ASPIS_KERNEL_MEDIAN_WS 3     /* median, warp-specialised                */
 #define ASPIS_KERNEL_MEDIAN_TILE 4   /* median, LDS key tile                    */
 #define ASPIS_KERNEL_MEDIAN_RADIX 5  /* median, radix select re-reading HBM     */

@@ -766,10 +766,6 @@ aspis_status aspis_plan(int32_t K, int32_t r, int64_t d, int32_t worker_major, u
     aspis::plan_median(f, vec, &med, full_keys);
     to_abi(fused, single_pass);
     to_abi(med, median);
-    // aspis.h: other shapes report the same kernel as ASPIS_KERNEL_FUSED
-    const bool listed = d % 4 == 0 && (r == 3 || (r == 5 && !worker_major && fused.half_keys));
-    if (!listed && single_pass->kernel == ASPIS_KERNEL_FUSED_WS)
-        single_pass->kernel = ASPIS_KERNEL_FUSED;
     if (fused.kind == aspis::kKernelUnbuilt || med.kind == aspis::kKernelUnbuilt)
         return fail(ASPIS_ERR_INVALID_ARG, "aspis_plan: K=%d r=%d d=%lld: a planned kernel is not built",
                     K, r, (long long)d);

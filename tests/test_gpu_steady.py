@@ -92,6 +92,10 @@ CASES = [
      dict(kernel="fused_ws", tile_cols=32, sweeps=24, stream_threads=768, row_table=2), 12),
     ("K=11 r=5 fused_ws<128,5,30,half>", 6, "file", 0,
      dict(kernel="fused_ws", tile_cols=128, sweeps=30, stream_threads=512), 36),
+    ("K=9 r=5 fused_ws<64,5,4>", (9, 5, 2, "weak", "reversed"), "file", 0,
+     dict(kernel="fused_ws", tile_cols=64, sweeps=4, half_keys=0, stream_threads=512), 20),
+    ("K=10 r=7 fused_ws<64,7,4>", (10, 7, 2, "weak", "reversed"), "file", 0,
+     dict(kernel="fused_ws", tile_cols=64, sweeps=4, half_keys=0, stream_threads=512), 20),
     ("headline two-pass median_ws<128,30,half>", 3, "file", _WS,
      dict(kernel="median_ws", tile_cols=128, sweeps=30), 36),
     ("K=25 two-pass median_ws<16,24,half>", 5, "file", _WS,
@@ -151,8 +155,8 @@ def test_steady_state_guess_miss_rerun():
 def test_steady_state_fused_mean(d):
     """The single pass of the mean (PAPER mode, detection succeeds):
     2,048 workgroups of 256 threads stride over the coordinates, four per
-    thread, so each walks two grid strides or more; d = 4k + 3 takes the
-    scalar-load instantiation."""
+    thread, so each walks two grid strides or more; with d = 4k + 3 the rows
+    start off 16-byte boundaries and the last chunk overlaps the one before."""
     wl = synth.WORKLOADS[1]
     s = oracle.assign(wl.K, wl.r)
     g, _ = synth.generate(wl, s, d=d)
@@ -165,20 +169,26 @@ def test_steady_state_fused_mean(d):
 
 
 def test_steady_state_generic_single_pass_r5():
-    """r = 5 (K = 9, 126 files): the load-then-select single pass with
-    64-column tiles, two workgroups per CU (a grid of 512), three or more
-    tiles each."""
-    K, r, q = 9, 5, 2
-    sp, _ = aspis.plan(K, r, 4096)
-    assert sp["kernel"] == "fused" and sp["tile_cols"] == 64, sp
-    d = _steady_d(64, 2 * CUS, 20)
-    wl = synth.Workload(0, K, r, q, d, synth.DIST_NORMAL, "weak", "reversed", "fixed")
+    """r = 5 on full keys (K = 10, 252 files): the load-then-select single pass
+    with 64-column tiles, three or more for each workgroup.  It runs when asked for and,
+    on tied data, when the device's tie probe picks it among the launched
+    candidates."""
+    K, r, q = 10, 5, 2
+    sp, _ = aspis.plan(K, r, 4096, "file", aspis.FLAG_FULL_KEYS)
+    assert sp["kernel"] == "fused" and sp["stream_threads"] == 0 and sp["tile_cols"] == 64, sp
+    assert sp["lds_bytes"] > 80 * 1024   # one workgroup per CU
+    d = _steady_d(64, CUS, 20)
     s = oracle.assign(K, r)
-    g, _ = synth.generate(wl, s, d=d)
-    print(f"r=5 single pass: d={d}", flush=True)
-    got = _run(g, K, r, q, "median")
-    _compare(got, _oracle(g, K, r, q, "median"), K, "median")
-    assert got["stats"]["fused"] == 1
+    for dist, flags in ((synth.DIST_NORMAL, aspis.FLAG_FULL_KEYS), (synth.DIST_TIED, 0)):
+        wl = synth.Workload(0, K, r, q, d, dist, "weak", "reversed", "fixed")
+        g, _ = synth.generate(wl, s, d=d)
+        print(f"r=5 generic single pass: d={d} dist={dist} flags={flags}", flush=True)
+        got = _run(g, K, r, q, "median", flags)
+        _compare(got, _oracle(g, K, r, q, "median"), K, "median")
+        st = got["stats"]
+        assert st["fused"] == 1 and (st["tile_cols"], st["half_keys"]) == (64, 0), st
+        if not flags:
+            assert st["tie_rows"] >= 16, st
 
 
 @pytest.mark.parametrize("K,r,q,d,mode", [
