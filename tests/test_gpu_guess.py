@@ -79,15 +79,16 @@ def test_row_table_of_many_workers(K, r):
 
 
 @pytest.mark.parametrize("d", [128 * 256, 128 * 256 + 4, 128 * 256 + 133])
-def test_few_files_either_side_of_the_half_key_line(d):
-    """35 files take half-key tiles from 32,769 coordinates on."""
-    K, r, q = 7, 3, 2
+@pytest.mark.parametrize("K,layout", [(K, lay) for K in (7, 9, 10) for lay in ("file", "worker")])
+def test_few_files_either_side_of_the_half_key_line(K, layout, d):
+    """35, 84 and 120 files take half-key tiles from 32,769 coordinates on."""
+    r, q = 3, 2
     wl = synth.Workload(0, K, r, q, d, synth.DIST_NORMAL, "weak", "reversed", "fixed")
     g, _ = synth.generate(wl, oracle.assign(K, r), d=d)
-    got = _run(g, K, r, q)
+    got = _run(g, K, r, q, layout=layout)
     _compare(got, _oracle(g, K, r, q, "median"), K, "median")
     assert (got["stats"]["tile_cols"], got["stats"]["half_keys"]) == \
         ((128, 1) if d > 128 * 256 else (64, 0))
-    full = _run(g, K, r, q, flags=aspis.FLAG_FULL_KEYS)
+    full = _run(g, K, r, q, flags=aspis.FLAG_FULL_KEYS, layout=layout)
     assert full["stats"]["half_keys"] == 0
     assert (full["out"] == got["out"]).all()

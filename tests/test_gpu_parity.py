@@ -44,8 +44,8 @@ def _check(g, K, r, q, mode, path, nan_equal=False, flags=0):
     return got, ref
 
 
-# d per workload: odd (scalar loads), and a multiple of 4 whose last tile is
-# ragged (vector loads, the warp-specialised single pass)
+# d per workload: odd (rows off 16-byte boundaries), and a multiple of 4 whose
+# last tile is ragged
 _D = {1: 4099, 2: 2053, 3: 1543, 4: 523, 5: 389}
 _D4 = {1: 4100, 2: 2056, 3: 1548, 4: 524, 5: 392}
 
@@ -456,8 +456,8 @@ def test_no_files_leaves_out_untouched():
 @pytest.mark.parametrize("d", [1, 2, 3, 4, 5])
 def test_tiny_d(idx, d):
     """Vectors shorter than one 16-byte chunk or one tile: d = 1..3 (scalar
-    loads), d = 4 (the warp-specialised kernel on a single tile almost all
-    past the end), d = 5; every path."""
+    loads, the generic kernels), d = 4 (the warp-specialised kernel on a single
+    tile almost all past the end), d = 5 (two chunks that overlap); every path."""
     wl = synth.WORKLOADS[idx]
     s = oracle.assign(wl.K, wl.r)
     g, _ = synth.generate(wl, s, d=d)
@@ -466,8 +466,9 @@ def test_tiny_d(idx, d):
     _check(g, wl.K, wl.r, wl.q, "paper", "fused")
 
 
-def test_unaligned_rows_use_scalar_loads():
-    """d not a multiple of 4 and a tensor that starts 4 bytes into a block."""
+def test_unaligned_rows_and_tensor():
+    """d not a multiple of 4 and a tensor that starts 4 bytes into a block:
+    the 16-byte loads start at any 4-byte boundary."""
     import torch
     wl = synth.WORKLOADS[1]
     s = oracle.assign(wl.K, wl.r)

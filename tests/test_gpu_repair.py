@@ -185,8 +185,8 @@ def test_repair_kept_files_differ():
 
 
 def test_repair_unaligned_rows():
-    """d not a multiple of 4: the generic single pass and the LDS-tile
-    median (scalar loads) repair the tiles of the deviating coordinates."""
+    """d not a multiple of 4: the rows' last chunks overlap the ones before,
+    in the single pass and in the median that repairs its tiles."""
     wl, kw = _late_workload(15, 3, 4)
     K, r, q = wl.K, wl.r, wl.q
     d = 32768 + 40000 + 3
@@ -196,6 +196,24 @@ def test_repair_unaligned_rows():
     print(f"unaligned rows: d={d}", flush=True)
     got, _, want = _repaired(g, K, r, q)
     assert want == len({c // got["stats"]["tile_cols"] for c in coords}) == 3
+
+
+def test_repair_generic_kernels():
+    """4,495 files, more than the warp-specialised kernels hold: the
+    load-then-select single pass on 4-column tiles, the guess from the host,
+    and the LDS-tile median on the deviating tiles of 8 columns."""
+    wl, kw = _late_workload(31, 3, 4)
+    K, r, q = wl.K, wl.r, wl.q
+    d = 4096 + 3003
+    sp, med = aspis.plan(K, r, d)
+    assert (sp["kernel"], med["kernel"], med["tile_cols"]) == ("fused", "median_tile", 8)
+    s = oracle.assign(K, r)
+    coords = _coords(wl.f, d)
+    g = _attack_only_at(wl, s, d, coords, **kw)
+    print(f"generic kernels: d={d}", flush=True)
+    got, _, want = _repaired(g, K, r, q)
+    assert got["stats"]["tile_cols"] == 8
+    assert want == len({c // 8 for c in coords})
 
 
 def test_repair_five_replicas():
@@ -256,7 +274,7 @@ def test_repair_mean(mode):
 def test_drawn_probe_just_past_its_length(extra):
     """A vector a few coordinates longer than the probe (32,768 coordinates at
     455 files): the 32 blocks are drawn from the few positions there are
-    (also with d odd, the scalar-load paths), and the result is the oracle's,
+    (also with d odd), and the result is the oracle's,
     with every worker honest and with the attack everywhere."""
     wl = synth.WORKLOADS[3]
     K, r, q = wl.K, wl.r, wl.q
