@@ -41,6 +41,19 @@ constexpr int ws_ring() {
     return SW <= 24 && SW % 3 == 0 ? 3 : SW % 2 == 0 ? 2 : 1;
 }
 
+// Sweeps of loads that stay in flight over the hand-over between two tiles: the
+// whole ring, but one sweep for 64-column full-key tiles of 16 sweeps.  There 64
+// key registers, the put's addresses and two sweeps of loads spill 21 registers:
+// 455 files, d = 11.2M, 10.05 ms, 9.76 with one sweep carried (3 spills), 9.84
+// with none and 10.22 with a ring of one; d = 2.5M + 1, 3.02 -> 2.51, d = 3M
+// through a row table 2.84 -> 2.74.
+// Narrower full-key tiles of 16 sweeps spill 11 to 13 and keep the ring: 2,300
+// files on 8 columns, d = 0.3M, 2.37 ms, 2.47 with one carried.
+template <int T, int R, int SW, bool HALF>
+constexpr int ws_carry() {
+    return R == 3 && !HALF && T == 64 && SW == 16 ? 1 : ws_ring<R, SW, HALF>();
+}
+
 // Row tables in LDS hold byte offsets (8 bytes a row: a row's address is one
 // addition then, no 64-bit product a load) in half-key tiles of 32 columns
 // or more, row numbers (4 bytes) where that room would cost tile width.
@@ -71,7 +84,8 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
     constexpr int CPR = T / 4;           // float4 chunks per row segment
     constexpr int RPI = FILL / CPR;      // rows per sweep of the streaming role
     constexpr int B = ws_ring<R, SW, HALF>();   // sweeps of loads in flight
-    static_assert(SW % B == 0, "the ring divides the tile");
+    constexpr int CARRY = ws_carry<T, R, SW, HALF>();   // of them over a hand-over
+    static_assert(SW % B == 0 && CARRY <= B, "the ring divides the tile");
     // key registers per sweep: 4 keys, or (HALF) 4 high halves packed in 2;
     // a half-key tile's rows are the files themselves
     constexpr int KW = HALF ? 2 : 4;
@@ -243,16 +257,20 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
             }
         };
         Chunks c[B];
-        // tile t from the ring, refilled with t's later sweeps and then with
-        // the first ones of tile tn
-        auto stream_tile = [&](int64_t t, int64_t tn) __attribute__((always_inline)) {
+        // tile t from the ring, which holds its sweeps [0, held); refilled with
+        // t's later sweeps and then with the first CARRY ones of tile tn
+        auto stream_tile = [&](int64_t t, int64_t tn, int held) __attribute__((always_inline)) {
             const float *base = tile_base(t);
+#pragma unroll
+            for (int x = 0; x < B; ++x)
+                if (x >= held) c[x] = load_sweep(base, x);
 #pragma unroll
             for (int x = 0; x < SW; ++x) {
                 proc_sweep(x, c[x % B]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (x == SW - B) base = tile_base(tn);
-                if (x + B < SW || tn < ntiles) c[x % B] = load_sweep(base, (x + B) % SW);
+                if (x + B < SW || (x + B - SW < CARRY && tn < ntiles))
+                    c[x % B] = load_sweep(base, (x + B) % SW);
                 // no scheduling across sweeps, which would hold more loads in
                 // registers than fit
                 __builtin_amdgcn_sched_barrier(0);
@@ -277,15 +295,13 @@ fused_ws_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of,
         };
         int64_t t = first_tile(!NT);
         if (t < ntiles) {
-#pragma unroll
-            for (int x = 0; x < B; ++x) c[x] = load_sweep(tile_base(t), x);
-            stream_tile(t, t + gridDim.x);
+            stream_tile(t, t + gridDim.x, 0);
             put_tile();
         }
         __syncthreads();
         for (; t < ntiles; t += gridDim.x) {
             const int64_t tn = t + gridDim.x;
-            if (tn < ntiles) stream_tile(tn, tn + gridDim.x);
+            if (tn < ntiles) stream_tile(tn, tn + gridDim.x, CARRY);
             __syncthreads();
             if (tn < ntiles) put_tile();
             __syncthreads();

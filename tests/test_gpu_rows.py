@@ -24,6 +24,7 @@ pytestmark = pytest.mark.gpu
     (15, 3, 4, "worker", 0, CUS + 3, 2),
     (15, 3, 4, "file", aspis.FLAG_TWO_PASS, CUS + 3, 3),
     (15, 3, 4, "file", aspis.FLAG_FULL_KEYS, CUS + 3, 5),
+    (15, 3, 4, "worker", aspis.FLAG_FULL_KEYS, CUS + 3, 6),
     (11, 5, 3, "file", 0, CUS + 1, 1),
     (21, 3, 5, "file", 0, 70, 33),
     (25, 3, 6, "worker", 0, 40, 3),
