@@ -28,6 +28,7 @@ pytestmark = pytest.mark.gpu
     (11, 5, 3, "file", 0, CUS + 1, 1),
     (21, 3, 5, "file", 0, 70, 33),
     (25, 3, 6, "worker", 0, 40, 3),
+    (24, 3, 5, "worker", 0, 130, 3),
     (7, 3, 2, "file", 0, 3 * CUS, 3),
     (10, 7, 2, "file", 0, 20, 1),
     (15, 3, 4, "file", 0, 0, 5),
