@@ -1421,13 +1421,13 @@ int round_sweeps(int64_t sw, bool half, int T, int fill) {
 // 64 of 28 0.88 ms; 1,716 files, d = 0.1M, 32 of 28 0.87, 16 of 16 0.91 ms.
 template <typename LdsFn>
 WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r = 3,
-                 int64_t min_rows = kHalfMinRows) {
+                 int64_t min_rows = kHalfMinRows, bool wide = true) {
     WsPlan p;
     if (f < min_rows || f > kHalfMaxRows) return p;
     for (int T : {128, 64, 32, 16}) {
         if (T <= narrower) break;
         for (int fill : {kWsFill, kWsFillWide}) {
-            if (fill == kWsFillWide && ((ind && !rtg) || T == 128 || T == 16 || r != 3)) continue;
+            if (fill == kWsFillWide && (!wide || (ind && !rtg) || T == 128 || T == 16 || r != 3)) continue;
             if (rtg && fill != kWsFillWide) continue;
             const int64_t rpi = half_rpi(T, fill);
             const int64_t sw = (f + rpi - 1) / rpi;
@@ -1450,8 +1450,8 @@ WsPlan half_plan(int64_t f, int narrower, bool ind, bool rtg, LdsFn &&lds, int r
 }
 
 // LDS of the warp-specialised median: histograms, key tile, row list.
-int64_t mws_lds_bytes(int64_t f, int T, int sweeps, bool half, int fill) {
-    return half ? half_tile_words(sweeps, fill) * 4 + f * (ws_offsets(T, half) ? 8 : 4)
+int64_t mws_lds_bytes(int64_t f, int T, int sweeps, bool half) {
+    return half ? half_tile_words(sweeps, kWsFill) * 4 + f * (ws_offsets(T, half) ? 8 : 4)
                 : (hist_words(T) + f * (int64_t)T) * 4 + f * 4;
 }
 
@@ -1459,7 +1459,7 @@ WsPlan mws_plan(int64_t f, bool vec, bool full_keys = false) {
     WsPlan p;
     if (!vec) return p;
     for (int T : {64, 32, 16, 8}) {
-        if (mws_lds_bytes(f, T, 0, false, kWsFill) > kLdsBytes) continue;
+        if (mws_lds_bytes(f, T, 0, false) > kLdsBytes) continue;
         const int64_t rpi = kWsFill / (T / 4);
         const int64_t sw = (f + rpi - 1) / rpi;
         // 16 sweeps fit the registers only next to the 64-column selection
@@ -1469,9 +1469,15 @@ WsPlan mws_plan(int64_t f, bool vec, bool full_keys = false) {
         break;
     }
     if (full_keys) return p;
-    const WsPlan h = half_plan(f, p.T, false, false, [&](int T, int sweeps, int fill) {
-        return mws_lds_bytes(f, T, sweeps, true, fill);
-    });
+    // The even split only: the wide one would give 1,140 files 64 columns instead
+    // of 32, but halves the selecting waves, which bound the median (the two-pass
+    // step at d = 1M 3.43 against 3.24 ms, at d = 200,003 0.82 against 0.76).  The
+    // single pass, bound by its stream, gains from it (d = 200,003 0.61 against
+    // 0.65 ms, d = 3M 6.40 against 6.50).
+    const WsPlan h = half_plan(
+        f, p.T, false, false,
+        [&](int T, int sweeps, int) { return mws_lds_bytes(f, T, sweeps, true); }, 3, kHalfMinRows,
+        false);
     return h.T != 0 ? h : p;
 }
 
@@ -1561,7 +1567,7 @@ bool plan_median(int64_t f, bool vec, KernelPlan *out, bool full_keys) {
     const WsPlan p = mws_plan(f, vec, full_keys);
     if (p.T != 0) {
         *out = ws_kernel_plan(median_ws_fn(p) ? kKernelMedianWs : kKernelUnbuilt, p,
-                              mws_lds_bytes(f, p.T, p.sweeps, p.half, p.fill), 0);
+                              mws_lds_bytes(f, p.T, p.sweeps, p.half), 0);
         return out->kind == kKernelMedianWs;
     }
     KernelPlan k;

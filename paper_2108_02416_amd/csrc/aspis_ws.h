@@ -389,12 +389,13 @@ constexpr int mws_ring() {
     return 1;
 }
 
-template <int T, int SW, bool HALF, int FILL>
+template <int T, int SW, bool HALF>
 __global__ void __launch_bounds__(kWsThreads)
 median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restrict__ rows,
                  const int32_t *__restrict__ n_sel, int64_t ntiles, bool by_xcd,
                  float *__restrict__ out, TileMask mask) {
     extern __shared__ __align__(16) uint32_t smem[];
+    constexpr int FILL = kWsFill;        // threads of the streaming role
     constexpr int G = (kWsThreads - FILL) / T;   // selection lanes per column
     constexpr int CPR = T / 4;           // float4 chunks per row segment
     constexpr int RPI = FILL / CPR;      // rows per sweep of the streaming role

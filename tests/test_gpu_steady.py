@@ -98,6 +98,10 @@ CASES = [
      dict(kernel="fused_ws", tile_cols=64, sweeps=4, half_keys=0, stream_threads=512), 20),
     ("headline two-pass median_ws<128,30,half>", 3, "file", _WS,
      dict(kernel="median_ws", tile_cols=128, sweeps=30), 36),
+    ("K=20 fused_ws<64,3,24,wide>", (20, 3, 4, "optimal", "reversed"), "file", 0,
+     dict(kernel="fused_ws", tile_cols=64, sweeps=24, stream_threads=768), 20),
+    ("K=20 two-pass median_ws<32,20,half>", (20, 3, 4, "optimal", "reversed"), "file", _WS,
+     dict(kernel="median_ws", tile_cols=32, sweeps=20, stream_threads=512), 12),
     ("K=25 two-pass median_ws<16,24,half>", 5, "file", _WS,
      dict(kernel="median_ws", tile_cols=16, sweeps=24), 8),
 ]

@@ -119,6 +119,14 @@ def test_median_plans(K, r, kernel):
     assert med["kernel"] == kernel, med
 
 
+def test_median_keeps_its_selecting_waves():
+    """1,140 files: the single pass takes 64 columns with 12 streaming and 4
+    selecting waves, the median, bound by its selection, 32 with 8 and 8."""
+    sp, med = aspis.plan(20, 3, 4096)
+    assert (sp["tile_cols"], sp["stream_threads"]) == (64, 768), sp
+    assert (med["tile_cols"], med["sweeps"], med["stream_threads"]) == (32, 20, 512), med
+
+
 @pytest.mark.parametrize("K,kernel,T", [(15, "fused_ws", 64), (21, "fused_ws", 16),
                                         (25, "fused_ws", 8)])
 def test_full_key_plans_of_the_workloads(K, kernel, T):
