@@ -630,10 +630,13 @@ fused_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, in
 // 0.20 ms (linear reads 0.77 and 0.17); 462 files at r = 5, d = 4M 6.83 -> 5.82
 // ms; 120 files at r = 7, d = 0.4M 0.55 -> 0.23 ms, all against bursts of
 // loads waited for together.  At r = 3 those bursts (62 registers, 8
-// workgroups per CU) stay where the vector gives each CU more than 4 and at
-// most 8 workgroups, which then run as one full round: 455 files, d = 2M, 1.67
-// against 1.72 ms.
-constexpr int64_t kMeanBurstMin = 4, kMeanBurstMax = 8;   // workgroups per CU
+// workgroups per CU) stay where the vector gives each CU at least 5 and at
+// most 8 workgroups, which then run as one full round.  Kernel times of bursts
+// and ring at 35, 120, 455 and 1,140 files, both layouts: d = 1.31M to 2.09M (5
+// to 8 workgroups) bursts 1 to 12 % faster (455 files, d = 1.6M, 1.29 against
+// 1.41 ms); d = 1.06M and 1,234,567 (4 to 5) ring 1 to 6 % faster (1,140 files, d =
+// 1.06M, 2.45 against 2.61 ms), d = 1.15M within 2 % either way.
+constexpr int64_t kMeanBurstMin = 5, kMeanBurstMax = 8;   // workgroups per CU
 
 // IND: rows through the table row_of.  SHORT: rows of fewer than four
 // coordinates.
@@ -1772,7 +1775,7 @@ hipError_t launch_fused_mean_if(const float *g, const int32_t *row_of, int64_t f
     const int64_t blocks = (nq + kBlock - 1) / kBlock;
     switch (r) {
     case 3:
-        if (blocks > kMeanBurstMin * num_cus() && blocks <= kMeanBurstMax * num_cus()) {
+        if (blocks >= kMeanBurstMin * num_cus() && blocks <= kMeanBurstMax * num_cus()) {
             fused_mean_burst_kernel<3><<<grid, kBlock, lds, s>>>(g, row_of, f, d, ws.sel, ws.pos,
                                                                  ws.n_sel, pair_diff, out, gate);
         } else {

@@ -60,8 +60,8 @@ def test_any_row_length(K, r, q, layout, flags, tiles, extra):
 @pytest.mark.parametrize("mode,K,r,q,d", [
     ("mean", 10, 3, 2, 4 * 256 * 11 + 3),
     ("paper", 10, 3, 2, 4 * 256 * 11 + 3),
-    ("mean", 5, 3, 1, 1024 * 4 * CUS),          # either side of the line to bursts
-    ("mean", 5, 3, 1, 1024 * 4 * CUS + 1),
+    ("mean", 5, 3, 1, 1024 * (5 * CUS - 1)),    # either side of the line to bursts
+    ("mean", 5, 3, 1, 1024 * (5 * CUS - 1) + 1),
     ("mean", 5, 3, 1, 1024 * 8 * CUS + 5),      # and back, two rounds of the grid
     ("mean", 8, 5, 2, 1024 * 3 + 2),
     ("mean", 8, 7, 2, 1024 * 3 + 1),
