@@ -6,57 +6,46 @@ namespace aspis {
 
 FusedWsFn fused_ws_r3_table_fn(const WsPlan &p) {
     if (p.r != 3) return nullptr;
-    if (p.rtg) {
-        // row table read from global memory: wide split, half keys
-        if (!p.half || p.fill != kWsFillWide) return nullptr;
-#define W(TT, SWW) \
-    case ws_key(TT, SWW, true): return ASPIS_NT(fused_ws_kernel, TT, 3, SWW, true, true, kWsFillWide, true);
-        switch (ws_key(p.T, p.sweeps, p.half)) {
-            W(64, 24)
-            W(32, 24)
-        default: return nullptr;
-        }
-#undef W
-    }
-    // row table in LDS: even split (no 36-sweep tile leaves room for it)
+    // row table read from global memory (wide split, half keys): 2,024 and
+    // 2,300 files
+    if (p.rtg)
+        return p.half && p.fill == kWsFillWide && p.T == 32 && p.sweeps == 24
+                   ? ASPIS_NT(fused_ws_kernel, 32, 3, 24, true, true, kWsFillWide, true)
+                   : nullptr;
+    // row table in LDS: even split, the plans of f = C(K,3), K = 3 to 28
     if (p.fill != kWsFill) return nullptr;
 #define ASPIS_FWS(TT, SWW, HH) \
     case ws_key(TT, SWW, HH): return ASPIS_NT(fused_ws_kernel, TT, 3, SWW, true, HH, kWsFill, false);
 #define ASPIS_FWS_NARROW(TT, SWW, HH) \
     case ws_key(TT, SWW, HH): return &fused_ws_kernel<TT, 3, SWW, true, HH, kWsFill, false, false>;
     switch (ws_key(p.T, p.sweeps, p.half)) {
-#define ASPIS_FWS_HALF(TT)    \
-    ASPIS_FWS(TT, 20, true)   \
-    ASPIS_FWS(TT, 24, true)   \
-    ASPIS_FWS(TT, 28, true)   \
-    ASPIS_FWS(TT, 32, true)
         ASPIS_FWS(64, 2, false)
         ASPIS_FWS(64, 4, false)
         ASPIS_FWS(64, 8, false)
         ASPIS_FWS(64, 12, false)
         ASPIS_FWS(64, 16, false)
-        ASPIS_FWS(32, 8, false)
         ASPIS_FWS(32, 12, false)
         ASPIS_FWS(32, 16, false)
-        ASPIS_FWS_NARROW(16, 8, false)
         ASPIS_FWS_NARROW(16, 12, false)
         ASPIS_FWS_NARROW(16, 16, false)
         ASPIS_FWS_NARROW(8, 8, false)
         ASPIS_FWS_NARROW(8, 12, false)
-        ASPIS_FWS_NARROW(8, 16, false)
         ASPIS_FWS(128, 4, true)
         ASPIS_FWS(128, 8, true)
         ASPIS_FWS(128, 12, true)
         ASPIS_FWS(128, 16, true)
+        ASPIS_FWS(128, 20, true)
+        ASPIS_FWS(128, 24, true)
         ASPIS_FWS(128, 30, true)
-        ASPIS_FWS_HALF(128)
-        ASPIS_FWS_HALF(64)
-        ASPIS_FWS_HALF(32)
-        ASPIS_FWS_NARROW(16, 16, true)
+        ASPIS_FWS(64, 20, true)
+        ASPIS_FWS(64, 24, true)
+        ASPIS_FWS(64, 28, true)
+        ASPIS_FWS(64, 32, true)
+        ASPIS_FWS(32, 20, true)
+        ASPIS_FWS(32, 24, true)
+        ASPIS_FWS(32, 28, true)
         ASPIS_FWS_NARROW(16, 24, true)
         ASPIS_FWS_NARROW(16, 28, true)
-        ASPIS_FWS_NARROW(16, 32, true)
-#undef ASPIS_FWS_HALF
     default: return nullptr;
     }
 #undef ASPIS_FWS
