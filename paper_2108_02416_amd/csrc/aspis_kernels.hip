@@ -30,14 +30,14 @@
 //                      pass (two-pass path, and the rerun after a wrong guess).
 //   fused_ws_kernel    agreement + median in one read, warp-specialised: some
 //                      waves stream the next tile while the others select on
-//                      the current one (the headline path, r = 3).  For
-//                      hundreds of rows or more the LDS tile keeps only the
-//                      high 16 bits of each key (select_half_tile), which
-//                      doubles the tile width; the low halves of the rows
+//                      the current one (the headline path).  Where it gives a
+//                      wider tile, the LDS tile keeps only the high 16 bits of
+//                      each key (select_half_tile); the low halves of the rows
 //                      that tie with the median's high half are read back.
 //   fused_kernel       agreement + median in one read, load then select per
-//                      tile, where no warp-specialised plan exists (r = 7,
-//                      small r = 5, rows of fewer than four coordinates).
+//                      tile, where no warp-specialised plan exists (rows of
+//                      fewer than four coordinates, more files than its tiles
+//                      hold, full keys of more than 128 files at r = 5 and 7).
 //   fused_mean_kernel  agreement + Case 1 mean in one read.
 //   mean_kernel        Algorithm 1 Case 1 mean, fp64 accumulation in file
 //                      order.
@@ -1048,8 +1048,8 @@ tie_probe_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of
 // The whole probe in one launch: workgroups [0, f*split) compare file b % f
 // over every split-th block of the probe (from block b / f on) into part[b],
 // the rest run the tie probe.  A file alone leaves a small cluster's probe to
-// a few workgroups: K = 7, d = 0.1M, 29 us
-// without the split, 18 us with it and the guess (guess_kernel).
+// a few workgroups: K = 7, d = 0.1M, 29 us without the split, 13 us with it and
+// the guess (guess_kernel).
 template <int R>
 __global__ void __launch_bounds__(kBlock)
 probe_kernel(const float *__restrict__ g, const int32_t *__restrict__ row_of, int64_t f, int split,
@@ -1378,7 +1378,8 @@ namespace {
 
 constexpr int64_t kHalfMinRows = 128;
 // The single pass at r = 3 takes half-key tiles of 128 columns from 24 files
-// on where the vector gives every CU one (256 CUs): their selection costs a
+// on where the vector gives every CU of an MI355X one (256; a constant, not the
+// device's count, so that aspis_plan needs no device): their selection costs a
 // quarter of the full keys' a column, K = 7 (35 files) d = 1M 133 against
 // 203 us, d = 0.1M 26 against 32 us, K = 10 (120 files) d = 1M 237 against 336 us;
 // shorter vectors spread over more CUs in tiles of 64 columns (K = 7, d =
@@ -1386,12 +1387,11 @@ constexpr int64_t kHalfMinRows = 128;
 constexpr int64_t kHalfFewRows = 24, kHalfFewCols = 128 * 256;
 constexpr int64_t kHalfMaxRows = 60000;   // row numbers (with padding) fit 16 bits
 
-// Most sweeps a half-key plan may take: 32, and 36 for the 32-column tile
-// with the even split.  There the streaming role spills 30 registers, and
-// still the 8 selecting waves (16 lanes a column) beat the wide split's 4:
-// 2,300 files, d = 2M, 9.14-9.58 against 11.36-11.40 ms (one process and
-// allocation).  Not with a row table: reading it as well, the streaming
-// role spills 88 registers (15.9 against 12.1 ms with the wide split).
+// Most sweeps a half-key plan may take: 32, and 36 for the 32-column tile with
+// the even split (2,300 files file-major; 2 to 4 spills).  Against the wide
+// split: kernel 8.97 ms either way at d = 2M, 2.69 against 2.48 ms at d = 0.6M,
+// where the wide one would be better.  Not with a row table, which 36 sweeps
+// leave to global memory: 9.29 against 8.98 ms, and 2.90 against 2.61 ms.
 constexpr int max_half_sweeps(int T, int fill) { return T == 32 && fill == kWsFill ? 36 : 32; }
 
 // Sweep counts built for each plan.  A half-key tile is padded to them (the
@@ -1409,15 +1409,12 @@ int round_sweeps(int64_t sw, bool half, int T, int fill) {
 }
 
 // The half-key plan wider than `narrower` columns, or none; lds(T, fill)
-// gives the kernel's LDS bytes.  The wide split is built for 64 and 32
-// columns only.  With a row table (ind) the 128-column tile spills 15
-// registers of the streaming role next to 30 sweeps of keys, and still
-// beats the 64-column full-key tile (10.9 against 11.6 ms at 455 files,
-// d = 11.2M, one process and allocation).  A row table staged in LDS rules
-// out the wide split; one read from global memory (rtg) takes the wide
-// split only: with the even split the streaming role would hold the
-// table's addresses next to its keys (the kernels built for a global
-// table are wide-split ones).
+// gives the kernel's LDS bytes.  The wide split serves 64 columns file-major
+// (1,140 files) and 32 with the row table in global memory (2,024 and 2,300).
+// It is not built for a row table in LDS (455 files take 128 columns of the even
+// split with one: d = 3M 2.61 ms a step, 2.73 on the 64-column full-key tile);
+// a table in global memory (rtg) takes it only: 2,024 files, d = 0.6M, 2.47 ms
+// a step, 2.73 with the even split's 32 sweeps.
 // r = 7: at most 16 sweeps of 64 or 128 columns, 28 of 32 or 16 (seven chunks
 // a sweep; the keys of more sweeps spill): 330 files, d = 0.4M, 64 columns of
 // 12 sweeps 0.58 ms, 128 of 24 0.66 ms; 792 files, d = 0.2M, 32 of 16 0.71,

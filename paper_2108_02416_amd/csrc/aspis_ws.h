@@ -522,14 +522,13 @@ median_ws_kernel(const float *__restrict__ g, int64_t d, const int32_t *__restri
 
 // Warp-specialised plans.  Full keys: the widest tile (8..64 columns) whose
 // key block fits in LDS and whose rows fit the streaming role's registers
-// (at most 16 sweeps of 4 key registers).  Half keys, for many rows: a wider
-// tile (16..128 columns) with up to 32 sweeps of 2 key registers; taken
-// only when it is wider than the full-key tile, since below kHalfMinRows
-// rows a tile is streamed too quickly to hide the reads of the low halves.
-// Half keys try the even split of streaming and selecting waves first, then
-// 12 streaming waves and 4 selecting ones (kWsFillWide): 1.5x the rows per
-// sweep, so that thousands of rows fit the registers of a 32- or 64-column
-// tile.
+// (at most 16 sweeps of 4 key registers).  Half keys: a wider tile (16..128
+// columns) with up to 36 sweeps of 2 key registers, taken only when it is wider
+// than the full-key tile, from kHalfMinRows rows on (the single pass at r = 3 in
+// long vectors: from kHalfFewRows).  The single pass's half keys try the even
+// split of streaming and selecting waves first, then 12 streaming waves and 4
+// selecting ones (kWsFillWide): 1.5x the rows per sweep, so that thousands of
+// rows fit the registers of a 32- or 64-column tile.
 struct WsPlan {
     int r = 3;
     int T = 0;
