@@ -197,11 +197,14 @@ constexpr int kKeysHalf = 0, kKeysFull = 1, kKeysProbe = 2;
 // about x times the fully tied case, and the mean, unlike a typical
 // coordinate's count, sees ties that cover less than half of the coordinates.
 // One line for every shape; where half and full keys cross, by the step's time
-// with t files tied in every column: t = 2 at 455 files, 5 at 286, 8 at 120, not
-// up to 15 at 35 (whose few files fit any tile), 50 to 70 at 1,330, past 100 at
-// 2,300 (full keys: 8 columns) and at 462 files of r = 5 (no warp-specialised
-// full-key tile).  The farthest off the line: 455 files, t = 15, d = 1.5M, half
-// 1.93, full 1.47 ms; 2,300 files, t = 20, d = 0.2M, half 1.08, full 1.75 ms.
+// with t files tied in every column, drawn per column: t = 2 at 455 files, 5 at
+// 286, 8 at 120, not up to 15 at 35 (whose few files fit any tile), 50 to 70 at
+// 1,330, past 100 at 2,300 (full keys: 8 columns) and at 462 files of r = 5 (no
+// warp-specialised full-key tile).  The farthest off the line: 455 files, t =
+// 15, d = 1.5M, half 1.93, full 1.47 ms; 2,300 files, t = 20, d = 0.2M, half
+// 1.08, full 1.75 ms.  Ties of the same files in every column are read back in
+// whole lines and cost less: 28 files of colluders sending the honest mean, 455
+// files, d = 11.2M, half 9.7, full 10.0 to 10.3 ms.
 constexpr uint32_t kTieFullKeys = 16;
 
 // A main kernel's condition: it runs when *path is want (or without a path).
